@@ -172,18 +172,18 @@ typedef struct {
  *     combine of tile partials that chunks spanning several tiles need.
  *     Either may be given alone, so a run of calls can be timed as a
  *     whole.
- *   grid_blocks: workgroups of the streaming kernel; 0 chooses one per tile.
- *     Results do not depend on it.
+ *   grid_blocks: workgroups of the streaming kernel; 0 chooses one per tile
+ *     (or per few small tiles).  Results do not depend on it.
  *   flags: C3_OPT_PLAN_STAGED -- the workspace still holds the plan that a
  *     previous c3_signature[_ex] call staged there with identical ptrs,
  *     metas, T, R, chunk_bytes and tile_bytes, and the caller has not written
  *     to the workspace since; staging is skipped.  The caller is responsible
  *     for that promise: a stale plan reads stale pointers.
- *   tile_bytes: bytes one workgroup folds into one partial; 0 chooses the
- *     default (the largest power of two up to 256 KiB dividing chunk_bytes).
- *     Must be a power-of-two multiple of 1024 dividing chunk_bytes
- *     (checked); the fp64 sums may differ in the last bits between tile
- *     sizes, everything else is identical. */
+ *   tile_bytes: bytes folded into one partial; 0 chooses the default (the
+ *     chunk in as few equal tiles of at most 256 KiB as it takes, whole KiB
+ *     each).  Any other value must be a power-of-two multiple of 1024
+ *     dividing chunk_bytes (checked); the fp64 sums may differ in the last
+ *     bits between tile sizes, everything else is identical. */
 typedef struct {
     c3_event_t ev_kernel_begin;
     c3_event_t ev_kernel_end;

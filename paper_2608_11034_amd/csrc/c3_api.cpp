@@ -64,11 +64,13 @@ int64_t tensor_nbytes(const c3_tensor_meta_t& m) {
     return (int64_t)n;
 }
 
-// Largest power-of-two multiple of 1024 dividing chunk_bytes, capped.
+// Default tile: the chunk in as few equal tiles of at most kDefaultTileMax
+// as it takes, rounded up to whole KiB (the chunk's last tile is shorter
+// where they do not divide it).  A power of two dividing the chunk, the rule
+// before, gave a chunk of 100 KiB tiles of 4 KiB.
 uint64_t default_tile(uint64_t chunk_bytes) {
-    uint64_t t = 1024;
-    while (t * 2 <= c3::kDefaultTileMax && chunk_bytes % (t * 2) == 0) t *= 2;
-    return t;
+    const uint64_t n = (chunk_bytes + c3::kDefaultTileMax - 1) / c3::kDefaultTileMax;
+    return align_up((chunk_bytes + n - 1) / n, 1024);
 }
 
 struct Plan {
@@ -84,10 +86,12 @@ int make_plan(const c3_tensor_meta_t* metas, int T, int R, uint64_t chunk_bytes,
               uint64_t tile_bytes, Plan& p) {
     if (metas == nullptr || T < 1 || R < 1 || R > C3_MAX_PEERS) return C3_E_INVAL;
     if (chunk_bytes == 0 || chunk_bytes % 1024 != 0 || chunk_bytes > (1ull << 40)) return C3_E_INVAL;
-    if (tile_bytes == 0) tile_bytes = default_tile(chunk_bytes);
-    if (tile_bytes < 1024 || (tile_bytes & (tile_bytes - 1)) != 0 || chunk_bytes % tile_bytes != 0 ||
-        tile_bytes > (1ull << 24))
+    if (tile_bytes == 0)
+        tile_bytes = default_tile(chunk_bytes);
+    else if (tile_bytes < 1024 || (tile_bytes & (tile_bytes - 1)) != 0 ||
+             chunk_bytes % tile_bytes != 0 || tile_bytes > (1ull << 24))
         return C3_E_INVAL;
+    const uint64_t tpc = (chunk_bytes + tile_bytes - 1) / tile_bytes;
     p.tile_base.assign(T + 1, 0);
     p.chunk_base.assign(T + 1, 0);
     p.tinfo.resize(T);
@@ -95,7 +99,10 @@ int make_plan(const c3_tensor_meta_t* metas, int T, int R, uint64_t chunk_bytes,
         const int64_t nb = tensor_nbytes(metas[t]);
         if (nb < 0) return C3_E_INVAL;
         const int64_t nc = nb == 0 ? 1 : (int64_t)(((uint64_t)nb + chunk_bytes - 1) / chunk_bytes);
-        const int64_t nt = nb == 0 ? 1 : (int64_t)(((uint64_t)nb + tile_bytes - 1) / tile_bytes);
+        // whole chunks of tpc tiles, then the tiles of the partial one
+        const uint64_t whole = (uint64_t)nb / chunk_bytes, rest = (uint64_t)nb % chunk_bytes;
+        const int64_t nt =
+            nb == 0 ? 1 : (int64_t)(whole * tpc + (rest + tile_bytes - 1) / tile_bytes);
         p.chunk_base[t + 1] = p.chunk_base[t] + nc;
         p.tile_base[t + 1] = p.tile_base[t] + nt;
         TensorInfo& ti = p.tinfo[t];
@@ -128,7 +135,7 @@ int make_plan(const c3_tensor_meta_t* metas, int T, int R, uint64_t chunk_bytes,
     h.tiles_per_replica = p.tile_base[T];
     h.chunk_bytes = chunk_bytes;
     h.tile_bytes = tile_bytes;
-    h.tiles_per_chunk = (uint32_t)(chunk_bytes / tile_bytes);
+    h.tiles_per_chunk = (uint32_t)tpc;
     h.direct = h.tiles_per_chunk == 1 ? 1u : 0u;
     uint64_t off = align_up(sizeof(SigPlan), 256);
     h.off_ptrs = off;

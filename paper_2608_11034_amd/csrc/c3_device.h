@@ -76,6 +76,89 @@ __device__ inline double shfl_f64(double v, int src) {
 
 __device__ inline uint64_t ballot64(bool p) { return __ballot(p); }
 
+// The value of the lane whose index differs in bit M (1, 2, 4 or 8), by DPP
+// moves inside a row of 16: no LDS round trip.
+template <int M>
+__device__ __forceinline__ uint32_t row_xor_u32(uint32_t v) {
+    const int iv = (int)v;
+    if constexpr (M == 1) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0xB1, 0xF, 0xF, false);
+    else if constexpr (M == 2) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0x4E, 0xF, 0xF, false);
+    else if constexpr (M == 4)      // mirror of 8 lanes (^7), then of 4 (^3)
+        return (uint32_t)__builtin_amdgcn_mov_dpp(
+            __builtin_amdgcn_mov_dpp(iv, 0x141, 0xF, 0xF, false), 0x1B, 0xF, 0xF, false);
+    else return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0x128, 0xF, 0xF, false);   // rotate by 8
+}
+template <int M>
+__device__ __forceinline__ uint64_t row_xor_u64(uint64_t v) {
+    return ((uint64_t)row_xor_u32<M>((uint32_t)(v >> 32)) << 32) | row_xor_u32<M>((uint32_t)v);
+}
+
+__device__ __forceinline__ uint64_t bits_of(double v) { return (uint64_t)__double_as_longlong(v); }
+__device__ __forceinline__ uint64_t bits_of(uint64_t v) { return v; }
+__device__ __forceinline__ void from_bits(uint64_t b, double& v) { v = __longlong_as_double((long long)b); }
+__device__ __forceinline__ void from_bits(uint64_t b, uint64_t& v) { v = b; }
+
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// One level of two reductions at once.  fold32(a, b): the lower 32 lanes get
+// a + (a of lane ^ 32), the upper ones the same of b; fold16(a, b): even rows
+// of 16 lanes get a + (a of lane ^ 16), odd rows the same of b.  One swap per
+// 32-bit word instead of a shuffle for each of the two values.
+template <typename V>
+__device__ __forceinline__ V fold32(V a, V b) {
+    const uint64_t x = bits_of(a), y = bits_of(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    V p, q;
+    from_bits(((uint64_t)hi[0] << 32) | lo[0], p);
+    from_bits(((uint64_t)hi[1] << 32) | lo[1], q);
+    return p + q;
+}
+template <typename V>
+__device__ __forceinline__ V fold16(V a, V b) {
+    const uint64_t x = bits_of(a), y = bits_of(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    V p, q;
+    from_bits(((uint64_t)hi[0] << 32) | lo[0], p);
+    from_bits(((uint64_t)hi[1] << 32) | lo[1], q);
+    return p + q;
+}
+// The remaining levels, 8 to 1: every lane gets its row's sum.
+template <int M, typename V>
+__device__ __forceinline__ V row_add(V a) {
+    V b;
+    from_bits(row_xor_u64<M>(bits_of(a)), b);
+    return a + b;
+}
+template <typename V>
+__device__ __forceinline__ V row_sum(V a) {
+    return row_add<1>(row_add<2>(row_add<4>(row_add<8>(a))));
+}
+// Maximum over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = max(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = max(b[0], b[1]);
+    v = max(v, row_xor_u32<8>(v));
+    v = max(v, row_xor_u32<4>(v));
+    v = max(v, row_xor_u32<2>(v));
+    return max(v, row_xor_u32<1>(v));
+}
+
+// Orders a wave's own LDS accesses (LDS instructions of one wave execute in
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // 128-bit streaming loads
 // ---------------------------------------------------------------------------

@@ -17,31 +17,38 @@
 // chunk index, n, A, B).  A and B are sums, so any partition of the chunk
 // gives the same bits.
 //
-// Work decomposition: a chunk is cut into tiles of tile_bytes (a power of two
-// >= 1 KiB dividing chunk_bytes).  One 256-thread workgroup folds one tile:
-// its four waves take the tile's 1 KiB blocks round-robin, every lane loads
-// 16 bytes of a block with one 128-bit load, so one wave-wide load covers
-// exactly 256 words and lane l always owns key positions 4l .. 4l+5 (held in
-// VGPRs for the whole kernel) while beta is wave-uniform.  Lanes reduce with
-// xor butterflies, waves combine through LDS in a fixed order, and each tile
-// writes one 64-byte partial.  When a chunk is a single tile the workgroup
-// writes the chunk record directly; otherwise a finalize kernel combines the
-// chunk's partials in tile order.  The per-tile arithmetic never depends on
-// which workgroup runs it, so results are independent of the grid size and
-// of the tile order: large launches take their tiles through the XCD map
-// (xcd_map_tile), the others in order.
+// Work decomposition: a chunk is cut into tiles of tile_bytes (whole KiB; the
+// last tile of a chunk may be shorter).  A tile's 1 KiB blocks form four
+// quarters, block b belonging to quarter b mod 4; every lane loads 16 bytes of
+// a block with one 128-bit load, so one wave-wide load covers exactly 256
+// words and lane l always owns key positions 4l .. 4l+5 (held in VGPRs for
+// the whole kernel) while beta is wave-uniform.  Either a 256-thread workgroup
+// folds a tile, one wave per quarter (signature_kernel), or one wave folds
+// all four (signature_wave_kernel, small tiles in large numbers).  Lanes
+// reduce with xor butterflies, quarters combine in a fixed order, and each
+// tile writes one 64-byte partial.  When a chunk is a single tile the chunk
+// record is written directly; otherwise a finalize kernel combines the
+// chunk's partials in tile order.  The per-tile arithmetic depends neither on
+// which workgroup or wave runs it nor on which of the two kernels does, so
+// results are independent of the grid size, of the tile order and of what
+// else is signed in the launch: large launches take their tiles through the
+// XCD map (xcd_map_tile), the others in order.
 //
 // Non-finite screen: a lane sums its elements in fp64 without looking at
 // them.  A non-finite element is the only way its sum or sum of squares can
 // become non-finite (finite fp32/bf16/fp16 values cannot overflow fp64 here),
 // so a lane whose sums end non-finite re-reads its own segments and
 // classifies every element.  Healthy data never takes that path.
+#include <type_traits>
+
 #include "c3_device.h"
 #include "c3_internal.h"
 #include "c3_localize_block.h"
 #include "c3_vote_row.h"
 
 namespace c3 {
+
+constexpr int kRedoLoads = 8;   // loads in flight where a lane classifies its elements
 
 struct LaneKeys {
     uint32_t k0, k1, k2, k3, k4, k5;
@@ -129,39 +136,30 @@ __device__ inline uint32_t magnitude_bits(float mf) {
     return __float_as_uint(mf);
 }
 
-// slow statistics: classify each element; `mx` is a plain magnitude
+// slow statistics: classify each element; `mx` is a plain magnitude.  A
+// non-finite element counts as +0, which changes no sum (they start at +0,
+// so none is ever -0), and there are no branches: one lane redoes its column
+// of the tile while the wave waits.
 template <int DT>
 __device__ inline void stats_slow(const u32x4 v, double& s, double& q, uint32_t& mx,
                                   uint32_t& nan_c, uint32_t& inf_c) {
+    constexpr uint32_t inf_bits = DT == C3_F32 ? 0x7F800000u : DT == C3_BF16 ? 0x7F80u : 0x7C00u;
+    constexpr int N = DT == C3_F32 ? 4 : 8;
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    if constexpr (DT == C3_F32) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint32_t mag = w[i] & 0x7FFFFFFFu;
-            if (mag >= 0x7F800000u) {
-                if (mag > 0x7F800000u) ++nan_c; else ++inf_c;
-                continue;
-            }
-            double d = (double)__uint_as_float(w[i]);
-            s += d;
-            q = __fma_rn(d, d, q);
-            mx = max(mx, mag);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint32_t h = (i & 1) ? (w[i >> 1] >> 16) : (w[i >> 1] & 0xFFFFu);
-            uint32_t mag = h & 0x7FFFu;
-            const uint32_t inf_bits = (DT == C3_BF16) ? 0x7F80u : 0x7C00u;
-            if (mag >= inf_bits) {
-                if (mag > inf_bits) ++nan_c; else ++inf_c;
-                continue;
-            }
-            double d = (DT == C3_BF16) ? (double)__uint_as_float(h << 16) : f16_to_f64(h);
-            s += d;
-            q = __fma_rn(d, d, q);
-            mx = max(mx, mag);
-        }
+    for (int i = 0; i < N; ++i) {
+        uint32_t x = w[DT == C3_F32 ? i : i >> 1];
+        if constexpr (DT != C3_F32) x = (i & 1) ? x >> 16 : x & 0xFFFFu;
+        const uint32_t mag = x & (DT == C3_F32 ? 0x7FFFFFFFu : 0x7FFFu);
+        const bool fin = mag < inf_bits;
+        nan_c += mag > inf_bits;
+        inf_c += mag == inf_bits;
+        x = fin ? x : 0u;
+        mx = max(mx, fin ? mag : 0u);
+        const double d = DT == C3_F32 ? (double)__uint_as_float(x)
+                         : DT == C3_BF16 ? (double)__uint_as_float(x << 16) : f16_to_f64(x);
+        s += d;
+        q = __fma_rn(d, d, q);
     }
 }
 
@@ -177,39 +175,53 @@ __device__ inline u32x4 load_partial(const uint8_t* p, uint32_t rem) {
     return v;
 }
 
+// A lane's share of a tile.  The sums are kept in quarters: quarter q holds
+// blocks q, q + 4, ... of the tile, in ascending order, whether one wave
+// folds all four (NQ = 4) or four waves one each (NQ = 1), so the sums have
+// the same bits either way.
+template <int NQ>
 struct LaneFold {
     uint64_t A, B;
-    double s, q;
+    double s[NQ], q[NQ];
     uint32_t mx, nan_c, inf_c;
 };
 
-// One wave's share of a tile: blocks wave, wave + 4, ... of `len` bytes.
+// Fold of `len` bytes of a tile by NW waves (4, or 1: the whole tile by one):
+// blocks wave, wave + NW, ...
 // Full blocks are read with raw buffer loads: the resource is the tile (a
 // wave-uniform base, `len` bytes), the scalar offset the block, the vector
 // offset the lane's 16 bytes, so no load spends vector instructions on its
 // address.  Each block's beta is pinned in a scalar register, so every key
 // sum is one three-input add.
-template <int DT, int U>
-__device__ inline LaneFold fold_lane(const uint8_t* tile, uint32_t len, uint32_t blk0,
-                                     const LaneKeys& K, int wave, int lane) {
-    LaneFold f{0, 0, 0.0, 0.0, 0u, 0u, 0u};
+template <int DT, int U, int NW>
+__device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, uint32_t blk0,
+                                             const LaneKeys& K, int wave, int lane) {
+    constexpr int NQ = 4 / NW;
+    static_assert((NW == 1 || NW == 4) && U % 4 == 0, "quarters of a tile");
+    LaneFold<NQ> f;
+    f.A = f.B = 0;
+    f.mx = f.nan_c = f.inf_c = 0u;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) f.s[i] = f.q[i] = 0.0;
     float mf = 0.0f;
     const uint32_t off = (uint32_t)lane * 16u;
     const int nfull = (int)(len >> 10);
     const uint32_t tail = len & 1023u;
     const __amdgpu_buffer_rsrc_t rs = tile_resource(tile, len);
     int k = wave;
-    for (; k + 4 * (U - 1) < nfull; k += 4 * U) {
+    // k - wave is a multiple of NW U in both loops, so load u of a batch
+    // belongs to quarter u % NQ
+    for (; k + NW * (U - 1) < nfull; k += NW * U) {
         u32x4 v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = load16_buf(rs, off, (uint32_t)(k + 4 * u) << 10);
+        for (int u = 0; u < U; ++u) v[u] = load16_buf(rs, off, (uint32_t)(k + NW * u) << 10);
         // keep all U loads in flight before the first use
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t beta = block_beta(blk0 + (uint32_t)(k + 4 * u));
+            const uint32_t beta = block_beta(blk0 + (uint32_t)(k + NW * u));
             nh16(v[u], K, beta, f.A, f.B);
-            stats_fast<DT>(v[u], f.s, f.q, mf);
+            stats_fast<DT>(v[u], f.s[u % NQ], f.q[u % NQ], mf);
         }
     }
     if (k < nfull) {
@@ -218,38 +230,60 @@ __device__ inline LaneFold fold_lane(const uint8_t* tile, uint32_t len, uint32_t
         u32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (k + 4 * u < nfull) v[u] = load16_buf(rs, off, (uint32_t)(k + 4 * u) << 10);
+            if (k + NW * u < nfull) v[u] = load16_buf(rs, off, (uint32_t)(k + NW * u) << 10);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (k + 4 * u < nfull) {
-                nh16(v[u], K, block_beta(blk0 + (uint32_t)(k + 4 * u)), f.A, f.B);
-                stats_fast<DT>(v[u], f.s, f.q, mf);
+            if (k + NW * u < nfull) {
+                nh16(v[u], K, block_beta(blk0 + (uint32_t)(k + NW * u)), f.A, f.B);
+                stats_fast<DT>(v[u], f.s[u % NQ], f.q[u % NQ], mf);
             }
         }
     }
-    const bool has_tail = tail != 0u && (nfull & 3) == wave && off < tail;
+    const bool has_tail = tail != 0u && nfull % NW == wave && off < tail;
     if (has_tail) {
         const uint8_t* seg = tile + ((size_t)nfull << 10) + off;
         u32x4 v = (off + 16u <= tail) ? load16(reinterpret_cast<const u32x4*>(seg))
                                       : load_partial(seg, tail - off);
         nh16(v, K, (blk0 + (uint32_t)nfull) * kBlockMul, f.A, f.B);
-        stats_fast<DT>(v, f.s, f.q, mf);
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+            if (nfull % NQ == i) stats_fast<DT>(v, f.s[i], f.q[i], mf);
     }
     if constexpr (DT != C3_RAW) {
-        if (!__builtin_isfinite(f.s) || !__builtin_isfinite(f.q)) {
+        bool finite = true;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+            finite = finite && __builtin_isfinite(f.s[i]) && __builtin_isfinite(f.q[i]);
+        if (!finite) {
             // rare: this lane saw a NaN or Inf; redo its statistics classifying
-            f.s = 0.0;
-            f.q = 0.0;
             f.mx = 0u;
-            for (int kk = wave; kk < nfull; kk += 4)
-                stats_slow<DT>(load16(reinterpret_cast<const u32x4*>(tile + ((size_t)kk << 10) + off)),
-                               f.s, f.q, f.mx, f.nan_c, f.inf_c);
-            if (has_tail) {
-                const uint8_t* seg = tile + ((size_t)nfull << 10) + off;
-                u32x4 v = (off + 16u <= tail) ? load16(reinterpret_cast<const u32x4*>(seg))
-                                              : load_partial(seg, tail - off);
-                stats_slow<DT>(v, f.s, f.q, f.mx, f.nan_c, f.inf_c);
+            for (int i = 0; i < NQ; ++i) {
+                double si = 0.0, qi = 0.0;
+                for (int kk = wave + i; kk < nfull; kk += 4 * kRedoLoads) {
+                    u32x4 v[kRedoLoads];
+#pragma unroll
+                    for (int u = 0; u < kRedoLoads; ++u)
+                        if (kk + 4 * u < nfull)
+                            v[u] = load16_buf(rs, off, (uint32_t)(kk + 4 * u) << 10);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < kRedoLoads; ++u)
+                        if (kk + 4 * u < nfull)
+                            stats_slow<DT>(v[u], si, qi, f.mx, f.nan_c, f.inf_c);
+                }
+                if (has_tail && nfull % NQ == i) {
+                    const uint8_t* seg = tile + ((size_t)nfull << 10) + off;
+                    u32x4 v = (off + 16u <= tail) ? load16(reinterpret_cast<const u32x4*>(seg))
+                                                  : load_partial(seg, tail - off);
+                    stats_slow<DT>(v, si, qi, f.mx, f.nan_c, f.inf_c);
+                }
+#pragma unroll
+                for (int j = 0; j < NQ; ++j)
+                    if (j == i) {
+                        f.s[j] = si;
+                        f.q[j] = qi;
+                    }
             }
         } else {
             f.mx = magnitude_bits<DT>(mf);
@@ -258,36 +292,38 @@ __device__ inline LaneFold fold_lane(const uint8_t* tile, uint32_t len, uint32_t
     return f;
 }
 
-__device__ inline TilePartial wave_reduce(const LaneFold& f) {
-    TilePartial p;
-    p.A = f.A;
-    p.B = f.B;
-    p.s = f.s;
-    p.sc = 0.0;
-    p.q = f.q;
-    p.qc = 0.0;
-    p.maxbits = f.mx;
-    p.nan_count = f.nan_c;
-    p.inf_count = f.inf_c;
+// Lanes meet in a fixed six-level butterfly (lane distances 32 to 1) of plain
+// fp64 adds (error at most 6 ulp of the sum of magnitudes); compensation
+// starts where quarters meet.
+__device__ inline void reduce_counts(TilePartial& p, uint32_t mx, uint32_t nan_c, uint32_t inf_c) {
     p.pad = 0u;
-    // Lane sums meet in a fixed six-level butterfly of plain fp64 adds (error
-    // at most 6 ulp of the sum of magnitudes); compensation starts at the
-    // cross-wave level.
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        p.A += shfl_xor_u64(p.A, m);
-        p.B += shfl_xor_u64(p.B, m);
-        p.s += shfl_xor_f64(p.s, m);
-        p.q += shfl_xor_f64(p.q, m);
-        p.maxbits = max(p.maxbits, shfl_xor_u32(p.maxbits, m));
-    }
-    if (ballot64(f.nan_c != 0u || f.inf_c != 0u) != 0ull) {
+    p.maxbits = wave_max_u32(mx);
+    p.nan_count = nan_c;
+    p.inf_count = inf_c;
+    if (ballot64(nan_c != 0u || inf_c != 0u) != 0ull) {
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) {
             p.nan_count += shfl_xor_u32(p.nan_count, m);
             p.inf_count += shfl_xor_u32(p.inf_count, m);
         }
     }
+}
+
+// One quarter of a tile (a wave of four): its partial, in every lane.
+__device__ inline TilePartial wave_reduce(const LaneFold<1>& f) {
+    TilePartial p;
+    // A and B, sum and sum of squares side by side: lanes 0-31 end with the
+    // first, lanes 32-63 with the second
+    uint64_t ab = fold32(f.A, f.B);
+    double sq = fold32(f.s[0], f.q[0]);
+    ab = row_sum(fold16(ab, ab));
+    sq = row_sum(fold16(sq, sq));
+    p.A = readlane_u64(ab, 0);
+    p.B = readlane_u64(ab, 32);
+    from_bits(readlane_u64(bits_of(sq), 0), p.s);
+    from_bits(readlane_u64(bits_of(sq), 32), p.q);
+    p.sc = p.qc = 0.0;
+    reduce_counts(p, f.mx, f.nan_c, f.inf_c);
     return p;
 }
 
@@ -299,6 +335,32 @@ __device__ inline void partial_add(TilePartial& a, const TilePartial& b) {
     a.maxbits = max(a.maxbits, b.maxbits);
     a.nan_count += b.nan_count;
     a.inf_count += b.inf_count;
+}
+
+// A whole tile (one wave): the four quarters' sums meet as those of four
+// waves do.
+__device__ inline TilePartial wave_reduce(const LaneFold<4>& f) {
+    TilePartial p;
+    uint64_t ab = fold32(f.A, f.B);
+    ab = row_sum(fold16(ab, ab));
+    p.A = readlane_u64(ab, 0);
+    p.B = readlane_u64(ab, 32);
+    // row i of 16 lanes ends with quarter i
+    const double s = row_sum(fold16(fold32(f.s[0], f.s[2]), fold32(f.s[1], f.s[3])));
+    const double q = row_sum(fold16(fold32(f.q[0], f.q[2]), fold32(f.q[1], f.q[3])));
+    from_bits(readlane_u64(bits_of(s), 0), p.s);
+    from_bits(readlane_u64(bits_of(q), 0), p.q);
+    p.sc = p.qc = 0.0;
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+        double si, qi;
+        from_bits(readlane_u64(bits_of(s), 16 * i), si);
+        from_bits(readlane_u64(bits_of(q), 16 * i), qi);
+        comp_add(p.s, p.sc, si, 0.0);
+        comp_add(p.q, p.qc, qi, 0.0);
+    }
+    reduce_counts(p, f.mx, f.nan_c, f.inf_c);
+    return p;
 }
 
 __device__ inline int find_segment(const int64_t* base, int n, int64_t j) {
@@ -345,10 +407,88 @@ __device__ inline void write_record(c3_chunk_record_t* rec, const TensorInfo* ti
     rec->reserved = 0;
 }
 
-// One launch per element type present in the plan.  The plan lists the
-// tensors grouped by type (order[], stable in call order) with a tile prefix
-// over that order (gtile[]); this launch covers group positions [gk0, gk1)
-// of every replica.
+// a / b, in 32 bits where a allows it (a 64-bit division is a sequence of
+// more than a hundred instructions; the operands here are wave-uniform)
+__device__ inline uint64_t udiv(uint64_t a, uint32_t b) {
+    if (b == 1u) return a;
+    if ((a >> 32) == 0ull) return (uint32_t)a / b;
+    return a / b;
+}
+
+// The plan's arrays, and where a tile's bytes are.
+struct PlanView {
+    const uint64_t* ptrs;
+    const int64_t* tile_base;
+    const int64_t* chunk_base;
+    const int32_t* order;
+    const int64_t* gtile;
+    const TensorInfo* tinfo;
+    TilePartial* partials;
+    __device__ explicit PlanView(const SigPlan* plan) {
+        const char* pb = reinterpret_cast<const char*>(plan);
+        ptrs = reinterpret_cast<const uint64_t*>(pb + plan->off_ptrs);
+        tile_base = reinterpret_cast<const int64_t*>(pb + plan->off_tile_base);
+        chunk_base = reinterpret_cast<const int64_t*>(pb + plan->off_chunk_base);
+        order = reinterpret_cast<const int32_t*>(pb + plan->off_order);
+        gtile = reinterpret_cast<const int64_t*>(pb + plan->off_gtile);
+        tinfo = reinterpret_cast<const TensorInfo*>(pb + plan->off_tmeta);
+        partials = reinterpret_cast<TilePartial*>(const_cast<char*>(pb) + plan->off_partials);
+    }
+};
+
+// Tile lt of a tensor of nbytes bytes: tile lt mod tpc of chunk lt / tpc.
+struct TileSpan {
+    uint64_t chunk, off;   // chunk within the tensor, first byte
+    uint32_t len, blk0;    // bytes, first 1 KiB block within the chunk
+};
+
+__device__ inline TileSpan tile_span(uint64_t lt, uint32_t tpc, uint64_t chunk_bytes,
+                                     uint64_t tile_bytes, uint64_t nbytes) {
+    TileSpan s;
+    s.chunk = udiv(lt, tpc);
+    const uint64_t within = (lt - s.chunk * tpc) * tile_bytes;
+    s.off = s.chunk * chunk_bytes + within;
+    const uint64_t end = min(nbytes, (s.chunk + 1) * chunk_bytes);
+    s.len = end > s.off ? (uint32_t)min(tile_bytes, end - s.off) : 0u;
+    s.blk0 = (uint32_t)(within >> 10);
+    return s;
+}
+
+__device__ inline LaneKeys lane_keys(int lane) {
+    LaneKeys K;
+    K.k0 = nh_key(4u * lane + 0u);
+    K.k1 = nh_key(4u * lane + 1u);
+    K.k2 = nh_key(4u * lane + 2u);
+    K.k3 = nh_key(4u * lane + 3u);
+    K.k4 = nh_key(4u * lane + 4u);
+    K.k5 = nh_key(4u * lane + 5u);
+    return K;
+}
+
+// fold_lane for a compile-time type, or (kMixed) the tensor's own
+constexpr int kMixed = -1;
+
+template <int DT, int U, int NW>
+__device__ inline LaneFold<4 / NW> fold_tile(int dtype, const uint8_t* tile, uint32_t len, uint32_t blk0,
+                                     const LaneKeys& K, int wave, int lane) {
+    if constexpr (DT != kMixed) {
+        return fold_lane<DT, U, NW>(tile, len, blk0, K, wave, lane);
+    } else {
+        switch (__builtin_amdgcn_readfirstlane(dtype)) {
+            case C3_F32: return fold_lane<C3_F32, U, NW>(tile, len, blk0, K, wave, lane);
+            case C3_BF16: return fold_lane<C3_BF16, U, NW>(tile, len, blk0, K, wave, lane);
+            case C3_F16: return fold_lane<C3_F16, U, NW>(tile, len, blk0, K, wave, lane);
+            default: return fold_lane<C3_RAW, U, NW>(tile, len, blk0, K, wave, lane);
+        }
+    }
+}
+
+// The plan lists the tensors grouped by element type (order[], stable in call
+// order) with a tile prefix over that order (gtile[]); a launch covers group
+// positions [gk0, gk1) of every replica: the one type present, or all of them
+// with DT = kMixed.
+//
+// One workgroup per tile.
 template <int DT, int U>
 __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
     signature_kernel(const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records,
@@ -357,27 +497,13 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
     const int lane = threadIdx.x & 63;
     // the wave index, uniform across the wave (keeps beta and addresses scalar)
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const char* pb = reinterpret_cast<const char*>(plan);
-    const uint64_t* ptrs = reinterpret_cast<const uint64_t*>(pb + plan->off_ptrs);
-    const int64_t* tile_base = reinterpret_cast<const int64_t*>(pb + plan->off_tile_base);
-    const int64_t* chunk_base = reinterpret_cast<const int64_t*>(pb + plan->off_chunk_base);
-    const int32_t* order = reinterpret_cast<const int32_t*>(pb + plan->off_order);
-    const int64_t* gtile = reinterpret_cast<const int64_t*>(pb + plan->off_gtile);
-    const TensorInfo* tinfo = reinterpret_cast<const TensorInfo*>(pb + plan->off_tmeta);
-    TilePartial* partials = reinterpret_cast<TilePartial*>(const_cast<char*>(pb) + plan->off_partials);
+    const PlanView pv(plan);
     const int T = plan->T;
     const int64_t ntiles = gtiles * plan->R;
-    const uint64_t tile_bytes = plan->tile_bytes;
+    const uint64_t tile_bytes = plan->tile_bytes, chunk_bytes = plan->chunk_bytes;
     const uint32_t tpc = plan->tiles_per_chunk;
-    const int64_t g0 = gtile[gk0];
-
-    LaneKeys K;
-    K.k0 = nh_key(4u * lane + 0u);
-    K.k1 = nh_key(4u * lane + 1u);
-    K.k2 = nh_key(4u * lane + 2u);
-    K.k3 = nh_key(4u * lane + 3u);
-    K.k4 = nh_key(4u * lane + 4u);
-    K.k5 = nh_key(4u * lane + 5u);
+    const int64_t g0 = pv.gtile[gk0];
+    const LaneKeys K = lane_keys(lane);
 
     // a mapped launch: one tile per workgroup, from the XCD map; otherwise
     // tiles blockIdx.x, blockIdx.x + gridDim.x, ...
@@ -385,16 +511,14 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
          i += mapped ? ntiles : (int64_t)gridDim.x) {
         const int64_t r = i / gtiles;
         const int64_t j = g0 + (i - r * gtiles);
-        const int k = gk0 + find_segment(gtile + gk0, gk1 - gk0, j);
-        const int t = order[k];
-        const int64_t lt = j - gtile[k];
-        const uint64_t nbytes = tinfo[t].nbytes;
-        const uint64_t toff = (uint64_t)lt * tile_bytes;
-        const uint32_t len = nbytes > toff ? (uint32_t)min(tile_bytes, nbytes - toff) : 0u;
-        const uint32_t blk0 = (uint32_t)(((uint64_t)(lt % tpc) * tile_bytes) >> 10);
-        const uint8_t* tile = reinterpret_cast<const uint8_t*>(ptrs[r * T + t]) + toff;
+        const int k = gk0 + find_segment(pv.gtile + gk0, gk1 - gk0, j);
+        const int t = pv.order[k];
+        const int64_t lt = j - pv.gtile[k];
+        const TileSpan ts = tile_span((uint64_t)lt, tpc, chunk_bytes, tile_bytes, pv.tinfo[t].nbytes);
+        const uint8_t* tile = reinterpret_cast<const uint8_t*>(pv.ptrs[r * T + t]) + ts.off;
 
-        const LaneFold f = fold_lane<DT, U>(tile, len, blk0, K, wave, lane);
+        const LaneFold<1> f = fold_tile<DT, U, 4>(pv.tinfo[t].dtype, tile, ts.len, ts.blk0,
+                                                     K, wave, lane);
         const TilePartial wp = wave_reduce(f);
         if (lane == 0) lds[wave] = wp;
         __syncthreads();
@@ -402,15 +526,81 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
             TilePartial p = lds[0];
 #pragma unroll
             for (int w = 1; w < kSigThreads / 64; ++w) partial_add(p, lds[w]);
-            if (plan->direct) {
-                const uint64_t kc = (uint64_t)lt;  // one tile per chunk
-                const uint64_t n = nbytes > toff ? min(plan->chunk_bytes, nbytes - toff) : 0;
-                write_record(&records[r * plan->C + chunk_base[t] + (int64_t)kc], tinfo + t, t, kc, n, p);
-            } else {
-                partials[r * plan->tiles_per_replica + tile_base[t] + lt] = p;
-            }
+            if (plan->direct)  // one tile per chunk
+                write_record(&records[r * plan->C + pv.chunk_base[t] + lt], pv.tinfo + t, t,
+                             (uint64_t)lt, ts.len, p);
+            else
+                pv.partials[r * plan->tiles_per_replica + pv.tile_base[t] + lt] = p;
         }
         __syncthreads();
+    }
+}
+
+// One wave per tile, `run` consecutive tiles (at most kWaveRunMax) per wave:
+// tiles up to kWaveTileMax bytes.  A workgroup on a 16 KiB tile has four loads in
+// flight per lane and then a barrier, four reductions and a record to write:
+// its latency, not the memory, sets the pace (2.8 TB/s on 1.6 GB of bf16 in
+// 16 KiB chunks).  A wave per tile keeps 16 loads in flight per lane; the
+// keys and the look-ups serve the whole run, and the run's records are hashed
+// and written by one lane each, together.  No barrier: waves are independent.
+// Each quarter of a tile's blocks is summed apart, as the four waves of a
+// workgroup do, so both kernels write the same bits.
+struct RunTile {
+    TilePartial p;
+    int64_t r, lt;
+    int32_t t;
+    uint32_t len;
+};
+
+template <int DT, int U>
+__global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
+    signature_wave_kernel(const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records,
+                          int gk0, int gk1, int64_t gtiles, int run) {
+    __shared__ RunTile done[kSigThreads / 64][kWaveRunMax];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t ntiles = gtiles * plan->R;
+    const PlanView pv(plan);
+    const int T = plan->T;
+    const uint64_t tile_bytes = plan->tile_bytes, chunk_bytes = plan->chunk_bytes;
+    const uint32_t tpc = plan->tiles_per_chunk;
+    const int64_t g0 = pv.gtile[gk0];
+    const LaneKeys K = lane_keys(lane);
+    const int64_t nruns = (ntiles + run - 1) / run;
+    for (int64_t w = (int64_t)blockIdx.x * (kSigThreads / 64) + wave; w < nruns;
+         w += (int64_t)gridDim.x * (kSigThreads / 64)) {
+        const int64_t i0 = w * run;
+        const int count = (int)min((int64_t)run, ntiles - i0);
+        int64_t r = i0 / gtiles;
+        int64_t j = g0 + (i0 - r * gtiles);
+        int k = gk0 + find_segment(pv.gtile + gk0, gk1 - gk0, j);
+        for (int m = 0; m < count; ++m, ++j) {
+            if (j == g0 + gtiles) {                    // on to the next replica
+                ++r;
+                j = g0;
+                k = gk0;
+            }
+            while (j >= pv.gtile[k + 1]) ++k;          // every tensor has a tile: at most one step
+            const int t = pv.order[k];
+            const int64_t lt = j - pv.gtile[k];
+            const TileSpan ts =
+                tile_span((uint64_t)lt, tpc, chunk_bytes, tile_bytes, pv.tinfo[t].nbytes);
+            const uint8_t* tile = reinterpret_cast<const uint8_t*>(pv.ptrs[r * T + t]) + ts.off;
+            const LaneFold<4> f =
+                fold_tile<DT, U, 1>(pv.tinfo[t].dtype, tile, ts.len, ts.blk0, K, 0, lane);
+            const TilePartial p = wave_reduce(f);
+            if (lane == 0) done[wave][m] = RunTile{p, r, lt, t, ts.len};
+        }
+        wave_lds_sync();
+        if (lane < count) {
+            const RunTile d = done[wave][lane];
+            if (plan->direct)
+                write_record(&records[d.r * plan->C + pv.chunk_base[d.t] + d.lt], pv.tinfo + d.t,
+                             d.t, (uint64_t)d.lt, d.len, d.p);
+            else
+                pv.partials[d.r * plan->tiles_per_replica + pv.tile_base[d.t] + d.lt] = d.p;
+        }
+        wave_lds_sync();                               // read before the next run writes
     }
 }
 
@@ -872,12 +1062,44 @@ hipError_t launch_plan_fetch(const void* host_src, void* dst, size_t bytes, hipS
     return hipGetLastError();
 }
 
+// A wave per tile instead of a workgroup: for small tiles, once there are
+// enough of them that waves fill the chip.  Either way the results are the
+// same bits.  Kernel us, workgroup / wave, bf16 (fp32 alike unless given):
+//   16 KiB tiles   490: 9.4 / 9.2   1,954: 15.0 / 11.2   7,814: 46 / 28   97,658: 535 / 249
+//   32 KiB tiles   246: 9.0 / 9.5     978: 11.5 / 10.7   7,814: 60 / 46   48,830: 332 / 241
+//   48 KiB tiles   652: 11.3 / 12.0 1,304: 18.3 / 19.3   2,606: 28.9 / 27.1  32,554: 281 / 235
+//   64 KiB tiles 3,908: 45.4 / 46.8 9,156: 98.6 / 95.4  24,416: 251 / 239 (fp32: 233 / 236)
+//   96 KiB tiles 16,278: 238 / 240
+// A lane that meets a NaN classifies its column of the tile, a quarter of it
+// per wave in a workgroup and all of it in a wave: 490 tiles of 16 KiB with
+// one NaN take 9.2 / 12.1 us, hence not below 1,024 tiles.
+static bool wave_tiles(int dt, uint64_t tile_bytes, int64_t ntiles) {
+    if (tile_bytes <= 32 * 1024) return ntiles >= 1024;
+    if (tile_bytes <= 48 * 1024) return ntiles >= 2048;
+    return dt != C3_F32 && tile_bytes <= kWaveTileMax && ntiles >= 8192;
+}
+
 template <int DT>
 static hipError_t launch_group(const SigPlan* dplan, c3_chunk_record_t* records, int gk0, int gk1,
                                int64_t gtiles, int R, uint64_t tile_bytes, int grid_blocks,
                                hipStream_t stream) {
     const int64_t ntiles = gtiles * R;
     if (ntiles <= 0) return hipSuccess;
+    if (wave_tiles(DT, tile_bytes, ntiles)) {
+        // a run of kWaveRunBytes, shorter while the launch has fewer waves
+        // than the chip holds at a time; results do not depend on it
+        int64_t run = (int64_t)(kWaveRunBytes / tile_bytes);
+        const int64_t fill = ntiles / kWaveFill;
+        run = run > fill ? fill : run;
+        run = run < 1 ? 1 : run > kWaveRunMax ? kWaveRunMax : run;
+        const int64_t per = run * (kSigThreads / 64);
+        int64_t grid = (ntiles + per - 1) / per;
+        if (grid_blocks > 0 && grid > grid_blocks) grid = grid_blocks;
+        if (grid > 0x7FFFFFFF) grid = 0x7FFFFFFF;
+        hipLaunchKernelGGL((signature_wave_kernel<DT, kUnroll>), dim3((unsigned)grid),
+                           dim3(kSigThreads), 0, stream, dplan, records, gk0, gk1, gtiles, (int)run);
+        return hipGetLastError();
+    }
     int64_t grid = grid_blocks > 0 ? grid_blocks : ntiles;
     if (grid > ntiles) grid = ntiles;
     const int mapped = grid_blocks <= 0 && xcd_map_applies(ntiles, tile_bytes);
@@ -893,18 +1115,27 @@ hipError_t launch_signature(const SigPlan* dplan, const SigPlan& hplan, const Si
                             hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
     hipError_t e;
     if (ev0 && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
-    for (int d = 0; d < 4; ++d) {
-        const int gk0 = groups.k0[d], gk1 = groups.k1[d];
-        if (gk1 <= gk0) continue;
-        const int64_t gt = groups.tiles[d];
-        switch (d) {
-            case C3_F32: e = launch_group<C3_F32>(dplan, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks, stream); break;
-            case C3_BF16: e = launch_group<C3_BF16>(dplan, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks, stream); break;
-            case C3_F16: e = launch_group<C3_F16>(dplan, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks, stream); break;
-            default: e = launch_group<C3_RAW>(dplan, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks, stream); break;
+    int only = -1, types = 0;
+    for (int d = 0; d < 4; ++d)
+        if (groups.k1[d] > groups.k0[d]) {
+            only = d;
+            ++types;
         }
-        if (e != hipSuccess) return e;
-    }
+    auto launch = [&](auto dt) {
+        constexpr int DT = decltype(dt)::value;
+        const int gk0 = DT == kMixed ? 0 : groups.k0[only], gk1 = DT == kMixed ? hplan.T : groups.k1[only];
+        const int64_t gt = DT == kMixed ? hplan.tiles_per_replica : groups.tiles[only];
+        return launch_group<DT>(dplan, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks,
+                                stream);
+    };
+    // several types in one launch: a launch for each drains the chip between
+    // them (767-wide layers with fp32 norms and fp16 biases: 20 us of 320)
+    if (types > 1) e = launch(std::integral_constant<int, kMixed>{});
+    else if (only == C3_F32) e = launch(std::integral_constant<int, C3_F32>{});
+    else if (only == C3_BF16) e = launch(std::integral_constant<int, C3_BF16>{});
+    else if (only == C3_F16) e = launch(std::integral_constant<int, C3_F16>{});
+    else e = launch(std::integral_constant<int, C3_RAW>{});
+    if (e != hipSuccess) return e;
     if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
     if (!hplan.direct && finalize) {
         const int64_t total = hplan.C * hplan.R;

@@ -19,7 +19,8 @@ struct SigPlan {
     int64_t C;                  // chunks per replica
     int64_t tiles_per_replica;  // tiles per replica
     uint64_t chunk_bytes;
-    uint64_t tile_bytes;        // power-of-two multiple of 1024, divides chunk_bytes
+    uint64_t tile_bytes;        // multiple of 1024; a chunk is tiles_per_chunk tiles, the last
+                                // of them shorter where the size does not divide the chunk
     uint32_t tiles_per_chunk;
     uint32_t direct;            // 1: one tile per chunk, tiles write records
     // byte offsets (from the SigPlan base) of the arrays below
@@ -66,6 +67,11 @@ static_assert(sizeof(c3_chunk_record_t) == 64, "record layout");
 constexpr uint64_t kDefaultTileMax = C3_SIG_TILE_MAX;
 constexpr int kSigThreads = 256;
 constexpr int kUnroll = C3_SIG_UNROLL;
+
+constexpr uint64_t kWaveTileMax = 64 * 1024;    // largest tile that one wave folds alone
+constexpr uint64_t kWaveRunBytes = 64 * 1024;   // bytes a wave folds, over consecutive tiles
+constexpr int64_t kWaveFill = 8192;             // waves a launch should have before runs grow
+constexpr int kWaveRunMax = 16;
 
 // Tile map of large launches.  The hardware hands workgroup b to XCD
 // b mod 8, and on MI355X XCDs 1, 3, 5 and 7 read about 6% slower than the

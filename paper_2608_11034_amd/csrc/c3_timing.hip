@@ -95,12 +95,6 @@ __device__ __forceinline__ int stage_slot(int u, int c) {
     return u * CP + ((c + (u >> S)) & (CP - 1));
 }
 
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Loads of one kind: the wave's rows start at wbase, nbytes of them exist
 // (non-temporal: every record is read once)
 // (whole rows, at least one); loads past them re-read the last 16 bytes.

@@ -77,12 +77,6 @@ __global__ void __launch_bounds__(kVoteThreads) statistical_vote_small_kernel(
 // ---------------------------------------------------------------------------
 constexpr int kWideUnitsPerBlock = kVoteThreads / 64;
 
-__device__ inline uint64_t readlane_u64(uint64_t v, int l) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ inline double readlane_f64(double v, int l) {
     return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
 }

@@ -1,0 +1,105 @@
+"""The signature's tiles: chunk sizes that are no power of two, element types
+side by side in one launch, and the two kernels that fold a tile (a workgroup,
+or one wave for small tiles in large numbers), against the CPU oracle and
+against each other bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from parity import compare_all_records
+
+pytestmark = pytest.mark.gpu
+
+c3 = pytest.importorskip("paper_2608_11034_amd.c3")
+DEV = "cuda"
+KIB = 1024
+CODE = {torch.float32: workloads.F32, torch.bfloat16: workloads.BF16, torch.float16: workloads.F16,
+        torch.uint8: workloads.RAW}
+
+
+def _tensor(dtype, n, gen, special=True):
+    if dtype == torch.uint8:
+        return torch.randint(0, 256, (n,), generator=gen, device=DEV, dtype=dtype)
+    t = torch.randn(n, generator=gen, device=DEV).to(dtype)
+    if special and n > 40:
+        t[n // 3] = float("nan")
+        t[n // 2] = float("inf")
+        t[-1] = float("nan")             # in the partial last segment, where there is one
+    return t
+
+
+def _sign(reps, chunk, tile=0, grid_blocks=0):
+    plan = c3.SignaturePlan(reps, chunk, tile)
+    rec = plan.new_records()
+    plan.run(rec, plan.new_workspace(), grid_blocks=grid_blocks)
+    torch.cuda.synchronize()
+    return rec
+
+
+def _oracle(reps, chunk):
+    metas = [(CODE[t.dtype], tuple(t.shape)) for t in reps[0]]
+    return oracle.signature([[workloads.host_bytes(t) for t in rep] for rep in reps], metas, chunk)
+
+
+# tile sizes by default: the chunk itself up to 256 KiB, then 2 x 160, 2 x 250
+# and 4 x 250 KiB, and 3 x 257 KiB of which the last is 1 KiB shorter than the
+# others (770 KiB); tensors end inside, at and just past tiles and chunks
+@pytest.mark.parametrize("chunk_kib", [5, 33, 100, 160, 255, 257, 320, 500, 770, 1000])
+def test_chunk_sizes_mixed_types(chunk_kib):
+    chunk = chunk_kib * KIB
+    print("CASE chunk", chunk_kib, flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(chunk_kib)
+    base = []
+    for dtype in (torch.bfloat16, torch.float32, torch.uint8, torch.float16, torch.bfloat16):
+        es = torch.empty(0, dtype=dtype).element_size()
+        for nbytes in (0, es, chunk // 2, chunk - es, chunk, chunk + es, 2 * chunk + 161 * KIB + 7 * es):
+            base.append(_tensor(dtype, nbytes // es, gen))
+    reps = [[t.clone() for t in base] for _ in range(2)]
+    reps[1][6].view(torch.uint8)[-1] ^= 1
+    rec = c3.records_numpy(_sign(reps, chunk))
+    compare_all_records(rec, _oracle(reps, chunk))
+    assert (rec["sig"][0] != rec["sig"][1]).sum() == 1
+
+
+# launches on both sides of the rule's tile counts; one replica alone (a
+# workgroup per tile) against the same replica among others (a wave per tile):
+# the records must be the same bits, sums included
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16, torch.uint8])
+@pytest.mark.parametrize("chunk_kib,tiles,R", [(16, 257, 4), (33, 160, 13), (48, 130, 16), (64, 129, 64)])
+def test_wave_tiles_same_bits(dtype, chunk_kib, tiles, R):
+    chunk = chunk_kib * KIB
+    print("CASE wave tiles", dtype, chunk_kib, tiles, R, flush=True)
+    es = torch.empty(0, dtype=dtype).element_size()
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(chunk_kib)
+    # two tensors, the first ending 3 elements into a 16-byte segment
+    half = (tiles // 2 - 1) * chunk // es
+    base = [_tensor(dtype, half + 515 * 16 // es + 3, gen), _tensor(dtype, half, gen, special=False)]
+    reps = [base] + [[t.clone() for t in base] for _ in range(R - 1)]
+    together = _sign(reps, chunk)
+    alone = _sign([reps[R - 1]], chunk)
+    assert torch.equal(together, alone.expand(R, *alone.shape[1:]))
+    compare_all_records(c3.records_numpy(alone), _oracle([base], chunk))
+
+
+# runs of one to sixteen consecutive tiles per wave, crossing tensors, types
+# and replicas, in as many workgroups as wanted and in three
+@pytest.mark.parametrize("tiles", [1500, 20_000, 140_000])
+def test_wave_runs(tiles):
+    print("CASE wave runs", tiles, flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(tiles)
+    n = tiles // 2 // 3 * KIB
+    base = [_tensor(torch.uint8, n + 1, gen), _tensor(torch.bfloat16, n // 2 + 1, gen),
+            _tensor(torch.float32, n // 4 - 1, gen)]
+    reps = [base, [t.clone() for t in base]]
+    rec = _sign(reps, KIB)
+    compare_all_records(c3.records_numpy(rec[:1]), _oracle([base], KIB))
+    assert torch.equal(rec[0], rec[1])
+    assert torch.equal(rec, _sign(reps, KIB, grid_blocks=3))
+    # the same chunks in smaller tiles go through partials
+    wide = _sign(reps, 4 * KIB, tile=KIB)
+    compare_all_records(c3.records_numpy(wide[:1]), _oracle([base], 4 * KIB))
