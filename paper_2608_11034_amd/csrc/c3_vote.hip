@@ -3,16 +3,13 @@
 // Which kernel decides a unit depends on the group size R:
 //   R <= 32   one thread per unit, the R values in registers (128-bit row
 //             loads when replicas are adjacent), deciding with the per-unit
-//             functions of c3_vote_row.h;
-//   R > 32    one wave per unit: lane l holds replicas l, l + 64, ... (see
-//             the wave kernels below) and bitmap word s is one ballot.  The
-//             exact vote broadcasts candidate values by readlane; the
-//             statistical vote sorts the wave's values once.
-// Per 256K units the wave kernel's statistical vote takes 0.09-0.11 ms at
-// R = 33-64 and 0.26-0.37 ms at R = 129-256 (fp32-fp64), 1.8x to 8x faster
-// than the rank loops and (value, replica) double sorts it replaced; on 1M-unit
-// rows its exact vote was up to 7.6x (R = 64) faster than lane-per-replica
-// counting.
+//             functions of c3_vote_row.h (fp64 statistics up to R = 16);
+//   above     exact: one wave per unit, lane l holding replicas l, l + 64,
+//             ..., candidate values broadcast by readlane, bitmap word s one
+//             ballot; statistical: sixteen lanes per unit, which sort the
+//             unit's values once.
+// On 1M-unit rows the wave's exact vote was up to 7.6x (R = 64) faster than
+// lane-per-replica counting.
 //
 // EXACT (Sec. 5.3): a strict majority exists iff some value is held by more
 // than R / 2 replicas; those are the majority, the bitmap marks the others
@@ -76,10 +73,6 @@ __global__ void __launch_bounds__(kVoteThreads) statistical_vote_small_kernel(
 // at a wave-uniform index; the statistical vote sorts the wave's values.
 // ---------------------------------------------------------------------------
 constexpr int kWideUnitsPerBlock = kVoteThreads / 64;
-
-__device__ inline double readlane_f64(double v, int l) {
-    return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
-}
 
 // Value of replica j (wave-uniform) from the slot registers.
 template <int NS>
@@ -167,174 +160,158 @@ __global__ void __launch_bounds__(kVoteThreads) exact_vote_wide_kernel(
     wide_write<NS>(u, any ? C3_ATTRIBUTED : C3_AGREE, ob, mj, status, bitmap, majority_idx);
 }
 
-// STATISTICAL over more than 32 replicas: the wave sorts the finite values
-// once and reads every order statistic off the sorted copy.
+// STATISTICAL over more than 32 replicas (fp64: 16): sixteen lanes decide a
+// unit, four units a wave.
 //
-// Sorted position p = NP lane + i lives in register i of lane `lane` (NP =
-// ceil(R / 64) rounded up to a power of two, excluded values as +inf), so
-// the network's shortest distances -- the most frequent ones -- are
-// compare-exchanges between a lane's own registers, and the rest pair lane l
-// with lane l ^ M.  The network is the bitonic sorter in its one-direction
-// form: merging blocks of K, position p first meets p ^ (K - 1) (the
-// reversed other half), then p ^ j for j = K / 4 .. 1, the smaller key
-// always going to the lower position.  Values only: equal values are
-// interchangeable, and the lower-median replica is found afterwards by
-// counting.
+// Lane l of the sixteen loads replicas l, l + 16, ... (NL of them, so a load
+// reads four runs of sixteen adjacent values), the group sorts the finite
+// values once and every order statistic is read off the sorted copy in LDS.
+// Sorted position p = NL l + i is register i of lane l (excluded values as
+// +inf): the network's short distances, the most frequent ones, are
+// comparators between a lane's own registers, one instruction per value and
+// stage, and only the distances between lanes, at most 15, cost a DPP move and
+// a select.  The network is
+// the bitonic sorter in its one-direction form: merging blocks of B lanes,
+// (lane, i) first meets (lane ^ (B - 1), NL - 1 - i), the reversed other half,
+// then lane ^ B / 4 .. lane ^ 1, and then a lane's own bitonic run is sorted.
+// Values only: equal values are interchangeable, and the lower-median replica
+// is found afterwards by counting.
+//
+// VALU-bound.  262,144 units, us per call, against one wave per unit with
+// R / 64 values a lane and order statistics by readlane:
+//   R          33     64    128    192    256
+//   fp32     82->42 92->45 179->73 265->105 288->139
+//   fp64     91->53 102->55 198->99 314->156 335->221
 
-// Lane l's copy of v from lane l ^ M: DPP where a row of 16 can express the
-// pattern (quad permutes, mirrors), ds_swizzle inside 32 lanes, ds_bpermute
-// across the halves.
 template <int M>
-__device__ __forceinline__ uint32_t xor_lane_u32(uint32_t v) {
+__device__ __forceinline__ uint32_t row_lane_u32(uint32_t v) {   // lane ^ M within a row of 16
     const int iv = (int)v;
-    if constexpr (M == 1) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0xB1, 0xF, 0xF, false);
-    else if constexpr (M == 2) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0x4E, 0xF, 0xF, false);
-    else if constexpr (M == 3) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0x1B, 0xF, 0xF, false);
+    if constexpr (M == 3) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0x1B, 0xF, 0xF, false);
     else if constexpr (M == 7) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0x141, 0xF, 0xF, false);
     else if constexpr (M == 15) return (uint32_t)__builtin_amdgcn_mov_dpp(iv, 0x140, 0xF, 0xF, false);
-    else if constexpr (M < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle(iv, 0x1F | (M << 10));
-    else return (uint32_t)__shfl_xor(iv, M, 64);
+    else return row_xor_u32<M>(v);
 }
-
 template <int M>
-__device__ __forceinline__ float xor_lane(float v) {
-    return __uint_as_float(xor_lane_u32<M>(__float_as_uint(v)));
+__device__ __forceinline__ float row_lane(float v) {
+    return __uint_as_float(row_lane_u32<M>(__float_as_uint(v)));
 }
-
 template <int M>
-__device__ __forceinline__ double xor_lane(double v) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint64_t lo = xor_lane_u32<M>((uint32_t)b), hi = xor_lane_u32<M>((uint32_t)(b >> 32));
+__device__ __forceinline__ double row_lane(double v) {
+    const uint64_t b = bits_of(v);
+    const uint64_t lo = row_lane_u32<M>((uint32_t)b), hi = row_lane_u32<M>((uint32_t)(b >> 32));
     return __longlong_as_double((long long)((hi << 32) | lo));
 }
 
-template <typename V>
-__device__ __forceinline__ void order_pair(V& a, V& b) {
-    const bool sw = b < a;
-    const V lo = sw ? b : a, hi = sw ? a : b;
+// Between lanes: the lane in the lower half of the pair keeps the smaller
+// value.  The median of a, b and -inf is their minimum, of a, b and +inf
+// their maximum, so one instruction serves both halves in fp32.
+struct KeepF32 {
+    float c;
+    __device__ explicit KeepF32(bool upper) : c(upper ? __builtin_huge_valf() : -__builtin_huge_valf()) {}
+    __device__ __forceinline__ float operator()(float a, float b) const {
+        return __builtin_amdgcn_fmed3f(a, b, c);
+    }
+};
+struct KeepF64 {
+    bool upper;
+    __device__ explicit KeepF64(bool u) : upper(u) {}
+    __device__ __forceinline__ double operator()(double a, double b) const {
+        return ((b < a) != upper) ? b : a;
+    }
+};
+
+// Plain min and max between a lane's own registers.  The builtins rather than
+// inline assembly: their results feed DPP moves, whose wait states the
+// compiler places only after instructions that it knows.
+__device__ __forceinline__ void order_pair(float& a, float& b) {
+    const float lo = __builtin_fminf(a, b), hi = __builtin_fmaxf(a, b);
     a = lo;
     b = hi;
 }
-
-// Between lanes: a lane in the lower half of the pair keeps the smaller key.
+__device__ __forceinline__ void order_pair(double& a, double& b) {
+    const double lo = __builtin_fmin(a, b), hi = __builtin_fmax(a, b);
+    a = lo;
+    b = hi;
+}
 template <typename V>
-__device__ __forceinline__ V keep(V mine, V other, bool upper) {
-    return ((other < mine) != upper) ? other : mine;
+__device__ __forceinline__ void order_three(V& a, V& b, V& c) {
+    order_pair(a, b);
+    order_pair(b, c);
+    order_pair(a, b);
 }
 
-template <int NP, int K, typename V>
-__device__ __forceinline__ void sort_flip(V (&k)[NP], int lane) {
-    if constexpr (K <= NP) {
+// Sorts registers [at, at + N) that hold a bitonic run (half-cleaners work on
+// any even length, so twelve go 6, 3 and then threes).
+template <int N, int NL, typename V>
+__device__ __forceinline__ void sort_run(V (&k)[NL], int at) {
+    if constexpr (N == 3) {
+        order_three(k[at], k[at + 1], k[at + 2]);
+    } else if constexpr (N >= 2) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i)
-            if (i < (i ^ (K - 1))) order_pair(k[i], k[i ^ (K - 1)]);
-    } else {
-        constexpr int M = K / NP - 1;               // (lane, i) meets (lane ^ M, i ^ (NP - 1))
-        const bool upper = (lane & (K / NP / 2)) != 0;
-        V o[NP];
+        for (int i = 0; i < N / 2; ++i) order_pair(k[at + i], k[at + i + N / 2]);
+        sort_run<N / 2>(k, at);
+        sort_run<N / 2>(k, at + N / 2);
+    }
+}
+// Sorts registers [at, at + N): halves, then the reversed merge.  (Batcher's
+// network would save 17 of 80 comparators at 16, 2% of the whole sort.)
+template <int N, int NL, typename V>
+__device__ __forceinline__ void sort_lane(V (&k)[NL], int at) {
+    if constexpr (N == 3) {
+        order_three(k[at], k[at + 1], k[at + 2]);
+    } else if constexpr (N >= 2) {
+        sort_lane<N / 2>(k, at);
+        sort_lane<N / 2>(k, at + N / 2);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) o[i] = xor_lane<M>(k[i ^ (NP - 1)]);
+        for (int i = 0; i < N / 2; ++i) order_pair(k[at + i], k[at + N - 1 - i]);
+        sort_run<N / 2>(k, at);
+        sort_run<N / 2>(k, at + N / 2);
+    }
+}
+template <int M, int NL, typename V>
+__device__ __forceinline__ void sort_halves(V (&k)[NL], int lane) {
+    using Keep = typename std::conditional<sizeof(V) == 4, KeepF32, KeepF64>::type;
+    if constexpr (M >= 1) {
+        const Keep keep((lane & M) != 0);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) k[i] = keep(k[i], o[i], upper);
+        for (int i = 0; i < NL; ++i) k[i] = keep(k[i], row_lane<M>(k[i]));
+        sort_halves<M / 2>(k, lane);
+    }
+}
+template <int B, int NL, typename V>
+__device__ __forceinline__ void sort_merge(V (&k)[NL], int lane) {
+    using Keep = typename std::conditional<sizeof(V) == 4, KeepF32, KeepF64>::type;
+    if constexpr (B <= 16) {
+        const Keep keep((lane & (B / 2)) != 0);
+        V o[NL];
+#pragma unroll
+        for (int i = 0; i < NL; ++i) o[i] = row_lane<B - 1>(k[NL - 1 - i]);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) k[i] = keep(k[i], o[i]);
+        sort_halves<B / 4>(k, lane);
+        sort_run<NL>(k, 0);
+        sort_merge<2 * B>(k, lane);
     }
 }
 
-template <int NP, int J, typename V>
-__device__ __forceinline__ void sort_halves(V (&k)[NP], int lane) {
-    if constexpr (J >= 1) {
-        if constexpr (J < NP) {
-#pragma unroll
-            for (int i = 0; i < NP; ++i)
-                if ((i & J) == 0) order_pair(k[i], k[i | J]);
-        } else {
-            constexpr int M = J / NP;
-            const bool upper = (lane & M) != 0;
-#pragma unroll
-            for (int i = 0; i < NP; ++i) k[i] = keep(k[i], xor_lane<M>(k[i]), upper);
-        }
-        sort_halves<NP, J / 2>(k, lane);
-    }
+__device__ __forceinline__ uint32_t row_sum_u32(uint32_t v) {
+    v += row_xor_u32<8>(v);
+    v += row_xor_u32<4>(v);
+    v += row_xor_u32<2>(v);
+    return v + row_xor_u32<1>(v);
+}
+__device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {
+    v = min(v, row_xor_u32<8>(v));
+    v = min(v, row_xor_u32<4>(v));
+    v = min(v, row_xor_u32<2>(v));
+    return min(v, row_xor_u32<1>(v));
 }
 
-template <int NP, int K, typename V>
-__device__ __forceinline__ void wave_sort(V (&k)[NP], int lane) {
-    if constexpr (K <= 64 * NP) {
-        sort_flip<NP, K>(k, lane);
-        sort_halves<NP, K / 4>(k, lane);
-        wave_sort<NP, 2 * K>(k, lane);
-    }
-}
+// The lowest R that takes NL registers a lane.
+constexpr int stat_least(int nl) { return nl == 2 ? 17 : nl == 4 ? 33 : nl == 8 ? 65 : nl == 12 ? 129 : 193; }
+constexpr int kStatUnits = kVoteThreads / 16;      // units per workgroup
 
-// The key at sorted position p (wave-uniform).
-template <int NP, typename V>
-__device__ __forceinline__ double sorted_at(const V (&k)[NP], int p) {
-    const int l = p / NP, i = p % NP;
-    V r = 0;
-#pragma unroll
-    for (int t = 0; t < NP; ++t)
-        if (t == i) {
-            if constexpr (sizeof(V) == 4)
-                r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(k[t]), l));
-            else
-                r = __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(k[t]), l));
-        }
-    return (double)r;
-}
-
-template <int NP, typename V>
-__device__ __forceinline__ double sorted_median(const V (&k)[NP], int nf) {
-    if (nf & 1) return sorted_at<NP>(k, (nf - 1) / 2);
-    const double a = sorted_at<NP>(k, nf / 2 - 1);
-    const double b = sorted_at<NP>(k, nf / 2);
-    return (a + b) * 0.5;
-}
-
-// Hyndman-Fan type 7: h = (n - 1) p; Q = s[floor h] + frac(h) (s[floor h + 1] - s[floor h]).
-template <int NP, typename V>
-__device__ __forceinline__ double sorted_quantile7(const V (&k)[NP], int nf, double p) {
-    const double h = (double)(nf - 1) * p;
-    const double fl = floor(h);
-    const int lo = (int)fl;
-    const double frac = h - fl;
-    if (lo + 1 >= nf) return sorted_at<NP>(k, nf - 1);
-    const double a = sorted_at<NP>(k, lo);
-    const double b = sorted_at<NP>(k, lo + 1);
-    const double diff = b - a;
-    const double prod = frac * diff;
-    return a + prod;
-}
-
-// Median of |s - m| over the nf sorted finite values s, without sorting the
-// deviations: the `split` values below m give m - s[split - 1 - i], the
-// others s[split + i] - m, two ascending runs (each deviation rounds as
-// |s - m| does, since rounding is symmetric).  Order statistic k of their
-// union is found by bisecting how many of the k + 1 smallest come from the
-// first run.
-template <int NP, typename V>
-__device__ __forceinline__ double deviation_median(const V (&k)[NP], int nf, int split, double m) {
-    const int nl = split, nh = nf - split;
-    auto L = [&](int i) { return m - sorted_at<NP>(k, split - 1 - i); };
-    auto H = [&](int i) { return sorted_at<NP>(k, split + i) - m; };
-    const int q = (nf - 1) / 2;                     // lower middle position
-    int lo = q + 1 - nh > 0 ? q + 1 - nh : 0;
-    int hi = q + 1 < nl ? q + 1 : nl;
-    while (lo < hi) {                               // uniform bisection
-        const int mid = (lo + hi) >> 1;
-        if (L(mid) < H(q - mid)) lo = mid + 1;
-        else hi = mid;
-    }
-    const int i = lo;                               // q + 1 smallest: i from L, q + 1 - i from H
-    double a = -__builtin_huge_val();
-    if (i > 0) a = L(i - 1);
-    if (q - i >= 0) a = fmax(a, H(q - i));
-    if (nf & 1) return a;
-    double b = __builtin_huge_val();
-    if (i < nl) b = L(i);
-    if (q + 1 - i < nh) b = fmin(b, H(q + 1 - i));
-    return (a + b) * 0.5;
-}
-
-template <int NS, int KIND>
+template <int NL, int KIND>
 __global__ void __launch_bounds__(kVoteThreads) statistical_vote_wide_kernel(
     const char* __restrict__ ev, int64_t rstride, int64_t ustride, int R, int64_t n_units,
     double kappa, uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap,
@@ -342,94 +319,176 @@ __global__ void __launch_bounds__(kVoteThreads) statistical_vote_wide_kernel(
     // fp32 evidence is ordered and compared in fp32 (the widening to fp64 is
     // exact and monotonic); every arithmetic step is fp64
     using V = typename std::conditional<KIND == C3_EV_F32, float, double>::type;
-    const int lane = threadIdx.x & 63;
-    const int64_t u = (int64_t)blockIdx.x * kWideUnitsPerBlock + (threadIdx.x >> 6);
-    if (u >= n_units) return;  // the whole wave leaves together
-    V x[NS];
-    bool fin[NS];
-    uint64_t B[NS];
-    int nf = 0;
+    constexpr int NS = (NL + 3) / 4;
+    constexpr int kPad = 16 / (int)sizeof(V);       // rows start on different LDS banks
+    const V inf = (V)__builtin_huge_val();
+    __shared__ __align__(16) V sorted[kStatUnits][16 * NL + kPad];
+    const int lane = threadIdx.x & 63, l = lane & 15, q4 = lane >> 4;
+    const int slot = threadIdx.x >> 4;
+    const int64_t u = (int64_t)blockIdx.x * kStatUnits + slot;
+    // whole waves past the end leave; lanes of a wave that is partly past it
+    // decide the last unit again and write nothing
+    if ((int64_t)blockIdx.x * kStatUnits + (threadIdx.x >> 6) * 4 >= n_units) return;
+    const bool live = u < n_units;
+    const char* row = ev + (live ? u : n_units - 1) * ustride;
+    V x[NL], k[NL];
+    uint32_t bad = 0;                               // bit j: replica 16 j + l is not finite
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int r = 64 * s + lane;
-        const bool valid = r < R;
-        x[s] = valid ? *reinterpret_cast<const V*>(ev + u * ustride + (int64_t)r * rstride) : (V)0;
-        fin[s] = valid && __builtin_isfinite(x[s]);
-        nf += __builtin_popcountll(ballot64(fin[s]));
-        B[s] = ballot64(valid && !fin[s]);  // a non-finite value is an outlier
+    for (int j = 0; j < NL; ++j) {
+        const int r = 16 * j + l;
+        const bool valid = 16 * (j + 1) <= stat_least(NL) || r < R;
+        x[j] = *reinterpret_cast<const V*>(row + (int64_t)(valid ? r : 0) * rstride);
+        if (!valid) x[j] = inf;
+        k[j] = __builtin_isfinite(x[j]) ? x[j] : inf;
+        bad |= (uint32_t)(valid && !__builtin_isfinite(x[j])) << j;
+        x[j] = k[j];                                // excluded values stay +inf
     }
-    if (2 * nf <= R) {  // finite values are not a strict majority
+    int nf = R;
+    const bool some_bad = ballot64(bad != 0u) != 0ull;
+    if (some_bad) nf -= (int)row_sum_u32((uint32_t)__builtin_popcount(bad));
+    const bool ok = 2 * nf > R;                     // finite values are a strict majority
+    const int n = nf > 1 ? nf : 1;
+    sort_lane<NL>(k, 0);
+    sort_merge<2>(k, l);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) B[s] = 0;
-        wide_write<NS>(u, C3_INCONCLUSIVE, B, -1, status, bitmap, majority_idx);
-        return;
+    for (int i = 0; i < NL; ++i) sorted[slot][NL * l + i] = k[i];
+    wave_lds_sync();
+    const V* s = sorted[slot];
+    auto S = [&](int p) { return (double)s[p]; };
+
+    const int pm = (n - 1) / 2;
+    const V target = s[pm];                         // the lower median
+    const double a0 = (double)target, b0 = S(n / 2);
+    const double m = (n & 1) ? a0 : (a0 + b0) * 0.5;
+    // values below the lower median, its holders, and the first holder
+    uint32_t cnt = 0, holder = 0xFFFFu;
+#pragma unroll
+    for (int j = NL - 1; j >= 0; --j) {
+        cnt += (uint32_t)(x[j] < target);
+        cnt += x[j] == target ? 0x10000u : 0u;
+        holder = x[j] == target ? (uint32_t)(16 * j + l) : holder;
     }
-    constexpr int NP = NS == 3 ? 4 : NS;
-    V k[NP];
+    cnt = row_sum_u32(cnt);
+    const int less = (int)(cnt & 0xFFFFu), same = (int)(cnt >> 16);
+    int mj = (int)row_min_u32(holder);
+    if (ballot64(same > 1) != 0ull) {
+        // ties: position pm of the stable (value, replica) order is holder
+        // pm - less, counted by replica index
+        int want = pm - less;
+        mj = -1;
 #pragma unroll
-    for (int i = 0; i < NP; ++i)
-        k[i] = i < NS && fin[i < NS ? i : 0] ? x[i < NS ? i : 0] : (V)__builtin_huge_val();
-    wave_sort<NP, 2>(k, lane);
-    const double m = sorted_median<NP>(k, nf);
-    int split = 0;                                  // finite values below m
+        for (int j = 0; j < NL; ++j) {
+            uint32_t eq = (uint32_t)(ballot64(x[j] == target) >> (16 * q4)) & 0xFFFFu;
+            const int c = __builtin_popcount(eq);
+            if (mj < 0 && want < c) {
+                for (int w = 0; w < want; ++w) eq &= eq - 1u;
+                mj = 16 * j + __builtin_ctz(eq | 0x10000u);
+            }
+            want -= c;
+        }
+    }
+    // The values below m: no value lies between the middle two, so they are
+    // those up to the lower middle one, or, where that equals m, those below
+    // it.  (The last two cases only where the sum of the middle two overflows.)
+    const int split = a0 < m ? (b0 < m ? n : pm + 1) : (a0 > m ? 0 : less);
+
+    // Median of |s - m| over the n sorted values without sorting the
+    // deviations: the `split` values below m give m - s[split - 1 - i], the
+    // others s[split + i] - m, two ascending runs (each deviation rounds as
+    // |s - m| does, since rounding is symmetric).  How many of the pm + 1
+    // smallest come from the first run is found by two rounds of sixteen
+    // probes.
+    const int nl = split, nh = n - split;
+    auto at = [&](int p) { return S(p < 0 ? 0 : p < 16 * NL ? p : 16 * NL - 1); };
+    auto L = [&](int i) { return m - at(split - 1 - i); };
+    auto H = [&](int i) { return at(split + i) - m; };
+    int lo = pm + 1 - nh > 0 ? pm + 1 - nh : 0;
+    int hi = pm + 1 < nl ? pm + 1 : nl;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) split += __builtin_popcountll(ballot64(fin[s] && (double)x[s] < m));
-    double d = deviation_median<NP>(k, nf, split, m);
+    for (int round = 0; round < 2; ++round) {
+        const int step = hi > lo ? (hi - lo + 15) >> 4 : 0;
+        const int p = lo + l * step;
+        const bool from_l = p < hi && L(p) < H(pm - p);
+        const int c = __builtin_popcount((uint32_t)(ballot64(from_l) >> (16 * q4)) & 0xFFFFu);
+        const int last = lo + (c - 1) * step;
+        hi = c > 0 ? (hi < last + step ? hi : last + step) : lo;
+        lo = c > 0 ? last + 1 : lo;
+    }
+    double d;
+    {
+        const double ninf = -__builtin_huge_val(), pinf = __builtin_huge_val();
+        const double a = fmax(lo > 0 ? L(lo - 1) : ninf, pm - lo >= 0 ? H(pm - lo) : ninf);
+        const double b = fmin(lo < nl ? L(lo) : pinf, pm + 1 - lo < nh ? H(pm + 1 - lo) : pinf);
+        d = (n & 1) ? a : (a + b) * 0.5;
+    }
+    const double s0 = S(0), s1 = S(n - 1);
     if (d == 0.0) {
-        const double q3 = sorted_quantile7<NP>(k, nf, 0.75);
-        const double q1 = sorted_quantile7<NP>(k, nf, 0.25);
-        d = (q3 - q1) * 0.5;
-    }
-    if (d == 0.0) {
-        const double hi = sorted_at<NP>(k, nf - 1);
-        const double lo = sorted_at<NP>(k, 0);
-        d = (hi - lo) / (double)nf;
+        // Hyndman-Fan type 7: h = (n - 1) p; Q = s[floor h] + frac(h) (s[floor h + 1] - s[floor h])
+        auto quantile7 = [&](double p) {
+            const double h = (double)(n - 1) * p;
+            const double fl = floor(h);
+            const int at_lo = (int)fl;
+            const double frac = h - fl;
+            if (at_lo + 1 >= n) return s1;
+            const double a = S(at_lo);
+            const double diff = S(at_lo + 1) - a;
+            const double prod = frac * diff;
+            return a + prod;
+        };
+        d = (quantile7(0.75) - quantile7(0.25)) * 0.5;
+        if (d == 0.0) d = (s1 - s0) / (double)n;
     }
     const double thr = kappa * d;
+    // the largest deviation is that of an end: the usual unit flags nothing
+    const bool far = ok && d != 0.0 && fmax(fabs(s0 - m), fabs(s1 - m)) > thr;
+    uint64_t B[NS];
+#pragma unroll
+    for (int w = 0; w < NS; ++w) B[w] = 0;
     bool any = false;
+    if (ballot64(far || bad != 0u) != 0ull) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const bool flag = d != 0.0 && fin[s] && fabs((double)x[s] - m) > thr;
-        B[s] |= ballot64(flag);
-        any = any || B[s] != 0;
-    }
-    // lower-median replica: position (nf - 1) / 2 of the stable (value,
-    // replica) order is the want-th replica, by index, holding the value
-    // there, after the replicas holding smaller values
-    const int pm = (nf - 1) / 2;
-    const V target = (V)sorted_at<NP>(k, pm);
-    int want = pm;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) want -= __builtin_popcountll(ballot64(fin[s] && x[s] < target));
-    int mj = -1;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        uint64_t eq = ballot64(fin[s] && x[s] == target);
-        const int c = __builtin_popcountll(eq);
-        if (mj < 0 && want < c) {
-            for (int w = 0; w < want; ++w) eq &= eq - 1ull;
-            mj = 64 * s + __builtin_ctzll(eq);
+        for (int j = 0; j < NL; ++j) {
+            // a non-finite value is an outlier
+            const bool flag = ok && (((bad >> j) & 1u) != 0u ||
+                                     (far && x[j] < inf && fabs((double)x[j] - m) > thr));
+            const uint32_t bits = (uint32_t)(ballot64(flag) >> (16 * q4)) & 0xFFFFu;
+            B[j >> 2] |= (uint64_t)bits << (16 * (j & 3));
+            any = any || bits != 0u;
         }
-        want -= c;
     }
-    wide_write<NS>(u, any ? C3_ATTRIBUTED : C3_AGREE, B, mj, status, bitmap, majority_idx);
+    if (!live) return;
+    if (l == 0) {
+        status[u] = !ok ? (uint8_t)C3_INCONCLUSIVE : any ? (uint8_t)C3_ATTRIBUTED : (uint8_t)C3_AGREE;
+        majority_idx[u] = ok ? mj : -1;
+    }
+#pragma unroll
+    for (int w = 0; w < NS; ++w)
+        if (l == w) bitmap[u * NS + w] = B[w];
 }
 
 template <int NS>
-static void launch_wide(const char* e, int kind, int64_t rstride, int64_t ustride, int R,
-                        int64_t n_units, int mode, double kappa, uint8_t* status, uint64_t* bitmap,
-                        int32_t* majority_idx, hipStream_t stream, unsigned blocks) {
-    if (mode == C3_EXACT)
-        hipLaunchKernelGGL(exact_vote_wide_kernel<NS>, dim3(blocks), dim3(kVoteThreads), 0, stream,
-                           e, kind, rstride, ustride, R, n_units, status, bitmap, majority_idx);
-    else if (kind == C3_EV_F32)
-        hipLaunchKernelGGL((statistical_vote_wide_kernel<NS, C3_EV_F32>), dim3(blocks),
+static void launch_exact_wide(const char* e, int kind, int64_t rstride, int64_t ustride, int R,
+                              int64_t n_units, uint8_t* status, uint64_t* bitmap,
+                              int32_t* majority_idx, hipStream_t stream, unsigned blocks) {
+    hipLaunchKernelGGL(exact_vote_wide_kernel<NS>, dim3(blocks), dim3(kVoteThreads), 0, stream, e,
+                       kind, rstride, ustride, R, n_units, status, bitmap, majority_idx);
+}
+
+template <int NL>
+static hipError_t launch_stat(const char* e, int kind, int64_t rstride, int64_t ustride, int R,
+                              int64_t n_units, double kappa, uint8_t* status, uint64_t* bitmap,
+                              int32_t* majority_idx, hipStream_t stream) {
+    const int64_t blocks = (n_units + kStatUnits - 1) / kStatUnits;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    if (kind == C3_EV_F32)
+        hipLaunchKernelGGL((statistical_vote_wide_kernel<NL, C3_EV_F32>), dim3((unsigned)blocks),
                            dim3(kVoteThreads), 0, stream, e, rstride, ustride, R, n_units, kappa,
                            status, bitmap, majority_idx);
     else
-        hipLaunchKernelGGL((statistical_vote_wide_kernel<NS, C3_EV_F64>), dim3(blocks),
+        hipLaunchKernelGGL((statistical_vote_wide_kernel<NL, C3_EV_F64>), dim3((unsigned)blocks),
                            dim3(kVoteThreads), 0, stream, e, rstride, ustride, R, n_units, kappa,
                            status, bitmap, majority_idx);
+    return hipGetLastError();
 }
 
 template <int NMAX>
@@ -457,10 +516,16 @@ hipError_t launch_consensus(const void* evidence, int kind, int64_t rstride, int
                             int64_t n_units, int mode, double kappa, uint8_t* status,
                             uint64_t* bitmap, int32_t* majority_idx, hipStream_t stream) {
     if (n_units <= 0) return hipSuccess;
-    // Up to 32 replicas one thread decides a unit: against a wave per unit,
-    // 0.035-0.044 against 0.092-0.102 ms per 262,144 units of fp32 times at
-    // R = 17-32, 0.055-0.072 against 0.106-0.117 for fp64, 0.027-0.046
-    // against 0.044-0.046 for 64-bit fingerprints; the same results.
+    // Otherwise, up to 32 replicas one thread decides a unit: exact, 0.027-0.046
+    // ms per 262,144 units of 64-bit fingerprints at R = 17-32 against
+    // 0.044-0.046 for a wave per unit; the same results.
+    // fp64 times of 17 to 32 replicas: sixteen lanes a unit, 36 us per 262,144
+    // units at R = 17, 24 and 32, against 46, 38 and 43 for a thread per unit
+    // (256 VGPRs); in fp32 a thread per unit is the faster one, 20-24 against
+    // 30 us.
+    if (mode == C3_STATISTICAL && kind == C3_EV_F64 && R >= stat_least(2) && R <= 32)
+        return launch_stat<2>(static_cast<const char*>(evidence), kind, rstride, ustride, R, n_units,
+                              kappa, status, bitmap, majority_idx, stream);
     if (R <= 32) {
         const int64_t blocks = (n_units + kVoteThreads - 1) / kVoteThreads;
         if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -479,22 +544,32 @@ hipError_t launch_consensus(const void* evidence, int kind, int64_t rstride, int
                              majority_idx, stream, (unsigned)blocks);
         return hipGetLastError();
     }
-    const int64_t blocks = (n_units + kWideUnitsPerBlock - 1) / kWideUnitsPerBlock;
-    if (blocks > 0x7FFFFFFF || R > C3_MAX_PEERS) return hipErrorInvalidValue;
+    if (R > C3_MAX_PEERS) return hipErrorInvalidValue;
     const char* e = static_cast<const char*>(evidence);
+    if (mode == C3_STATISTICAL) {
+        if (R <= 64)
+            return launch_stat<4>(e, kind, rstride, ustride, R, n_units, kappa, status, bitmap,
+                                  majority_idx, stream);
+        if (R <= 128)
+            return launch_stat<8>(e, kind, rstride, ustride, R, n_units, kappa, status, bitmap,
+                                  majority_idx, stream);
+        if (R <= 192)
+            return launch_stat<12>(e, kind, rstride, ustride, R, n_units, kappa, status, bitmap,
+                                   majority_idx, stream);
+        return launch_stat<16>(e, kind, rstride, ustride, R, n_units, kappa, status, bitmap,
+                               majority_idx, stream);
+    }
+    const int64_t blocks = (n_units + kWideUnitsPerBlock - 1) / kWideUnitsPerBlock;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const unsigned nb = (unsigned)blocks;
     if (R <= 64)
-        launch_wide<1>(e, kind, rstride, ustride, R, n_units, mode, kappa, status, bitmap,
-                       majority_idx, stream, nb);
+        launch_exact_wide<1>(e, kind, rstride, ustride, R, n_units, status, bitmap, majority_idx, stream, nb);
     else if (R <= 128)
-        launch_wide<2>(e, kind, rstride, ustride, R, n_units, mode, kappa, status, bitmap,
-                       majority_idx, stream, nb);
+        launch_exact_wide<2>(e, kind, rstride, ustride, R, n_units, status, bitmap, majority_idx, stream, nb);
     else if (R <= 192)
-        launch_wide<3>(e, kind, rstride, ustride, R, n_units, mode, kappa, status, bitmap,
-                       majority_idx, stream, nb);
+        launch_exact_wide<3>(e, kind, rstride, ustride, R, n_units, status, bitmap, majority_idx, stream, nb);
     else
-        launch_wide<4>(e, kind, rstride, ustride, R, n_units, mode, kappa, status, bitmap,
-                       majority_idx, stream, nb);
+        launch_exact_wide<4>(e, kind, rstride, ustride, R, n_units, status, bitmap, majority_idx, stream, nb);
     return hipGetLastError();
 }
 
