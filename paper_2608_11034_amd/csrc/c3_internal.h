@@ -98,12 +98,13 @@ int localize_check(const uint8_t* status, const uint64_t* bitmap, const int32_t*
                    const c3_outlier_t* outliers, int64_t out_cap, const int64_t* undecided,
                    int64_t und_cap, const int64_t* counts);
 
+// shared_ws: ws is the device-wide scratch array, left alone up to 32,768 units.
 size_t localize_ws_bytes(int64_t n_units);
 hipError_t launch_localize(const uint8_t* status, const uint64_t* bitmap,
                            const int32_t* majority_idx, const c3_chunk_record_t* records, int R,
                            int64_t n_units, c3_outlier_t* outliers, int64_t out_cap,
                            int64_t* undecided, int64_t und_cap, int64_t* counts, void* ws,
-                           hipStream_t stream);
+                           hipStream_t stream, bool shared_ws = false);
 
 // Read-only probe over `bytes` (a multiple of 1024) in tiles of tile_bytes;
 // writes the xor of each tile's 64-bit words to checksum[tile].

@@ -2,7 +2,10 @@
 // (unit, replica) outliers with both replicas' numerical summaries, plus the
 // undecided (Inconclusive) units.
 //
-// Deterministic three-pass compaction with no atomics:
+// Deterministic compaction with no atomics.  Up to kSingleMaxUnits one
+// workgroup walks the units; up to kWordMaxUnits two launches (count and emit,
+// each emitting workgroup adding up the counts of the segments before its
+// own); above that three:
 //   1. count   -- each workgroup counts outlier bits, undecided units and
 //                 attributed units over its segment of kSegUnits units;
 //   2. scan    -- one workgroup turns the segment counts into exclusive
@@ -147,7 +150,13 @@ __device__ inline void emit_units(const uint8_t* __restrict__ status,
 // the fused check) walks the units in rounds, one launch instead of three.
 constexpr int kSingleThreads = 1024;
 constexpr int kSinglePerThread = 4;  // 8 spilled registers at this block size
-constexpr int64_t kSingleMaxUnits = 8 * (int64_t)kSingleThreads * kSinglePerThread;
+// One round of the workgroup.  Units of 8 replicas, us per call, one workgroup
+// against two launches: 4,096 units 10.4 (one call's host work), 5,000 14.7 /
+// 13.7, 8,192 18.3 / 13.9, 16,384 of 192 replicas 68 / 15, 32,768 70 / 13.9.
+constexpr int64_t kSingleMaxUnits = (int64_t)kSingleThreads * kSinglePerThread;
+// with the device-wide scratch array, which concurrent calls would share: up to
+// here the call does not touch it
+constexpr int64_t kSingleMaxShared = 8 * kSingleMaxUnits;
 
 template <bool WIDE>
 __global__ void __launch_bounds__(kSingleThreads) localize_single_kernel(
@@ -160,6 +169,158 @@ __global__ void __launch_bounds__(kSingleThreads) localize_single_kernel(
                                                            undecided, und_cap, counts);
 }
 
+// ---------------------------------------------------------------------------
+// Two launches for middle sizes.  A segment is kWordUnits units, four per
+// thread, so that 65,536 units occupy 64 workgroups (the 2,048-unit segments
+// of the three launches 32); its counts are one word, and every emitting
+// workgroup sums the at most kWordMaxSegs words before its own, 8 KiB from
+// the L2, in place of the scan launch.  262,144 units, us per call, three
+// launches / two: 25.8 / 14.8 at R = 17, 34.5 / 15.9 at 192, 40.4 / 19.3 at 256.
+// ---------------------------------------------------------------------------
+constexpr int kWordPerThread = 4;
+constexpr int64_t kWordUnits = (int64_t)kLocThreads * kWordPerThread;
+constexpr int64_t kWordMaxSegs = 1024;
+constexpr int64_t kWordMaxUnits = kWordUnits * kWordMaxSegs;
+static_assert(kWordUnits * C3_MAX_PEERS <= kOutMask && kWordUnits <= kUnitMask, "packed counts");
+
+// Outliers, undecided and attributed units of one unit, packed.
+template <bool WIDE>
+__device__ inline uint64_t unit_word(uint8_t st, uint64_t bits) {
+    if (st == C3_INCONCLUSIVE) return 1ull << kOutBits;
+    const uint64_t n = WIDE ? bits : (uint64_t)__builtin_popcountll(bits);
+    return n | ((uint64_t)(n != 0) << (kOutBits + kUnitBits));
+}
+
+// A unit's bitmap word (one-word bitmaps) or its number of set bits.
+template <bool WIDE>
+__device__ inline uint64_t unit_bits(const uint64_t* __restrict__ bitmap, int W, int64_t u) {
+    if constexpr (WIDE) return (uint64_t)unit_popcount(bitmap, W, u);
+    else return bitmap[u];
+}
+
+template <bool WIDE>
+__global__ void __launch_bounds__(kLocThreads) localize_count_words_kernel(
+    const uint8_t* __restrict__ status, const uint64_t* __restrict__ bitmap, int W,
+    int64_t n_units, uint64_t* __restrict__ words) {
+    __shared__ uint64_t lds[kLocThreads / 64];
+    const int64_t base = (int64_t)blockIdx.x * kWordUnits + threadIdx.x;
+    uint8_t st[kWordPerThread];
+    uint64_t b[kWordPerThread];
+#pragma unroll
+    for (int i = 0; i < kWordPerThread; ++i) {          // any order does for a count: adjacent units
+        const int64_t u = base + (int64_t)i * kLocThreads;
+        st[i] = u < n_units ? status[u] : (uint8_t)C3_AGREE;
+        b[i] = u < n_units ? unit_bits<WIDE>(bitmap, W, u) : 0ull;
+    }
+    uint64_t w = 0;
+#pragma unroll
+    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<WIDE>(st[i], b[i]);
+    w = row_sum(fold16(w, w));
+    w = fold32(w, w);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kLocThreads / 64; ++i) w += lds[i];
+        words[blockIdx.x] = w;
+    }
+}
+
+template <bool WIDE>
+__global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
+    const uint8_t* __restrict__ status, const uint64_t* __restrict__ bitmap,
+    const int32_t* __restrict__ majority_idx, const c3_chunk_record_t* __restrict__ records, int R,
+    int W, int64_t n_units, const uint64_t* __restrict__ words, c3_outlier_t* __restrict__ outliers,
+    int64_t out_cap, int64_t* __restrict__ undecided, int64_t und_cap, int64_t* __restrict__ counts) {
+    __shared__ int64_t lds[kLocThreads / 64];
+    __shared__ uint64_t before[kLocThreads / 64][3];
+    const int64_t u0 = (int64_t)blockIdx.x * kWordUnits + (int64_t)threadIdx.x * kWordPerThread;
+    uint8_t st[kWordPerThread];
+    uint64_t b[kWordPerThread];
+#pragma unroll
+    for (int i = 0; i < kWordPerThread; ++i) {
+        const int64_t u = u0 + i;
+        st[i] = u < n_units ? status[u] : (uint8_t)C3_AGREE;
+        b[i] = u < n_units ? unit_bits<WIDE>(bitmap, W, u) : 0ull;
+    }
+    // the segments before this one; a sum of words could overflow a field
+    uint64_t so = 0, su = 0, sa = 0;
+    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kLocThreads) {
+        const uint64_t w = words[i];
+        so += w & kOutMask;
+        su += (w >> kOutBits) & kUnitMask;
+        sa += w >> (kOutBits + kUnitBits);
+    }
+    so = row_sum(fold16(so, so));
+    su = row_sum(fold16(su, su));
+    sa = row_sum(fold16(sa, sa));
+    so = fold32(so, so);
+    su = fold32(su, su);
+    sa = fold32(sa, sa);
+    if ((threadIdx.x & 63) == 0) {
+        before[threadIdx.x >> 6][0] = so;
+        before[threadIdx.x >> 6][1] = su;
+        before[threadIdx.x >> 6][2] = sa;
+    }
+    uint64_t w = 0;
+#pragma unroll
+    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<WIDE>(st[i], b[i]);
+    int64_t total;
+    const uint64_t excl = (uint64_t)block_inclusive_scan<kLocThreads>((int64_t)w, lds, total) - w;
+    int64_t po = 0, pu = 0, pa = 0;                     // block_inclusive_scan ended with a barrier
+#pragma unroll
+    for (int i = 0; i < kLocThreads / 64; ++i) {
+        po += (int64_t)before[i][0];
+        pu += (int64_t)before[i][1];
+        pa += (int64_t)before[i][2];
+    }
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) {
+        counts[0] = po + (total & kOutMask);
+        counts[1] = pu + ((total >> kOutBits) & kUnitMask);
+        counts[2] = pa + (int64_t)((uint64_t)total >> (kOutBits + kUnitBits));
+    }
+    po += (int64_t)(excl & kOutMask);
+    pu += (int64_t)((excl >> kOutBits) & kUnitMask);
+#pragma unroll
+    for (int i = 0; i < kWordPerThread; ++i) {
+        const int64_t u = u0 + i;
+        if (st[i] == C3_INCONCLUSIVE) {
+            if (pu < und_cap) undecided[pu] = u;
+            ++pu;
+            continue;
+        }
+        if (b[i] == 0ull) continue;
+        const int32_t mj = majority_idx[u];
+        for (int j = 0; j < (WIDE ? W : 1); ++j) {
+            uint64_t bits = WIDE ? bitmap[u * W + j] : b[i];
+            while (bits) {
+                const int r = 64 * j + __builtin_ctzll(bits);
+                bits &= bits - 1;
+                if (po < out_cap) write_outlier(&outliers[po], u, r, mj, records, R, n_units);
+                ++po;
+            }
+        }
+    }
+}
+
+template <bool WIDE>
+static hipError_t launch_words(const uint8_t* status, const uint64_t* bitmap,
+                               const int32_t* majority_idx, const c3_chunk_record_t* records, int R,
+                               int W, int64_t n_units, c3_outlier_t* outliers, int64_t out_cap,
+                               int64_t* undecided, int64_t und_cap, int64_t* counts, void* ws,
+                               hipStream_t stream) {
+    const unsigned n_seg = (unsigned)((n_units + kWordUnits - 1) / kWordUnits);
+    uint64_t* words = static_cast<uint64_t*>(ws);
+    hipLaunchKernelGGL(localize_count_words_kernel<WIDE>, dim3(n_seg), dim3(kLocThreads), 0, stream,
+                       status, bitmap, W, n_units, words);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(localize_emit_words_kernel<WIDE>, dim3(n_seg), dim3(kLocThreads), 0, stream,
+                       status, bitmap, majority_idx, records, R, W, n_units, words, outliers,
+                       out_cap, undecided, und_cap, counts);
+    return hipGetLastError();
+}
+
+// (the words of the two launches, n_units / 128 bytes, take less)
 size_t localize_ws_bytes(int64_t n_units) {
     const int64_t n_seg = n_units > 0 ? (n_units + kSegUnits - 1) / kSegUnits : 0;
     return (size_t)(n_seg * (int64_t)sizeof(SegCount)) + 256;
@@ -169,9 +330,9 @@ hipError_t launch_localize(const uint8_t* status, const uint64_t* bitmap,
                            const int32_t* majority_idx, const c3_chunk_record_t* records, int R,
                            int64_t n_units, c3_outlier_t* outliers, int64_t out_cap,
                            int64_t* undecided, int64_t und_cap, int64_t* counts, void* ws,
-                           hipStream_t stream) {
+                           hipStream_t stream, bool shared_ws) {
     const int W = (R + 63) / 64;
-    if (n_units <= kSingleMaxUnits) {
+    if (n_units <= (shared_ws ? kSingleMaxShared : kSingleMaxUnits)) {
         if (W == 1)
             hipLaunchKernelGGL(localize_single_kernel<false>, dim3(1), dim3(kSingleThreads), 0,
                                stream, status, bitmap, majority_idx, records, R, W, n_units,
@@ -182,6 +343,11 @@ hipError_t launch_localize(const uint8_t* status, const uint64_t* bitmap,
                                outliers, out_cap, undecided, und_cap, counts);
         return hipGetLastError();
     }
+    if (n_units <= kWordMaxUnits)
+        return W == 1 ? launch_words<false>(status, bitmap, majority_idx, records, R, W, n_units,
+                                            outliers, out_cap, undecided, und_cap, counts, ws, stream)
+                      : launch_words<true>(status, bitmap, majority_idx, records, R, W, n_units,
+                                           outliers, out_cap, undecided, und_cap, counts, ws, stream);
     const int64_t n_seg = (n_units + kSegUnits - 1) / kSegUnits;
     if (n_seg > 0x7FFFFFFF) return hipErrorInvalidValue;
     SegCount* seg = static_cast<SegCount*>(ws);
@@ -269,6 +435,7 @@ extern "C" int c3_localize_noalloc(const uint8_t* status, const uint64_t* bitmap
     void* ws = nullptr;
     if (scratch_address(s, &ws) != hipSuccess) return C3_E_HIP;
     const hipError_t e = c3::launch_localize(status, bitmap, majority_idx, records, R, n_units,
-                                             outliers, out_cap, undecided, und_cap, counts, ws, s);
+                                             outliers, out_cap, undecided, und_cap, counts, ws, s,
+                                             true);
     return e == hipSuccess ? C3_OK : C3_E_HIP;
 }
