@@ -743,7 +743,6 @@ def bench_optimizer(args, torch, workloads, c3, dev):
     w = workloads.make(6, device=dev, scale="full")
     torch.cuda.synchronize()
     chk = c3.OptimizerBoundaryCheck(*w.state, slice_elems=w.slice_elems, tile_bytes=args.tile)
-    tile = chk.st.tile_bytes or 65536
     hp = c3.adamw_hparams(w.hparams["lr"], w.hparams["betas"], w.hparams["eps"],
                           w.hparams["weight_decay"], w.hparams["step"])
     n_slices = -(-w.numel // w.slice_elems)
@@ -774,11 +773,10 @@ def bench_optimizer(args, torch, workloads, c3, dev):
     ms = e0.elapsed_time(e1) / args.steps
     n = w.slice_elems
     R = w.R
-    # Per-kernel durations in the check's launch configuration (slice k0, row
-    # stride S, the same signature tile).  These kernels last microseconds:
-    # a per-launch event pair would add several microseconds of its own, and
-    # the host needs about as long to enqueue one call as the GPU to run it.
-    # So a 4 GiB device copy is queued first, a run of back-to-back launches
+    # Duration of the check's two kernels together, without the host: they
+    # last microseconds, a per-launch event pair would add several of its own,
+    # and the host needs about as long to enqueue one call as the GPU to run
+    # it.  So a 4 GiB device copy is queued first, a run of back-to-back checks
     # is enqueued behind it between one pair of HIP events on the launch
     # stream, and the interval is divided by the run's length.
     head_src = torch.empty(1 << 32, dtype=torch.uint8, device=dev)
@@ -788,34 +786,21 @@ def bench_optimizer(args, torch, workloads, c3, dev):
     def batch_ms(fn):
         a = torch.cuda.Event(enable_timing=True)
         b = torch.cuda.Event(enable_timing=True)
-        fn(0, None, None)
+        fn(0)
         torch.cuda.synchronize()
         head_dst.copy_(head_src)
         a.record()
         for i in range(batch):
-            fn(i, a if i == 0 else None, b if i == batch - 1 else None)
+            fn(i)
         b.record()
         torch.cuda.synchronize()
         return a.elapsed_time(b) / batch
 
-    k_adamw = batch_ms(lambda i, x, y: c3.adamw_slice(*w.state, k0 * n, n, hp, out=chk.updated,
-                                                       out_stride=n, _tables=chk.tables))
-    views = [[x[r][k0 * n:(k0 + 1) * n] for x in w.state] + [chk.updated[r, j] for j in range(3)]
-             for r in range(R)]
-    plan = c3.SignaturePlan(views, n * 4, tile)
-    rec = plan.new_records()
-    sws = plan.new_workspace()
-    plan.run(rec, sws)
-    # the staged plan is reused (no fetch kernel); the library records the
-    # first event right before the first signature kernel, and the last one
-    # is recorded again after the loop, behind the last partial combine
-    k_sig = batch_ms(lambda i, a, b: plan.run(rec, sws, plan_staged=True, ev_begin=a, ev_end=b))
+    k_check = batch_ms(lambda i: chk.run(k0 + i, hp))
     del head_src, head_dst
-    adamw_bytes = R * n * 28                 # read p, g, m, v; write p', m', v'
-    sig_bytes = R * 7 * n * 4                # the seven signed slices per replica
-    kern = {"adamw_slice_vec4_kernel": (k_adamw, adamw_bytes),
-            "signature_kernel+finalize_kernel": (k_sig, sig_bytes)}
-    dom = max(kern, key=lambda k: kern[k][0])
+    # read p, g, m, v; write p', m', v' (which are signed from registers)
+    kern = {"optimizer_slices_kernel+optimizer_tail_kernel": (k_check, R * n * 28)}
+    dom = next(iter(kern))
     d_ms, d_bytes = kern[dom]
     cpu = None
     if not args.no_cpu_baseline:
@@ -848,7 +833,7 @@ def bench_optimizer(args, torch, workloads, c3, dev):
         "dtype": "f32+u64",
         "data": "synthetic",
         "config": {"workload": w.name, "R": R, "params_per_replica": w.numel,
-                   "slice_elems": n, "slices": n_slices, "tile_bytes": tile,
+                   "slice_elems": n, "slices": n_slices, "tile_bytes": args.tile,
                    "outliers_at_fault_slices": {str(k): v for k, v in found.items()}},
         "roofline": {"bound": "hbm", "achieved": round(d_bytes / (d_ms * 1e-3) / 1e9, 2),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",

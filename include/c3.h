@@ -37,8 +37,8 @@
  *     can be captured.  c3_signature stages its plan from host memory when
  *     called; capture it with C3_OPT_PLAN_STAGED after an eager call with
  *     the same arguments staged the plan into the workspace, and each
- *     replay reads the tensors' current bytes.  c3_optimizer_check stages a
- *     new plan per slice and is not meant for capture.
+ *     replay reads the tensors' current bytes.  c3_optimizer_check only
+ *     launches kernels; a captured one checks the same slice at each replay.
  */
 #ifndef C3_H_
 #define C3_H_
@@ -343,7 +343,8 @@ typedef struct {
     int64_t numel;
     int64_t slice_elems;             /* S: multiple of 256 (65536 in Sec. 9) */
     uint64_t tile_bytes;             /* signature tile: a power of two >= 1024,
-                                        lowered until it divides 4 S; 0 = 64 KiB */
+                                        lowered until it divides 4 S; 0 = one of
+                                        at most 64 KiB, for 32 tiles or more */
 } c3_optimizer_state_t;
 
 /* Device outputs of c3_optimizer_check, all caller-owned.  Unit u of the
@@ -374,9 +375,10 @@ size_t c3_optimizer_check_workspace_size(const c3_optimizer_state_t *st);
  *      four input slices, read in place, and the three updated slices),
  *      one chunk each;
  *   3. c3_consensus (exact) over the seven units; 4. c3_localize.
- * The outputs are those of these four calls; after the streaming kernel of
- * step 2, one single-workgroup kernel combines the tile partials into the
- * records, votes and writes the lists (R <= 64: always).
+ * The outputs are those of these four calls (the signature with this tile).
+ * Two launches: one replays and signs in a single pass over the inputs, and
+ * one workgroup combines the tile partials into the records, votes and writes
+ * the lists.
  * Healthy data-parallel replicas agree on all seven units; an outlier on an
  * input unit names replicas whose state diverged before the step, one on an
  * output unit only names replicas whose replayed update differs.

@@ -8,7 +8,6 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
-#include <functional>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -169,9 +168,7 @@ inline bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)
 // stream.  A slot is reused only after the kernel that read it has
 // completed: the plan fetch kernel stores the slot's sequence number into a
 // pinned coherent word when it is done, which costs nothing on the stream
-// (an event recorded per call idled the GPU about 6 us per call); kernels
-// that copy a plan as a side job (the optimizer check's replay) record an
-// event instead.  A plan larger than a slot (256 KB, about 1,500 tensors at
+// (an event recorded per call idled the GPU about 6 us per call).  A plan larger than a slot (256 KB, about 1,500 tensors at
 // R = 8) falls back to a pageable copy.  The buffer
 // holds whole 16-byte words, so the staged size is rounded up to 16.
 // ---------------------------------------------------------------------------
@@ -187,8 +184,6 @@ struct Stager {
     uint64_t* seen = nullptr;                 // [kStageSlots][kFetchBlocks], written by the fetch kernel
     uint64_t issued[kStageSlots] = {};        // sequence of the last fetch from each slot
     int blocks[kStageSlots] = {};             // its workgroups, each of which signals
-    hipEvent_t ev[kStageSlots] = {};
-    bool ev_pending[kStageSlots] = {};
     uint64_t seq = 0;
     int next = 0;
 };
@@ -196,24 +191,11 @@ struct Stager {
 Stager g_stagers[kMaxDevices];
 
 // Copies `bytes` of `src` to device `dst` on `s`; returns a HIP error code.
-// `enqueue(h, seen, seq)` launches the kernel that copies the staged bytes
-// from the pinned slot h to dst (with whatever else it does); if it can
-// store `seq` into `seen` when done (plan_fetch_kernel) it returns true in
-// `signals`, else an event marks the slot.  When staging falls back to a
-// pageable copy, that copy is enqueued first and enqueue(nullptr, ...) after
-// it.
-using Enqueue = std::function<hipError_t(const void*, uint64_t*, uint64_t, bool&)>;
-
-hipError_t stage_to_device(void* dst, const void* src, size_t bytes, hipStream_t s,
-                           const Enqueue& enqueue) {
+hipError_t stage_to_device(void* dst, const void* src, size_t bytes, hipStream_t s) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    bool unused = false;
-    auto pageable = [&]() {
-        hipError_t e2 = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
-        return e2 != hipSuccess ? e2 : enqueue(nullptr, nullptr, 0, unused);
-    };
+    auto pageable = [&]() { return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s); };
     if (dev < 0 || dev >= kMaxDevices || bytes > kStageSlotBytes) return pageable();
     Stager& st = g_stagers[dev];
     std::lock_guard<std::mutex> lock(st.mu);
@@ -226,18 +208,11 @@ hipError_t stage_to_device(void* dst, const void* src, size_t bytes, hipStream_t
             st.failed = true;
         } else {
             for (int i = 0; i < kStageSlots * c3::kFetchBlocks; ++i) st.seen[i] = 0;
-            for (int i = 0; i < kStageSlots && !st.failed; ++i)
-                if (hipEventCreateWithFlags(&st.ev[i], hipEventDisableTiming) != hipSuccess)
-                    st.failed = true;
-            st.ready = !st.failed;
+            st.ready = true;
         }
     }
     if (!st.ready) return pageable();
     const int slot = st.next;
-    if (st.ev_pending[slot]) {
-        if ((e = hipEventSynchronize(st.ev[slot])) != hipSuccess) return e;
-        st.ev_pending[slot] = false;
-    }
     // The fetch from this slot kStageSlots calls ago may still be queued
     // when the host runs far ahead of the GPU: wait for it, which keeps the
     // host that many calls ahead (a pageable copy instead would wait for the
@@ -262,27 +237,10 @@ hipError_t stage_to_device(void* dst, const void* src, size_t bytes, hipStream_t
     unsigned char* h = st.host + (size_t)slot * kStageSlotBytes;
     memcpy(h, src, bytes);
     const uint64_t seq = ++st.seq;
-    bool signals = false;
-    if ((e = enqueue(h, seen, seq, signals)) != hipSuccess) return e;
-    if (signals) {
-        st.issued[slot] = seq;
-        st.blocks[slot] = c3::plan_fetch_blocks(bytes);
-    } else {
-        st.issued[slot] = 0;
-        st.blocks[slot] = 0;
-        if ((e = hipEventRecord(st.ev[slot], s)) != hipSuccess) return e;
-        st.ev_pending[slot] = true;
-    }
+    if ((e = c3::launch_plan_fetch(h, dst, bytes, s, seen, seq)) != hipSuccess) return e;
+    st.issued[slot] = seq;
+    st.blocks[slot] = c3::plan_fetch_blocks(bytes);
     return hipSuccess;
-}
-
-hipError_t stage_to_device(void* dst, const void* src, size_t bytes, hipStream_t s) {
-    return stage_to_device(dst, src, bytes, s,
-                           [&](const void* h, uint64_t* seen, uint64_t seq, bool& signals) {
-                               if (h == nullptr) return hipSuccess;
-                               signals = true;
-                               return c3::launch_plan_fetch(h, dst, bytes, s, seen, seq);
-                           });
 }
 
 }  // namespace
@@ -500,18 +458,21 @@ int c3_check(const void* const* ptrs, const c3_tensor_meta_t* metas, int T, int 
     // groups: the separate steps.
     const bool small = R <= C3_MAX_REPLICAS && c3::small_tail_fits(R, p.h.C);
     const bool fused = c3::check_group_bound(R) != 0;
+    const bool finalize = !(small || fused) || c3::finalize_first(p.h, small);
+    const bool ready = p.h.direct || finalize;
     hipError_t e = c3::launch_signature(
-        dplan, p.h, p.groups, records, opts ? opts->grid_blocks : 0, !(small || fused), s,
+        dplan, p.h, p.groups, records, opts ? opts->grid_blocks : 0, finalize, s,
         opts ? reinterpret_cast<hipEvent_t>(opts->ev_kernel_begin) : nullptr,
         opts ? reinterpret_cast<hipEvent_t>(opts->ev_kernel_end) : nullptr);
     if (e != hipSuccess) return C3_E_HIP;
     void* lws = static_cast<unsigned char*>(ws) + sig_ws;
     if (small) {
-        e = c3::launch_small_tail(dplan, records, status, bitmap, majority_idx, outliers, out_cap,
-                                  undecided, und_cap, counts, s);
+        e = c3::launch_small_tail(dplan, p.h, records, ready,
+                                  {status, bitmap, majority_idx, outliers, out_cap, undecided,
+                                   und_cap, counts}, s);
     } else if (fused) {
         const bool lists = c3::check_stage_bytes(R, p.h.C) != 0;
-        e = c3::launch_check_tail(dplan, p.h, records, status, bitmap, majority_idx, outliers,
+        e = c3::launch_check_tail(dplan, p.h, records, ready, status, bitmap, majority_idx, outliers,
                                   out_cap, undecided, und_cap, counts, lists ? lws : nullptr, s);
         if (e == hipSuccess && !lists)
             e = c3::launch_localize(status, bitmap, majority_idx, records, R, p.h.C, outliers,
@@ -625,50 +586,40 @@ int c3_localize(const uint8_t* status, const uint64_t* bitmap, const int32_t* ma
 
 // ---------------------------------------------------------------------------
 // Optimizer-boundary check: replay, signatures of the seven slices per
-// replica, exact vote and localization, enqueued by one host call.
+// replica, exact vote and localization, enqueued by one host call as two
+// launches.
 // ---------------------------------------------------------------------------
-static int optimizer_plan(const c3_optimizer_state_t* st, int64_t n, c3_tensor_meta_t metas[7],
-                          uint64_t* chunk, uint64_t* tile) {
+// Unless the caller says otherwise a slice is cut into this many tiles, or
+// into tiles of this size if that is more (c3_optimizer.hip has the times).
+constexpr uint64_t kOptTiles = 32, kOptTileMax = 64 * 1024;
+
+// The signature tile of a valid state: the caller's, or the smallest power of
+// two up to kOptTileMax that cuts the slice into at most kOptTiles, lowered
+// until it divides the slice; 0 if the state is invalid.
+static uint64_t optimizer_tile(const c3_optimizer_state_t* st) {
     if (st == nullptr || st->R < 2 || st->R > C3_MAX_REPLICAS || st->numel < 1 ||
         st->slice_elems < 256 || st->slice_elems % 256 != 0 || st->slice_elems > (1ll << 30))
-        return C3_E_INVAL;
-    *chunk = (uint64_t)st->slice_elems * 4;
-    uint64_t t = st->tile_bytes ? st->tile_bytes : 65536;
-    if (t < 1024 || (t & (t - 1)) != 0) return C3_E_INVAL;
-    while (*chunk % t != 0) t /= 2;  // chunk is a multiple of 1024
-    *tile = t;
-    for (int i = 0; i < 7; ++i) {
-        memset(&metas[i], 0, sizeof(metas[i]));
-        metas[i].dtype = C3_F32;
-        metas[i].ndim = 1;
-        metas[i].shape[0] = n;
-    }
-    return C3_OK;
-}
-
-static uint64_t optimizer_sig_ws(const c3_optimizer_state_t* st, const c3_tensor_meta_t* metas,
-                                 uint64_t chunk, uint64_t tile) {
-    Plan p;
-    if (make_plan(metas, 7, st->R, chunk, tile, p) != C3_OK) return 0;
-    return p.h.total_bytes;
+        return 0;
+    const uint64_t slice = (uint64_t)st->slice_elems * 4;
+    uint64_t t = st->tile_bytes;
+    if (t == 0)
+        for (t = 1024; t * kOptTiles < slice && t < kOptTileMax;) t *= 2;
+    if (t < 1024 || (t & (t - 1)) != 0) return 0;
+    while (slice % t != 0) t /= 2;  // the slice is a multiple of 1024
+    return t;
 }
 
 size_t c3_optimizer_check_workspace_size(const c3_optimizer_state_t* st) {
-    c3_tensor_meta_t metas[7];
-    uint64_t chunk, tile;
-    if (optimizer_plan(st, st ? st->slice_elems : 0, metas, &chunk, &tile) != C3_OK) return 0;
-    const uint64_t sig = optimizer_sig_ws(st, metas, chunk, tile);
-    if (sig == 0) return 0;
-    return (size_t)(align_up(sig, 256) + align_up(c3::localize_ws_bytes(7), 256));
+    const uint64_t tile = optimizer_tile(st);
+    if (tile == 0) return 0;
+    return (size_t)align_up(c3::optimizer_partials_bytes(st->R, st->slice_elems, tile), 256);
 }
 
 int c3_optimizer_check(const c3_optimizer_state_t* st, int64_t k, const c3_adamw_hparams_t* hp,
                        const c3_optimizer_check_out_t* out, void* ws, size_t ws_bytes,
                        c3_stream_t stream) {
-    c3_tensor_meta_t metas[7];
-    uint64_t chunk, tile;
-    int rc = optimizer_plan(st, 0, metas, &chunk, &tile);
-    if (rc != C3_OK) return rc;
+    const uint64_t tile = optimizer_tile(st);
+    if (tile == 0) return C3_E_INVAL;
     if (k < 0 || out == nullptr || out->updated == nullptr || out->records == nullptr ||
         out->status == nullptr || out->bitmap == nullptr || out->majority_idx == nullptr ||
         out->outliers == nullptr || out->undecided == nullptr || out->counts == nullptr)
@@ -676,16 +627,13 @@ int c3_optimizer_check(const c3_optimizer_state_t* st, int64_t k, const c3_adamw
     if (st->param == nullptr || st->grad == nullptr || st->exp_avg == nullptr ||
         st->exp_avg_sq == nullptr)
         return C3_E_INVAL;
-    const size_t need = c3_optimizer_check_workspace_size(st);
-    if (need == 0) return C3_E_INVAL;
-    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < need) return C3_E_WORKSPACE;
+    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < c3_optimizer_check_workspace_size(st))
+        return C3_E_WORKSPACE;
     if (!aligned(out->updated, 16) || !aligned(out->records, 8) || !aligned(out->bitmap, 8) ||
         !aligned(out->majority_idx, 4) || !aligned(out->outliers, 8) ||
         !aligned(out->undecided, 8) || !aligned(out->counts, 8))
         return C3_E_ALIGN;
-    // every check that a later step would make is made here, before the
-    // first launch: the slices are signed in place, so the bases must meet
-    // the signature's 16-byte alignment
+    // the slices are signed in place, 16 bytes at a time
     for (int r = 0; r < st->R; ++r) {
         if (st->param[r] == nullptr || st->grad[r] == nullptr || st->exp_avg[r] == nullptr ||
             st->exp_avg_sq[r] == nullptr)
@@ -694,55 +642,24 @@ int c3_optimizer_check(const c3_optimizer_state_t* st, int64_t k, const c3_adamw
             !aligned(st->exp_avg[r], 16) || !aligned(st->exp_avg_sq[r], 16))
             return C3_E_ALIGN;
     }
-    if (hp == nullptr || hp->step < 1 || !(hp->lr >= 0.0) ||
-        !(hp->beta1 >= 0.0 && hp->beta1 < 1.0) || !(hp->beta2 >= 0.0 && hp->beta2 < 1.0) ||
-        !(hp->eps > 0.0) || !(hp->weight_decay >= 0.0))
-        return C3_E_INVAL;
     const int R = st->R;
     const int64_t S = st->slice_elems;
     const int64_t n_slices = (st->numel + S - 1) / S;
     const int64_t off = (k % n_slices) * S;
     const int64_t n = st->numel - off < S ? st->numel - off : S;
-    for (int i = 0; i < 7; ++i) metas[i].shape[0] = n;
-    if (!c3::small_tail_fits(R, 7)) return C3_E_UNSUPPORTED;
     // the replay writes row (r, j) at updated + (3 r + j) S
     c3::AdamwPtrs aptrs;
     c3::AdamwConst ac;
     bool vec4 = false;
     int64_t ostride = S;
-    rc = adamw_prepare(st->param, st->grad, st->exp_avg, st->exp_avg_sq, R, st->numel, off, n, hp,
-                       out->updated, ostride, aptrs, ac, vec4);
+    const int rc = adamw_prepare(st->param, st->grad, st->exp_avg, st->exp_avg_sq, R, st->numel, off,
+                                 n, hp, out->updated, ostride, aptrs, ac, vec4);
     if (rc != C3_OK) return rc;
-    const void* ptrs[7 * C3_MAX_REPLICAS];
-    for (int r = 0; r < R; ++r) {
-        const void** row = ptrs + 7 * r;
-        row[0] = st->param[r] + off;
-        row[1] = st->grad[r] + off;
-        row[2] = st->exp_avg[r] + off;
-        row[3] = st->exp_avg_sq[r] + off;
-        for (int j = 0; j < 3; ++j) row[4 + j] = out->updated + (3 * (int64_t)r + j) * S;
-    }
-    const uint64_t sig_ws = align_up(optimizer_sig_ws(st, metas, chunk, tile), 256);
-    Plan p;
-    std::vector<unsigned char> buf;
-    rc = prepare_signature(ptrs, metas, 7, R, chunk, out->records, ws, sig_ws, tile, p, buf);
-    if (rc != C3_OK) return rc;
-    // Three launches: the replay, which also copies the staged signature
-    // plan into the workspace; the streaming signature kernel; one workgroup
-    // that combines tile partials into records, votes and writes the lists.
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    hipError_t e = stage_to_device(ws, buf.data(), buf.size(), s,
-                                   [&](const void* h, uint64_t*, uint64_t, bool& signals) {
-        signals = false;
-        return c3::launch_adamw_slice(aptrs, ac, R, vec4, off, n, out->updated, S, s, h,
-                                      h != nullptr ? ws : nullptr, h != nullptr ? buf.size() : 0);
-    });
-    const SigPlan* dplan = static_cast<const SigPlan*>(ws);
-    if (e == hipSuccess)
-        e = c3::launch_signature(dplan, p.h, p.groups, out->records, 0, false, s, nullptr, nullptr);
-    if (e == hipSuccess)
-        e = c3::launch_small_tail(dplan, out->records, out->status, out->bitmap, out->majority_idx,
-                                  out->outliers, 7 * (int64_t)R, out->undecided, 7, out->counts, s);
+    const hipError_t e = c3::launch_optimizer_check(
+        aptrs, ac, R, off, n, tile, out->updated, S, ws, out->records,
+        {out->status, out->bitmap, out->majority_idx, out->outliers, 7 * (int64_t)R, out->undecided,
+         7, out->counts},
+        reinterpret_cast<hipStream_t>(stream));
     return e == hipSuccess ? C3_OK : C3_E_HIP;
 }
 

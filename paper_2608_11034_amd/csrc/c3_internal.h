@@ -23,14 +23,26 @@ hipError_t launch_signature(const SigPlan* dplan, const SigPlan& hplan, const Si
                             c3_chunk_record_t* records, int grid_blocks, bool finalize,
                             hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 
-// Records (from partials unless chunks are whole tiles), exact votes and
-// lists of a small plan in one workgroup: at most 256 chunks and 1,024
-// records, R <= 64 (small_tail_fits checks the sizes).
+// Votes and lists that the one-workgroup tail writes.
+struct TailOut {
+    uint8_t* status;
+    uint64_t* bitmap;
+    int32_t* majority;
+    c3_outlier_t* outliers;
+    int64_t out_cap;
+    int64_t* undecided;
+    int64_t und_cap;
+    int64_t* counts;
+};
+
+// Records (from partials unless `ready`), exact votes and lists of a small
+// plan in one workgroup: at most 256 chunks and 1,024 records, R <= 64
+// (small_tail_fits checks the sizes).
 bool small_tail_fits(int R, int64_t C);
-hipError_t launch_small_tail(const SigPlan* dplan, c3_chunk_record_t* records, uint8_t* status,
-                             uint64_t* bitmap, int32_t* majority, c3_outlier_t* outliers,
-                             int64_t out_cap, int64_t* undecided, int64_t und_cap, int64_t* counts,
-                             hipStream_t stream);
+hipError_t launch_small_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
+                             bool ready, const TailOut& out, hipStream_t stream);
+// Whether launch_signature should combine partials itself before a tail.
+bool finalize_first(const SigPlan& hplan, bool small);
 
 // Tail of c3_check for R <= 32 (check_group_bound(R) != 0): records from
 // partials and exact votes in one kernel; with stage_ws (check_stage_bytes(R,
@@ -39,7 +51,7 @@ hipError_t launch_small_tail(const SigPlan* dplan, c3_chunk_record_t* records, u
 int check_group_bound(int R);
 uint64_t check_stage_bytes(int R, int64_t C);
 hipError_t launch_check_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
-                             uint8_t* status, uint64_t* bitmap, int32_t* majority,
+                             bool ready, uint8_t* status, uint64_t* bitmap, int32_t* majority,
                              c3_outlier_t* outliers, int64_t out_cap, int64_t* undecided,
                              int64_t und_cap, int64_t* counts, void* stage_ws,
                              hipStream_t stream);
@@ -68,12 +80,19 @@ struct AdamwConst {
     float decay, w, one_minus_w, beta2, c2, s2, eps, neg_step;
     int lerp_small;
 };
-// With plan_src set, the same launch also copies plan_bytes (rounded up to
-// 16) from plan_src (pinned host memory) to plan_dst.
 hipError_t launch_adamw_slice(const AdamwPtrs& ptrs, const AdamwConst& c, int R, bool vec4,
                               int64_t offset, int64_t n, float* out, int64_t stride,
-                              hipStream_t stream, const void* plan_src = nullptr,
-                              void* plan_dst = nullptr, size_t plan_bytes = 0);
+                              hipStream_t stream);
+
+// Replay and signatures of the seven slices (4 in place, 3 updated) in one
+// pass, then records, votes and lists in one workgroup.  Bases 16-byte
+// aligned, offset and stride multiples of 256, tile_bytes a multiple of 1024;
+// `partials` holds optimizer_partials_bytes(R, n, tile_bytes).
+uint64_t optimizer_partials_bytes(int R, int64_t slice_elems, uint64_t tile_bytes);
+hipError_t launch_optimizer_check(const AdamwPtrs& ptrs, const AdamwConst& c, int R, int64_t offset,
+                                  int64_t n, uint64_t tile_bytes, float* updated, int64_t stride,
+                                  void* partials, c3_chunk_record_t* records, const TailOut& out,
+                                  hipStream_t stream);
 
 // Fused timing consensus (R <= 16, window <= 64): vote both evidence kinds
 // per (iteration, group), collect per-rank outlier bits, confirm per rank.

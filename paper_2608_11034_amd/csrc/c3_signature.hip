@@ -42,326 +42,13 @@
 #include <type_traits>
 
 #include "c3_device.h"
+#include "c3_fold.h"
 #include "c3_internal.h"
 #include "c3_localize_block.h"
+#include "c3_tail.h"
 #include "c3_vote_row.h"
 
 namespace c3 {
-
-constexpr int kRedoLoads = 8;   // loads in flight where a lane classifies its elements
-
-struct LaneKeys {
-    uint32_t k0, k1, k2, k3, k4, k5;
-};
-
-// beta of block b (wave-uniform, so it stays in a scalar register)
-__device__ inline uint32_t block_beta(uint32_t b) { return b * kBlockMul; }
-
-// m + k + beta as one three-input add with beta as the scalar operand.  The
-// compiler would otherwise re-associate to m + (k + beta) and spend a
-// separate add on each of the six key sums per block.
-__device__ inline uint32_t add3(uint32_t m, uint32_t k, uint32_t beta) {
-    uint32_t r;
-    asm("v_add3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(k), "s"(beta));
-    return r;
-}
-
-// NH over one 16-byte segment (two word pairs) at key offset 4 * lane.
-__device__ inline void nh16(const u32x4 v, const LaneKeys& K, uint32_t beta, uint64_t& A,
-                            uint64_t& B) {
-    A += (uint64_t)add3(v.x, K.k0, beta) * (uint64_t)add3(v.y, K.k1, beta);
-    B += (uint64_t)add3(v.x, K.k2, beta) * (uint64_t)add3(v.y, K.k3, beta);
-    A += (uint64_t)add3(v.z, K.k2, beta) * (uint64_t)add3(v.w, K.k3, beta);
-    B += (uint64_t)add3(v.z, K.k4, beta) * (uint64_t)add3(v.w, K.k5, beta);
-}
-
-__device__ inline double f16_to_f64(uint32_t h) {
-    _Float16 x = __builtin_bit_cast(_Float16, (uint16_t)h);
-    return (double)(float)x;
-}
-
-// ---------------------------------------------------------------------------
-// fast statistics: no classification.  `mf` collects the largest magnitude as
-// an fp32 value (every fp32, bf16 and fp16 value is one exactly); a NaN or
-// Inf may poison it, but such a lane takes the classifying path below, which
-// starts over.
-// ---------------------------------------------------------------------------
-// max(|a|, |b|, |c|) in one instruction (abs source modifiers); NaN
-// propagates, which only matters on lanes the classifying path redoes.
-__device__ inline float absmax3(float a, float b, float c) {
-    float r;
-    asm("v_maximum3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-template <int DT>
-__device__ inline void stats_fast(const u32x4 v, double& s, double& q, float& mf) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    if constexpr (DT == C3_F32) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            double d = (double)__uint_as_float(w[i]);
-            s += d;
-            q = __fma_rn(d, d, q);
-        }
-        mf = absmax3(mf, absmax3(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2])),
-                     __uint_as_float(w[3]));
-    } else if constexpr (DT == C3_BF16 || DT == C3_F16) {
-        float x[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (DT == C3_BF16) {
-                x[2 * i] = __uint_as_float(w[i] << 16);
-                x[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-            } else {
-                x[2 * i] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w[i] & 0xFFFFu));
-                x[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w[i] >> 16));
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const double d = (double)x[i];
-            s += d;
-            q = __fma_rn(d, d, q);
-        }
-        mf = absmax3(absmax3(x[0], x[1], x[2]), absmax3(x[3], x[4], x[5]), absmax3(x[6], x[7], mf));
-    }
-}
-
-// magnitude bits of the type from the fp32 value of a finite magnitude
-template <int DT>
-__device__ inline uint32_t magnitude_bits(float mf) {
-    if constexpr (DT == C3_BF16) return __float_as_uint(mf) >> 16;  // exact: a bf16 value
-    if constexpr (DT == C3_F16) return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)mf);
-    return __float_as_uint(mf);
-}
-
-// slow statistics: classify each element; `mx` is a plain magnitude.  A
-// non-finite element counts as +0, which changes no sum (they start at +0,
-// so none is ever -0), and there are no branches: one lane redoes its column
-// of the tile while the wave waits.
-template <int DT>
-__device__ inline void stats_slow(const u32x4 v, double& s, double& q, uint32_t& mx,
-                                  uint32_t& nan_c, uint32_t& inf_c) {
-    constexpr uint32_t inf_bits = DT == C3_F32 ? 0x7F800000u : DT == C3_BF16 ? 0x7F80u : 0x7C00u;
-    constexpr int N = DT == C3_F32 ? 4 : 8;
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        uint32_t x = w[DT == C3_F32 ? i : i >> 1];
-        if constexpr (DT != C3_F32) x = (i & 1) ? x >> 16 : x & 0xFFFFu;
-        const uint32_t mag = x & (DT == C3_F32 ? 0x7FFFFFFFu : 0x7FFFu);
-        const bool fin = mag < inf_bits;
-        nan_c += mag > inf_bits;
-        inf_c += mag == inf_bits;
-        x = fin ? x : 0u;
-        mx = max(mx, fin ? mag : 0u);
-        const double d = DT == C3_F32 ? (double)__uint_as_float(x)
-                         : DT == C3_BF16 ? (double)__uint_as_float(x << 16) : f16_to_f64(x);
-        s += d;
-        q = __fma_rn(d, d, q);
-    }
-}
-
-// Tail segment of a tile: bytes [0, rem) of a 16-byte segment, rest zero.
-__device__ inline u32x4 load_partial(const uint8_t* p, uint32_t rem) {
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-    for (uint32_t b = 0; b < rem; ++b) w[b >> 2] |= (uint32_t)p[b] << (8 * (b & 3));
-    u32x4 v;
-    v.x = w[0];
-    v.y = w[1];
-    v.z = w[2];
-    v.w = w[3];
-    return v;
-}
-
-// A lane's share of a tile.  The sums are kept in quarters: quarter q holds
-// blocks q, q + 4, ... of the tile, in ascending order, whether one wave
-// folds all four (NQ = 4) or four waves one each (NQ = 1), so the sums have
-// the same bits either way.
-template <int NQ>
-struct LaneFold {
-    uint64_t A, B;
-    double s[NQ], q[NQ];
-    uint32_t mx, nan_c, inf_c;
-};
-
-// Fold of `len` bytes of a tile by NW waves (4, or 1: the whole tile by one):
-// blocks wave, wave + NW, ...
-// Full blocks are read with raw buffer loads: the resource is the tile (a
-// wave-uniform base, `len` bytes), the scalar offset the block, the vector
-// offset the lane's 16 bytes, so no load spends vector instructions on its
-// address.  Each block's beta is pinned in a scalar register, so every key
-// sum is one three-input add.
-template <int DT, int U, int NW>
-__device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, uint32_t blk0,
-                                             const LaneKeys& K, int wave, int lane) {
-    constexpr int NQ = 4 / NW;
-    static_assert((NW == 1 || NW == 4) && U % 4 == 0, "quarters of a tile");
-    LaneFold<NQ> f;
-    f.A = f.B = 0;
-    f.mx = f.nan_c = f.inf_c = 0u;
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) f.s[i] = f.q[i] = 0.0;
-    float mf = 0.0f;
-    const uint32_t off = (uint32_t)lane * 16u;
-    const int nfull = (int)(len >> 10);
-    const uint32_t tail = len & 1023u;
-    const __amdgpu_buffer_rsrc_t rs = tile_resource(tile, len);
-    int k = wave;
-    // k - wave is a multiple of NW U in both loops, so load u of a batch
-    // belongs to quarter u % NQ
-    for (; k + NW * (U - 1) < nfull; k += NW * U) {
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = load16_buf(rs, off, (uint32_t)(k + NW * u) << 10);
-        // keep all U loads in flight before the first use
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t beta = block_beta(blk0 + (uint32_t)(k + NW * u));
-            nh16(v[u], K, beta, f.A, f.B);
-            stats_fast<DT>(v[u], f.s[u % NQ], f.q[u % NQ], mf);
-        }
-    }
-    if (k < nfull) {
-        // fewer than U blocks left for this wave: one more batch, all loads in
-        // flight together; the tests are wave-uniform (scalar branches).
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (k + NW * u < nfull) v[u] = load16_buf(rs, off, (uint32_t)(k + NW * u) << 10);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (k + NW * u < nfull) {
-                nh16(v[u], K, block_beta(blk0 + (uint32_t)(k + NW * u)), f.A, f.B);
-                stats_fast<DT>(v[u], f.s[u % NQ], f.q[u % NQ], mf);
-            }
-        }
-    }
-    const bool has_tail = tail != 0u && nfull % NW == wave && off < tail;
-    if (has_tail) {
-        const uint8_t* seg = tile + ((size_t)nfull << 10) + off;
-        u32x4 v = (off + 16u <= tail) ? load16(reinterpret_cast<const u32x4*>(seg))
-                                      : load_partial(seg, tail - off);
-        nh16(v, K, (blk0 + (uint32_t)nfull) * kBlockMul, f.A, f.B);
-#pragma unroll
-        for (int i = 0; i < NQ; ++i)
-            if (nfull % NQ == i) stats_fast<DT>(v, f.s[i], f.q[i], mf);
-    }
-    if constexpr (DT != C3_RAW) {
-        bool finite = true;
-#pragma unroll
-        for (int i = 0; i < NQ; ++i)
-            finite = finite && __builtin_isfinite(f.s[i]) && __builtin_isfinite(f.q[i]);
-        if (!finite) {
-            // rare: this lane saw a NaN or Inf; redo its statistics classifying
-            f.mx = 0u;
-            for (int i = 0; i < NQ; ++i) {
-                double si = 0.0, qi = 0.0;
-                for (int kk = wave + i; kk < nfull; kk += 4 * kRedoLoads) {
-                    u32x4 v[kRedoLoads];
-#pragma unroll
-                    for (int u = 0; u < kRedoLoads; ++u)
-                        if (kk + 4 * u < nfull)
-                            v[u] = load16_buf(rs, off, (uint32_t)(kk + 4 * u) << 10);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int u = 0; u < kRedoLoads; ++u)
-                        if (kk + 4 * u < nfull)
-                            stats_slow<DT>(v[u], si, qi, f.mx, f.nan_c, f.inf_c);
-                }
-                if (has_tail && nfull % NQ == i) {
-                    const uint8_t* seg = tile + ((size_t)nfull << 10) + off;
-                    u32x4 v = (off + 16u <= tail) ? load16(reinterpret_cast<const u32x4*>(seg))
-                                                  : load_partial(seg, tail - off);
-                    stats_slow<DT>(v, si, qi, f.mx, f.nan_c, f.inf_c);
-                }
-#pragma unroll
-                for (int j = 0; j < NQ; ++j)
-                    if (j == i) {
-                        f.s[j] = si;
-                        f.q[j] = qi;
-                    }
-            }
-        } else {
-            f.mx = magnitude_bits<DT>(mf);
-        }
-    }
-    return f;
-}
-
-// Lanes meet in a fixed six-level butterfly (lane distances 32 to 1) of plain
-// fp64 adds (error at most 6 ulp of the sum of magnitudes); compensation
-// starts where quarters meet.
-__device__ inline void reduce_counts(TilePartial& p, uint32_t mx, uint32_t nan_c, uint32_t inf_c) {
-    p.pad = 0u;
-    p.maxbits = wave_max_u32(mx);
-    p.nan_count = nan_c;
-    p.inf_count = inf_c;
-    if (ballot64(nan_c != 0u || inf_c != 0u) != 0ull) {
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            p.nan_count += shfl_xor_u32(p.nan_count, m);
-            p.inf_count += shfl_xor_u32(p.inf_count, m);
-        }
-    }
-}
-
-// One quarter of a tile (a wave of four): its partial, in every lane.
-__device__ inline TilePartial wave_reduce(const LaneFold<1>& f) {
-    TilePartial p;
-    // A and B, sum and sum of squares side by side: lanes 0-31 end with the
-    // first, lanes 32-63 with the second
-    uint64_t ab = fold32(f.A, f.B);
-    double sq = fold32(f.s[0], f.q[0]);
-    ab = row_sum(fold16(ab, ab));
-    sq = row_sum(fold16(sq, sq));
-    p.A = readlane_u64(ab, 0);
-    p.B = readlane_u64(ab, 32);
-    from_bits(readlane_u64(bits_of(sq), 0), p.s);
-    from_bits(readlane_u64(bits_of(sq), 32), p.q);
-    p.sc = p.qc = 0.0;
-    reduce_counts(p, f.mx, f.nan_c, f.inf_c);
-    return p;
-}
-
-__device__ inline void partial_add(TilePartial& a, const TilePartial& b) {
-    a.A += b.A;
-    a.B += b.B;
-    comp_add(a.s, a.sc, b.s, b.sc);
-    comp_add(a.q, a.qc, b.q, b.qc);
-    a.maxbits = max(a.maxbits, b.maxbits);
-    a.nan_count += b.nan_count;
-    a.inf_count += b.inf_count;
-}
-
-// A whole tile (one wave): the four quarters' sums meet as those of four
-// waves do.
-__device__ inline TilePartial wave_reduce(const LaneFold<4>& f) {
-    TilePartial p;
-    uint64_t ab = fold32(f.A, f.B);
-    ab = row_sum(fold16(ab, ab));
-    p.A = readlane_u64(ab, 0);
-    p.B = readlane_u64(ab, 32);
-    // row i of 16 lanes ends with quarter i
-    const double s = row_sum(fold16(fold32(f.s[0], f.s[2]), fold32(f.s[1], f.s[3])));
-    const double q = row_sum(fold16(fold32(f.q[0], f.q[2]), fold32(f.q[1], f.q[3])));
-    from_bits(readlane_u64(bits_of(s), 0), p.s);
-    from_bits(readlane_u64(bits_of(q), 0), p.q);
-    p.sc = p.qc = 0.0;
-#pragma unroll
-    for (int i = 1; i < 4; ++i) {
-        double si, qi;
-        from_bits(readlane_u64(bits_of(s), 16 * i), si);
-        from_bits(readlane_u64(bits_of(q), 16 * i), qi);
-        comp_add(p.s, p.sc, si, 0.0);
-        comp_add(p.q, p.qc, qi, 0.0);
-    }
-    reduce_counts(p, f.mx, f.nan_c, f.inf_c);
-    return p;
-}
 
 __device__ inline int find_segment(const int64_t* base, int n, int64_t j) {
     // largest t in [0, n) with base[t] <= j  (base[0] = 0, base ascending)
@@ -371,40 +58,6 @@ __device__ inline int find_segment(const int64_t* base, int n, int64_t j) {
         if (base[mid] <= j) lo = mid; else hi = mid;
     }
     return lo;
-}
-
-__device__ inline double maxbits_to_f64(uint32_t bits, int dtype) {
-    if (dtype == C3_F32) return (double)__uint_as_float(bits);
-    if (dtype == C3_BF16) return (double)__uint_as_float(bits << 16);
-    if (dtype == C3_F16) return f16_to_f64(bits);
-    return 0.0;
-}
-
-__device__ inline void write_record(c3_chunk_record_t* rec, const TensorInfo* tip, int t,
-                                    uint64_t k, uint64_t n, const TilePartial& p) {
-    // the tensor's description in one batch of loads, so that the chain over
-    // the dimensions runs on registers instead of waiting for each in turn
-    const TensorInfo ti = *tip;
-    const int dtype = ti.dtype, ndim = ti.ndim;
-    uint64_t h = fmix64(kTag ^ ((uint64_t)(uint32_t)dtype << 32) ^ (uint64_t)(uint32_t)ndim);
-#pragma unroll
-    for (int d = 0; d < C3_MAX_NDIM; ++d)
-        if (d < ndim) h = fmix64(h ^ (uint64_t)ti.shape[d]);
-    h = fmix64(h ^ k);
-    h = fmix64(h ^ n);
-    h = fmix64(h ^ p.A);
-    h = fmix64(h ^ p.B);
-    const uint64_t es = dtype == C3_F32 ? 4 : (dtype == C3_RAW ? 1 : 2);
-    rec->sig = h;
-    rec->n_elems = n / es;
-    rec->nan_count = p.nan_count;
-    rec->inf_count = p.inf_count;
-    rec->tensor = (uint32_t)t;
-    rec->chunk_in_tensor = (uint32_t)k;
-    rec->absmax = maxbits_to_f64(p.maxbits, dtype);
-    rec->sum = p.s + p.sc;
-    rec->sumsq = p.q + p.qc;
-    rec->reserved = 0;
 }
 
 // a / b, in 32 bits where a allows it (a 64-bit division is a sequence of
@@ -452,17 +105,6 @@ __device__ inline TileSpan tile_span(uint64_t lt, uint32_t tpc, uint64_t chunk_b
     s.len = end > s.off ? (uint32_t)min(tile_bytes, end - s.off) : 0u;
     s.blk0 = (uint32_t)(within >> 10);
     return s;
-}
-
-__device__ inline LaneKeys lane_keys(int lane) {
-    LaneKeys K;
-    K.k0 = nh_key(4u * lane + 0u);
-    K.k1 = nh_key(4u * lane + 1u);
-    K.k2 = nh_key(4u * lane + 2u);
-    K.k3 = nh_key(4u * lane + 3u);
-    K.k4 = nh_key(4u * lane + 4u);
-    K.k5 = nh_key(4u * lane + 5u);
-    return K;
 }
 
 // fold_lane for a compile-time type, or (kMixed) the tensor's own
@@ -527,7 +169,7 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
 #pragma unroll
             for (int w = 1; w < kSigThreads / 64; ++w) partial_add(p, lds[w]);
             if (plan->direct)  // one tile per chunk
-                write_record(&records[r * plan->C + pv.chunk_base[t] + lt], pv.tinfo + t, t,
+                write_record(&records[r * plan->C + pv.chunk_base[t] + lt], pv.tinfo[t], t,
                              (uint64_t)lt, ts.len, p);
             else
                 pv.partials[r * plan->tiles_per_replica + pv.tile_base[t] + lt] = p;
@@ -595,7 +237,7 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
         if (lane < count) {
             const RunTile d = done[wave][lane];
             if (plan->direct)
-                write_record(&records[d.r * plan->C + pv.chunk_base[d.t] + d.lt], pv.tinfo + d.t,
+                write_record(&records[d.r * plan->C + pv.chunk_base[d.t] + d.lt], pv.tinfo[d.t],
                              d.t, (uint64_t)d.lt, d.len, d.p);
             else
                 pv.partials[d.r * plan->tiles_per_replica + pv.tile_base[d.t] + d.lt] = d.p;
@@ -604,181 +246,117 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
     }
 }
 
-// Record of (replica r, chunk c) from its tile partials, combined in tile
-// order.
-__device__ inline void combine_chunk(const SigPlan* __restrict__ plan, int64_t r, int64_t c,
-                                     c3_chunk_record_t* out) {
+// Where chunk c of replica r has its tile partials, and what its record needs.
+struct ChunkParts {
+    const TilePartial* pp;
+    int64_t nt;            // tiles
+    uint64_t k, n;         // chunk within the tensor, bytes
+    int t;
+};
+
+__device__ inline ChunkParts chunk_parts(const SigPlan* __restrict__ plan, int64_t r, int64_t c) {
     const char* pb = reinterpret_cast<const char*>(plan);
-    const int64_t* tile_base = reinterpret_cast<const int64_t*>(pb + plan->off_tile_base);
-    const int64_t* chunk_base = reinterpret_cast<const int64_t*>(pb + plan->off_chunk_base);
-    const TensorInfo* tinfo = reinterpret_cast<const TensorInfo*>(pb + plan->off_tmeta);
-    const TilePartial* partials = reinterpret_cast<const TilePartial*>(pb + plan->off_partials);
-    const int t = reinterpret_cast<const int32_t*>(pb + plan->off_chunk_tensor)[c];
-    const uint64_t k = (uint64_t)(c - chunk_base[t]);
-    const uint64_t nbytes = tinfo[t].nbytes;
-    const int64_t tiles_t = tile_base[t + 1] - tile_base[t];
-    const int64_t lt0 = (int64_t)k * plan->tiles_per_chunk;
-    const int64_t nt = min((int64_t)plan->tiles_per_chunk, tiles_t - lt0);
-    const TilePartial* pp = partials + r * plan->tiles_per_replica + tile_base[t] + lt0;
-    TilePartial p = pp[0];
-    // in tile order, four partials loaded at a time before they are added
-    for (int64_t x0 = 1; x0 < nt; x0 += 4) {
-        TilePartial q[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (x0 + j < nt) q[j] = pp[x0 + j];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (x0 + j < nt) partial_add(p, q[j]);
-    }
-    const uint64_t coff = k * plan->chunk_bytes;
-    const uint64_t n = nbytes > coff ? min(plan->chunk_bytes, nbytes - coff) : 0;
-    write_record(out, tinfo + t, t, k, n, p);
+    const PlanView pv(plan);
+    ChunkParts o;
+    o.t = reinterpret_cast<const int32_t*>(pb + plan->off_chunk_tensor)[c];
+    o.k = (uint64_t)(c - pv.chunk_base[o.t]);
+    const uint64_t nbytes = pv.tinfo[o.t].nbytes;
+    const int64_t tb = pv.tile_base[o.t];
+    const int64_t tiles_t = pv.tile_base[o.t + 1] - tb;
+    const int64_t lt0 = (int64_t)o.k * plan->tiles_per_chunk;
+    o.nt = min((int64_t)plan->tiles_per_chunk, tiles_t - lt0);
+    o.pp = pv.partials + r * plan->tiles_per_replica + tb + lt0;
+    const uint64_t coff = o.k * plan->chunk_bytes;
+    o.n = nbytes > coff ? min(plan->chunk_bytes, nbytes - coff) : 0;
+    return o;
 }
 
-// Combine the partials of each (replica, chunk) in tile order.
+// Record of (replica r, chunk c) by one thread, where a chunk has at most
+// kThreadCombine tiles.
+__device__ inline void combine_chunk(const SigPlan* __restrict__ plan, int64_t r, int64_t c,
+                                     c3_chunk_record_t* out) {
+    const ChunkParts cp = chunk_parts(plan, r, c);
+    const TilePartial p = combine_few(cp.pp, (int)cp.nt);
+    write_record(out, PlanView(plan).tinfo[cp.t], cp.t, cp.k, cp.n, p);
+}
+
+// Combine the partials of each (replica, chunk), sixteen lanes each.
 __global__ void __launch_bounds__(256) finalize_kernel(const SigPlan* __restrict__ plan,
                                                        c3_chunk_record_t* __restrict__ records) {
     const int64_t C = plan->C;
     const int64_t total = C * plan->R;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
+    const int l = threadIdx.x & 15;
+    for (int64_t idx = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); idx < total;
+         idx += (int64_t)gridDim.x * 16) {
         const int64_t r = idx / C;
-        combine_chunk(plan, r, idx - r * C, &records[idx]);
+        const ChunkParts cp = chunk_parts(plan, r, idx - r * C);
+        const TilePartial p = combine_row(cp.pp, cp.nt, l);
+        if (l == 0) write_record(&records[idx], PlanView(plan).tinfo[cp.t], cp.t, cp.k, cp.n, p);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Finalize, exact vote and localize of a small plan in one workgroup (the
-// optimizer-boundary check signs 7 chunks per replica; c3_check takes it for
-// plans of up to kTailThreads chunks and kTailMaxRecords records): three
-// launches of a few microseconds each become one.  (1) Every record --
-// combined from its tile partials, or as the streaming kernel wrote it when
-// chunks are whole tiles -- is written out and kept in LDS.  (2) One thread
-// per chunk votes with exact_vote_row, the rule c3_consensus applies, on the
-// signatures.  (3) The lists of c3_localize: a scan over the chunks of their
-// outlier and undecided counts gives each chunk's thread the place of its
-// entries (chunk ascending, replica ascending within a chunk, both
-// replicas' summaries), and thread 0 writes the counts.
+// Records, votes and lists of a small plan in one workgroup (c3_tail.h), in
+// place of three launches of a few microseconds each: plans of up to
+// kTailMaxChunks chunks and kTailMaxRecords records.  `mode` says where the
+// records are: kTailReady as the streaming or the finalize kernel wrote them,
+// else combined here from tile partials, by a thread or by sixteen lanes each.
 // ---------------------------------------------------------------------------
-constexpr int kTailThreads = 256;
-constexpr int kTailMaxRecords = 1024;
-
-// Inclusive prefix sum over the 64 lanes of a wave.
-__device__ inline uint64_t wave_inclusive_scan(uint64_t x, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint64_t y = shfl_u64(x, lane >= d ? lane - d : lane);
-        if (lane >= d) x += y;
-    }
-    return x;
-}
-
-__device__ inline void outlier_from(c3_outlier_t& o, int64_t u, int r, int mj,
-                                    const c3_chunk_record_t& a, const c3_chunk_record_t& b) {
-    o.chunk = u;
-    o.replica = r;
-    o.majority_replica = mj;
-    o.nan_count[0] = a.nan_count;
-    o.nan_count[1] = b.nan_count;
-    o.inf_count[0] = a.inf_count;
-    o.inf_count[1] = b.inf_count;
-    o.absmax[0] = a.absmax;
-    o.absmax[1] = b.absmax;
-    o.sum[0] = a.sum;
-    o.sum[1] = b.sum;
-    o.sumsq[0] = a.sumsq;
-    o.sumsq[1] = b.sumsq;
-}
+enum { kTailReady = 0, kTailThread = 1, kTailRow = 2 };
 
 __global__ void __launch_bounds__(kTailThreads) small_tail_kernel(
-    const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records,
-    uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap, int32_t* __restrict__ majority,
-    c3_outlier_t* __restrict__ outliers, int64_t out_cap, int64_t* __restrict__ undecided,
-    int64_t und_cap, int64_t* __restrict__ counts) {
+    const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records, int mode, TailOut out) {
     __shared__ c3_chunk_record_t rec[kTailMaxRecords];
-    __shared__ uint64_t wave_total[kTailThreads / 64];
     const int R = plan->R;
     const int C = (int)plan->C;
-    for (int i = threadIdx.x; i < R * C; i += kTailThreads) {
-        if (plan->direct) {
-            rec[i] = records[i];
-        } else {
-            combine_chunk(plan, i / C, i % C, &rec[i]);
-            records[i] = rec[i];
+    if (mode == kTailRow) {
+        const int l = threadIdx.x & 15;
+        for (int i = threadIdx.x >> 4; i < R * C; i += kTailThreads / 16) {
+            const ChunkParts cp = chunk_parts(plan, i / C, i % C);
+            const TilePartial p = combine_row(cp.pp, cp.nt, l);
+            if (l == 0) {
+                write_record(&rec[i], PlanView(plan).tinfo[cp.t], cp.t, cp.k, cp.n, p);
+                records[i] = rec[i];
+            }
+        }
+    } else {
+        for (int i = threadIdx.x; i < R * C; i += kTailThreads) {
+            if (mode == kTailReady) {
+                rec[i] = records[i];
+            } else {
+                combine_chunk(plan, i / C, i % C, &rec[i]);
+                records[i] = rec[i];
+            }
         }
     }
-    __syncthreads();
-    const int u = threadIdx.x;
-    UnitVote v{0ull, -1, (uint8_t)C3_AGREE};
-    if (u < C) {
-        if (R <= 16) {
-            uint64_t e[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) e[r] = r < R ? rec[r * C + u].sig : 0ull;
-            v = exact_vote_row<16>(e, R);
-        } else if (R <= 32) {
-            uint64_t e[32];
-#pragma unroll
-            for (int r = 0; r < 32; ++r) e[r] = r < R ? rec[r * C + u].sig : 0ull;
-            v = exact_vote_row<32>(e, R);
-        } else {
-            uint64_t e[C3_MAX_REPLICAS];
-            for (int r = 0; r < C3_MAX_REPLICAS; ++r) e[r] = r < R ? rec[r * C + u].sig : 0ull;
-            v = exact_vote_row<C3_MAX_REPLICAS>(e, R);
-        }
-        status[u] = v.status;
-        bitmap[u] = v.bitmap;
-        majority[u] = v.majority;
-    }
-    // counts packed as outliers (24 bits: at most 256 chunks x 63), undecided
-    // and attributed chunks (20 bits each)
-    const bool und = u < C && v.status == C3_INCONCLUSIVE;
-    const uint64_t n_o = u < C && !und ? (uint64_t)__builtin_popcountll(v.bitmap) : 0ull;
-    const uint64_t packed = n_o | ((uint64_t)und << 24) | ((uint64_t)(n_o != 0ull) << 44);
-    const int lane = u & 63, wave = u >> 6;
-    const uint64_t incl = wave_inclusive_scan(packed, lane);
-    if (lane == 63) wave_total[wave] = incl;
-    __syncthreads();
-    uint64_t before = 0ull, total = 0ull;
-#pragma unroll
-    for (int w = 0; w < kTailThreads / 64; ++w) {
-        const uint64_t t = wave_total[w];
-        before += w < wave ? t : 0ull;
-        total += t;
-    }
-    const uint64_t excl = before + incl - packed;
-    int64_t po = (int64_t)(excl & 0xFFFFFFull);
-    const int64_t pu = (int64_t)((excl >> 24) & 0xFFFFFull);
-    for (uint64_t b = n_o ? v.bitmap : 0ull; b != 0ull && po < out_cap; b &= b - 1ull, ++po) {
-        const int r = __builtin_ctzll(b);
-        c3_outlier_t o;
-        outlier_from(o, u, r, v.majority, rec[r * C + u], rec[v.majority * C + u]);
-        outliers[po] = o;
-    }
-    if (und && pu < und_cap) undecided[pu] = u;
-    if (u == 0) {
-        counts[0] = (int64_t)(total & 0xFFFFFFull);
-        counts[1] = (int64_t)((total >> 24) & 0xFFFFFull);
-        counts[2] = (int64_t)((total >> 44) & 0xFFFFFull);
-    }
+    tail_votes_and_lists(rec, R, C, out);
 }
 
-bool small_tail_fits(int R, int64_t C) { return C >= 1 && C <= kTailThreads && R * C <= kTailMaxRecords; }
+bool small_tail_fits(int R, int64_t C) {
+    return C >= 1 && C <= kTailMaxChunks && R * C <= kTailMaxRecords;
+}
 
-hipError_t launch_small_tail(const SigPlan* dplan, c3_chunk_record_t* records, uint8_t* status,
-                             uint64_t* bitmap, int32_t* majority, c3_outlier_t* outliers,
-                             int64_t out_cap, int64_t* undecided, int64_t und_cap, int64_t* counts,
-                             hipStream_t stream) {
+hipError_t launch_small_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
+                             bool ready, const TailOut& out, hipStream_t stream) {
+    const int mode = ready ? kTailReady
+                     : hplan.tiles_per_chunk <= (uint32_t)kThreadCombine ? kTailThread : kTailRow;
     hipLaunchKernelGGL(small_tail_kernel, dim3(1), dim3(kTailThreads), 0, stream, dplan, records,
-                       status, bitmap, majority, outliers, out_cap, undecided, und_cap, counts);
+                       mode, out);
     return hipGetLastError();
+}
+
+// Records that the finalize kernel should combine before the tail: more than
+// a thread combines, and for the one-workgroup tail more than a few rounds of
+// its groups of sixteen lanes.
+bool finalize_first(const SigPlan& hplan, bool small) {
+    if (hplan.direct || hplan.tiles_per_chunk <= (uint32_t)kThreadCombine) return false;
+    return !small || hplan.C * hplan.R > 4 * (kTailThreads / 16);
 }
 
 // ---------------------------------------------------------------------------
 // Tail of c3_check: the records of every (replica, chunk) from their tile
-// partials (finalize_kernel's combine) or as the streaming kernel wrote
-// them, the exact vote of every chunk (exact_vote_row, the rule of
+// partials (at most kThreadCombine a chunk) or as the streaming or finalize
+// kernel wrote them (`ready`), the exact vote of every chunk (exact_vote_row, the rule of
 // c3_consensus) and the lists of c3_localize, in two launches.
 // check_vote_kernel:
 //   - a workgroup of kCheckThreads threads takes CPB = kCheckThreads / N
@@ -812,8 +390,8 @@ struct CheckStage {
 template <int N>
 __global__ void __launch_bounds__(kCheckThreads) check_vote_kernel(
     const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records,
-    uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap, int32_t* __restrict__ majority,
-    CheckStage stage) {
+    bool ready, uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap,
+    int32_t* __restrict__ majority, CheckStage stage) {
     constexpr int CPB = kCheckThreads / N;
     static_assert(CPB <= 64, "a segment's units must fit one wave");
     __shared__ c3_chunk_record_t rec[CPB][N];
@@ -825,7 +403,7 @@ __global__ void __launch_bounds__(kCheckThreads) check_vote_kernel(
     const int64_t c = (int64_t)blockIdx.x * CPB + cu;
     if (slot < R && c < C) {
         c3_chunk_record_t* dst = &records[(int64_t)slot * C + c];
-        if (plan->direct) {
+        if (ready) {
             rec[cu][slot] = *dst;
         } else {
             c3_chunk_record_t r;
@@ -964,7 +542,7 @@ uint64_t check_stage_bytes(int R, int64_t C) {
 }
 
 hipError_t launch_check_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
-                             uint8_t* status, uint64_t* bitmap, int32_t* majority,
+                             bool ready, uint8_t* status, uint64_t* bitmap, int32_t* majority,
                              c3_outlier_t* outliers, int64_t out_cap, int64_t* undecided,
                              int64_t und_cap, int64_t* counts, void* stage_ws,
                              hipStream_t stream) {
@@ -988,19 +566,19 @@ hipError_t launch_check_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chun
     switch (N) {
         case 4:
             hipLaunchKernelGGL(check_vote_kernel<4>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, status, bitmap, majority, st);
+                               stream, dplan, records, ready, status, bitmap, majority, st);
             break;
         case 8:
             hipLaunchKernelGGL(check_vote_kernel<8>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, status, bitmap, majority, st);
+                               stream, dplan, records, ready, status, bitmap, majority, st);
             break;
         case 16:
             hipLaunchKernelGGL(check_vote_kernel<16>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, status, bitmap, majority, st);
+                               stream, dplan, records, ready, status, bitmap, majority, st);
             break;
         default:
             hipLaunchKernelGGL(check_vote_kernel<32>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, status, bitmap, majority, st);
+                               stream, dplan, records, ready, status, bitmap, majority, st);
             break;
     }
     hipError_t e = hipGetLastError();
@@ -1139,7 +717,7 @@ hipError_t launch_signature(const SigPlan* dplan, const SigPlan& hplan, const Si
     if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
     if (!hplan.direct && finalize) {
         const int64_t total = hplan.C * hplan.R;
-        const int64_t blocks = (total + 255) / 256 < 65536 ? (total + 255) / 256 : 65536;
+        const int64_t blocks = (total + 15) / 16 < 65536 ? (total + 15) / 16 : 65536;
         hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, dplan,
                            records);
         e = hipGetLastError();

@@ -103,3 +103,34 @@ def test_wave_runs(tiles):
     # the same chunks in smaller tiles go through partials
     wide = _sign(reps, 4 * KIB, tile=KIB)
     compare_all_records(c3.records_numpy(wide[:1]), _oracle([base], 4 * KIB))
+
+
+# partials of 2 to 33 tiles a chunk: combined by one thread (up to four tiles)
+# or by sixteen lanes, in the finalize kernel, the one-workgroup tail (up to
+# 256 records of them, beyond that finalized first) and the check's tail
+@pytest.mark.parametrize("tiles", [2, 4, 5, 16, 17, 33])
+@pytest.mark.parametrize("R,chunks", [(2, 3), (5, 60), (3, 90), (8, 300), (33, 8), (40, 30)])
+def test_partials_combined_alike(tiles, R, chunks):
+    print("CASE partials", tiles, R, chunks, flush=True)
+    chunk = tiles * KIB
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(tiles * 100 + chunks)
+    n = chunks // 2 * chunk // 4
+    base = [_tensor(torch.float32, n + 77, gen), _tensor(torch.float32, n - 300, gen, special=False)]
+    reps = [base] + [[t.clone() for t in base] for _ in range(R - 1)]
+    reps[R - 1][0].view(torch.uint8)[chunk + 5] ^= 4
+    plan = c3.SignaturePlan(reps, chunk, KIB)
+    outs = plan.new_check_outputs()
+    ws = torch.empty(plan.check_workspace_size(), dtype=torch.uint8, device=DEV)
+    plan.run_check(outs, ws)
+    rec, st, bm, mj, outl, und, cnt = outs
+    apart = _sign(reps, chunk, tile=KIB)
+    st2, bm2, mj2 = c3.consensus(apart, c3.EXACT)
+    outl2, und2, cnt2 = c3.localize(st2, bm2, mj2, apart)
+    torch.cuda.synchronize()
+    assert torch.equal(rec, apart)
+    assert torch.equal(st, st2) and torch.equal(bm, bm2) and torch.equal(mj, mj2)
+    assert torch.equal(cnt, cnt2)
+    assert np.array_equal(c3.outliers_numpy(outl, cnt), c3.outliers_numpy(outl2, cnt2))
+    if R <= 8:
+        compare_all_records(c3.records_numpy(rec), _oracle(reps, chunk))
