@@ -498,7 +498,7 @@ size_t c3_timing_consensus_workspace_size(int R, int64_t G, int64_t T, int windo
  * Execution (results do not depend on it):
  *   - R in {4, 8, 16}, both arrays 16-byte aligned, W <= 64,
  *     2 * ceil(T / 32) * R * 64 bytes <= 64 KiB and G / 16 at least the
- *     device's compute-unit count: one kernel, with the per-unit results of
+ *     device's compute-unit count or R * T <= 512: one kernel, with the per-unit results of
  *     either kind, both or neither; each workgroup votes 16 groups over all
  *     T iterations (writing their per-unit results when requested),
  *     collects its ranks' outlier bits in LDS and confirms them there (the

@@ -426,7 +426,8 @@ __global__ void __launch_bounds__(kConfirmThreads) timing_confirm_kernel(
 // kPassGroups, group g0 + l % kPassGroups).  Used with the per-unit results
 // of either kind, both or neither, when R equals the group bound, both
 // kinds' rows are 16-byte aligned, W <= 64, the masks fit kPassMaskLds
-// bytes and there are at least as many workgroups as compute units.
+// bytes and there are at least as many workgroups as compute units or few
+// iterations (pass_applies).
 // Per-unit results are written as 16- to 128-byte pieces of each
 // iteration's row; on the 32,768-rank workload the pass with those of both
 // kinds takes 91.2 us of kernel time against 106.2 us for the three
@@ -738,7 +739,17 @@ static hipError_t launch_pass(const char* fp, const char* tp, int64_t G, int64_t
 }
 
 // The single pass applies: R is a group bound with dense 16-byte aligned rows,
-// the masks fit in LDS, and the groups give every compute unit a workgroup.
+// the masks fit in LDS, and either the groups give every compute unit a
+// workgroup or a workgroup's walk over the iterations is shorter than the two
+// launches it saves.  GPU us per call, three launches / the pass, fp32 times
+// without per-unit results (fp64 and per-unit results within 10%, except the
+// last row: fp64 with per-unit results 10.2 / 11.4):
+//   R = 4, 64 groups   T = 16: 7.6 / 3.7    64: 8.7 / 4.8    256: 8.6 / 9.0    1024: 11.3 / 27.4
+//   R = 8, 64 groups   T = 16: 8.3 / 4.0    64: 9.4 / 5.7    256: 8.9 / 13.0   1024: 11.4 / 41.6
+//   R = 8, 2,048       T = 16: 8.5 / 4.2    64: 10.0 / 6.1   256: 15.4 / 13.8  1024: 45.3 / 42.8
+//   R = 16, 64 groups  T = 16: 9.5 / 4.8    64: 10.4 / 8.0   256: 9.9 / 20.8   1024: 11.9 / 69.3
+constexpr int64_t kPassShortRows = 512;          // R * T of a short walk
+
 static bool pass_applies(const void* fp, const void* times, int time_kind, int R, int64_t G,
                          int64_t T, int Wt, hipStream_t stream, size_t& lds) {
     if (R != 4 && R != 8 && R != 16) return false;
@@ -752,7 +763,7 @@ static bool pass_applies(const void* fp, const void* times, int time_kind, int R
     const int64_t bytes = 2 * n_seg * R * kPassGroups * 4;
     if (bytes > kPassMaskLds) return false;
     const int cus = stream_cu_count(stream);
-    if (cus <= 0 || (G + kPassGroups - 1) / kPassGroups < cus) return false;
+    if (R * T > kPassShortRows && (cus <= 0 || (G + kPassGroups - 1) / kPassGroups < cus)) return false;
     lds = (size_t)bytes;
     return true;
 }
