@@ -56,6 +56,8 @@ VERDICT_DTYPE = np.dtype([("flags", "<u4"), ("first_divergent_iter", "<i4"),
                           ("max_window_slow", "<u4"), ("first_straggler_window", "<i4")])
 assert RECORD_DTYPE.itemsize == 64 and OUTLIER_DTYPE.itemsize == 80 and VERDICT_DTYPE.itemsize == 24
 
+_TIME_KIND = {torch.float32: EV_F32, torch.float64: EV_F64}
+_EVIDENCE_KIND = {torch.int64: EV_U64, torch.int32: EV_U32, **_TIME_KIND}
 _TORCH_CODE = {torch.float32: F32, torch.bfloat16: BF16, torch.float16: F16, torch.uint8: RAW}
 
 
@@ -183,14 +185,20 @@ def _check(rc: int, what: str):
         raise C3Error(f"{what}: {lib().c3_status_string(rc).decode()} ({rc})")
 
 
+# the current stream's handle without a Stream object per call
+_raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else None
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _dev_tensor(t: torch.Tensor, name: str) -> torch.Tensor:
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise C3Error(f"{name} must be a tensor on a ROCm GPU device")
     if not t.is_contiguous():
         raise C3Error(f"{name} must be contiguous")
@@ -212,7 +220,7 @@ def bitmap_words(R: int) -> int:
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _empty(shape, dtype, device):
@@ -279,6 +287,9 @@ class SignaturePlan:
         self.metas = make_metas(replicas[0])
         self.C = num_chunks(replicas[0], chunk_bytes)
         self.ws_bytes = signature_workspace_size(replicas[0], self.R, chunk_bytes, tile_bytes)
+        # launch options of a call without any, which the library only reads
+        self._plain = LaunchOpts(None, None, 0, 0, self.tile_bytes)
+        self._plain_ref = ctypes.byref(self._plain)
 
     def new_records(self):
         return _empty((self.R, self.C, 64), torch.uint8, self.device)
@@ -286,18 +297,22 @@ class SignaturePlan:
     def new_workspace(self):
         return _empty((self.ws_bytes,), torch.uint8, self.device)
 
+    def _opts(self, ev_begin, ev_end, grid_blocks, plan_staged):
+        if ev_begin is None and ev_end is None and not grid_blocks and not plan_staged:
+            return self._plain_ref
+        return ctypes.byref(LaunchOpts(ev_begin.cuda_event if ev_begin is not None else None,
+                                       ev_end.cuda_event if ev_end is not None else None,
+                                       int(grid_blocks), OPT_PLAN_STAGED if plan_staged else 0,
+                                       self.tile_bytes))
+
     def run(self, records, workspace, stream=None, ev_begin=None, ev_end=None, grid_blocks=0,
             plan_staged=False):
         """Launch c3_signature.  plan_staged=True promises that `workspace` still
         holds the plan a previous run of this object staged (see
         C3_OPT_PLAN_STAGED)."""
-        opts = LaunchOpts(ev_begin.cuda_event if ev_begin is not None else None,
-                          ev_end.cuda_event if ev_end is not None else None,
-                          int(grid_blocks), OPT_PLAN_STAGED if plan_staged else 0,
-                          self.tile_bytes)
         rc = lib().c3_signature_ex(self.ptrs, self.metas, self.T, self.R, self.chunk_bytes,
-                                   _ptr(records), _ptr(workspace), workspace.numel(),
-                                   _stream(stream), ctypes.byref(opts))
+                                   _ptr(records), _ptr(workspace), workspace.numel(), _stream(stream),
+                                   self._opts(ev_begin, ev_end, grid_blocks, plan_staged))
         _check(rc, "c3_signature")
         return records
 
@@ -335,13 +350,10 @@ class SignaturePlan:
         _check_out(cnt, torch.int64, 3, "counts")
         out_cap = outl.shape[0] if out_cap is None else min(out_cap, outl.shape[0])
         und_cap = und.numel() if und_cap is None else min(und_cap, und.numel())
-        opts = LaunchOpts(ev_begin.cuda_event if ev_begin is not None else None,
-                          ev_end.cuda_event if ev_end is not None else None,
-                          int(grid_blocks), OPT_PLAN_STAGED if plan_staged else 0,
-                          self.tile_bytes)
         rc = lib().c3_check(self.ptrs, self.metas, self.T, R, self.chunk_bytes, _ptr(rec), _ptr(st),
                             _ptr(bm), _ptr(mj), _ptr(outl), out_cap, _ptr(und), und_cap, _ptr(cnt),
-                            _ptr(workspace), workspace.numel(), _stream(stream), ctypes.byref(opts))
+                            _ptr(workspace), workspace.numel(), _stream(stream),
+                            self._opts(ev_begin, ev_end, grid_blocks, plan_staged))
         _check(rc, "c3_check")
         return outputs
 
@@ -395,8 +407,7 @@ def consensus(evidence: torch.Tensor, mode: int = EXACT, *, kind: int = None, R:
         n_units = C if n_units is None else n_units
     else:
         if kind is None:
-            kind = {torch.int64: EV_U64, torch.int32: EV_U32, torch.float32: EV_F32,
-                    torch.float64: EV_F64}[evidence.dtype]
+            kind = _EVIDENCE_KIND[evidence.dtype]
         R = evidence.shape[-1] if R is None else R
         es = evidence.element_size()
         replica_stride = es if replica_stride is None else replica_stride
@@ -532,7 +543,7 @@ def timing_consensus(fingerprints, times, window: int = 16, kappa: float = KAPPA
         raise C3Error("fingerprints must be int64 [T, G, R]")
     if times.shape != fingerprints.shape:
         raise C3Error("times must have the fingerprints' shape [T, G, R]")
-    kind = {torch.float32: EV_F32, torch.float64: EV_F64}.get(times.dtype)
+    kind = _TIME_KIND.get(times.dtype)
     if kind is None:
         raise C3Error("times must be float32 or float64")
     T, G, R = fingerprints.shape
