@@ -372,6 +372,26 @@ int adamw_prepare(const float* const* param, const float* const* grad,
     return C3_OK;
 }
 
+// The plan as the kernels get it: with the kernels' arguments when it fits
+// (without the chunk-to-tensor table, which they then search for), else staged
+// into the workspace on the stream unless the caller says that it is there.
+// us per call, staged / as an argument: 3 x 1M fp32 15.1 / 12.1, the 3 GB fp32
+// shard (256 KiB tiles) 430.9 / 427.9.  Over many smaller tiles the look-ups,
+// which go through the scalar cache then, cost more than the launch saved:
+// 12,352 tiles of 128 KiB 244.7 / 246.2.
+constexpr int64_t kArgPlanMaxTiles = 8192;
+
+hipError_t place_plan(void* ws, const Plan& p, const std::vector<unsigned char>& buf, bool staged,
+                      hipStream_t s, c3::PlanSource& src) {
+    if (p.h.off_chunk_tensor <= c3::kArgPlanBytes &&
+        (p.h.tile_bytes >= c3::kDefaultTileMax || p.h.tiles_per_replica * p.h.R <= kArgPlanMaxTiles)) {
+        src = {ws, buf.data(), (size_t)p.h.off_chunk_tensor};
+        return hipSuccess;
+    }
+    src = {ws, nullptr, 0};
+    return staged ? hipSuccess : stage_to_device(ws, buf.data(), buf.size(), s);
+}
+
 int signature_impl(const void* const* ptrs, const c3_tensor_meta_t* metas, int T, int R,
                    uint64_t chunk_bytes, c3_chunk_record_t* records, void* ws, size_t ws_bytes,
                    c3_stream_t stream, const c3_launch_opts_t* opts) {
@@ -382,12 +402,13 @@ int signature_impl(const void* const* ptrs, const c3_tensor_meta_t* metas, int T
     if (rc != C3_OK) return rc;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool staged = opts != nullptr && (opts->flags & C3_OPT_PLAN_STAGED) != 0;
-    if (!staged && stage_to_device(ws, buf.data(), buf.size(), s) != hipSuccess) return C3_E_HIP;
+    c3::PlanSource src;
+    if (place_plan(ws, p, buf, staged, s, src) != hipSuccess) return C3_E_HIP;
     // the events bracket the streaming kernels only: the end event is
     // recorded before the combine of tile partials of multi-tile chunks
     const hipError_t e = c3::launch_signature(
-        static_cast<const SigPlan*>(ws), p.h, p.groups, records, opts ? opts->grid_blocks : 0,
-        true, s, opts ? reinterpret_cast<hipEvent_t>(opts->ev_kernel_begin) : nullptr,
+        src, p.h, p.groups, records, opts ? opts->grid_blocks : 0,
+        true, nullptr, s, opts ? reinterpret_cast<hipEvent_t>(opts->ev_kernel_begin) : nullptr,
         opts ? reinterpret_cast<hipEvent_t>(opts->ev_kernel_end) : nullptr);
     return e == hipSuccess ? C3_OK : C3_E_HIP;
 }
@@ -448,31 +469,31 @@ int c3_check(const void* const* ptrs, const c3_tensor_meta_t* metas, int T, int 
     if (rc != C3_OK) return rc;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool staged = opts != nullptr && (opts->flags & C3_OPT_PLAN_STAGED) != 0;
-    if (!staged && stage_to_device(ws, buf.data(), buf.size(), s) != hipSuccess) return C3_E_HIP;
-    const SigPlan* dplan = static_cast<const SigPlan*>(ws);
+    c3::PlanSource src;
+    if (place_plan(ws, p, buf, staged, s, src) != hipSuccess) return C3_E_HIP;
     // A plan small enough for one workgroup's LDS (small_tail_fits, up to 64
     // replicas): the streaming kernels, then one workgroup that combines
     // partials, votes and lists.  Otherwise, up to 32 replicas: a tail
-    // kernel that combines partials and votes, and (for up to 8,192 chunks)
-    // a one-workgroup kernel that places the lists it staged.  Larger
-    // groups: the separate steps.
+    // kernel that combines partials, votes and (for up to 8,192 chunks)
+    // writes the lists.  Larger groups: the separate steps.
     const bool small = R <= C3_MAX_REPLICAS && c3::small_tail_fits(R, p.h.C);
     const bool fused = c3::check_group_bound(R) != 0;
     const bool finalize = !(small || fused) || c3::finalize_first(p.h, small);
     const bool ready = p.h.direct || finalize;
+    void* lws = static_cast<unsigned char*>(ws) + sig_ws;
+    const bool lists = !small && fused && c3::check_stage_bytes(R, p.h.C) != 0;
     hipError_t e = c3::launch_signature(
-        dplan, p.h, p.groups, records, opts ? opts->grid_blocks : 0, finalize, s,
+        src, p.h, p.groups, records, opts ? opts->grid_blocks : 0, finalize,
+        lists ? c3::check_arrivals(R, p.h.C, lws) : nullptr, s,
         opts ? reinterpret_cast<hipEvent_t>(opts->ev_kernel_begin) : nullptr,
         opts ? reinterpret_cast<hipEvent_t>(opts->ev_kernel_end) : nullptr);
     if (e != hipSuccess) return C3_E_HIP;
-    void* lws = static_cast<unsigned char*>(ws) + sig_ws;
     if (small) {
-        e = c3::launch_small_tail(dplan, p.h, records, ready,
+        e = c3::launch_small_tail(src, p.h, records, ready,
                                   {status, bitmap, majority_idx, outliers, out_cap, undecided,
                                    und_cap, counts}, s);
     } else if (fused) {
-        const bool lists = c3::check_stage_bytes(R, p.h.C) != 0;
-        e = c3::launch_check_tail(dplan, p.h, records, ready, status, bitmap, majority_idx, outliers,
+        e = c3::launch_check_tail(src, p.h, records, ready, status, bitmap, majority_idx, outliers,
                                   out_cap, undecided, und_cap, counts, lists ? lws : nullptr, s);
         if (e == hipSuccess && !lists)
             e = c3::launch_localize(status, bitmap, majority_idx, records, R, p.h.C, outliers,

@@ -17,11 +17,22 @@ int stream_cu_count(hipStream_t stream);
 static_assert(sizeof(c3_outlier_t) == 80, "outlier layout");
 static_assert(sizeof(c3_rank_verdict_t) == 24, "verdict layout");
 
+// Where the kernels find the plan: staged at `ws`, or, with arg_bytes != 0, the
+// first arg_bytes of the plan's bytes at `arg` go along as an argument of every
+// kernel; `ws` holds the partials either way.
+constexpr size_t kArgPlanBytes = 3584;     // a kernel's arguments may take 4,096
+struct PlanSource {
+    void* ws;
+    const unsigned char* arg;
+    size_t arg_bytes;
+};
+
 // finalize: combine tile partials into records when a chunk spans several
 // tiles (false leaves that to launch_small_tail).
-hipError_t launch_signature(const SigPlan* dplan, const SigPlan& hplan, const SigGroups& groups,
+// clear (may be null): a device word that the first streaming kernel sets to 0.
+hipError_t launch_signature(const PlanSource& src, const SigPlan& hplan, const SigGroups& groups,
                             c3_chunk_record_t* records, int grid_blocks, bool finalize,
-                            hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
+                            uint32_t* clear, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 
 // Votes and lists that the one-workgroup tail writes.
 struct TailOut {
@@ -39,18 +50,19 @@ struct TailOut {
 // plan in one workgroup: at most 256 chunks and 1,024 records, R <= 64
 // (small_tail_fits checks the sizes).
 bool small_tail_fits(int R, int64_t C);
-hipError_t launch_small_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
+hipError_t launch_small_tail(const PlanSource& src, const SigPlan& hplan, c3_chunk_record_t* records,
                              bool ready, const TailOut& out, hipStream_t stream);
 // Whether launch_signature should combine partials itself before a tail.
 bool finalize_first(const SigPlan& hplan, bool small);
 
 // Tail of c3_check for R <= 32 (check_group_bound(R) != 0): records from
-// partials and exact votes in one kernel; with stage_ws (check_stage_bytes(R,
-// C) bytes, 256-byte aligned; C up to 8,192) also the lists of c3_localize,
-// staged per segment by that kernel and placed by a one-workgroup kernel.
+// partials (unless `ready`) and exact votes; with stage_ws (check_stage_bytes(R,
+// C) bytes, 256-byte aligned; C up to 8,192) also the lists of c3_localize.
+// The word check_arrivals(R, C, stage_ws) must be 0 when it starts.
 int check_group_bound(int R);
 uint64_t check_stage_bytes(int R, int64_t C);
-hipError_t launch_check_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
+uint32_t* check_arrivals(int R, int64_t C, void* stage_ws);
+hipError_t launch_check_tail(const PlanSource& src, const SigPlan& hplan, c3_chunk_record_t* records,
                              bool ready, uint8_t* status, uint64_t* bitmap, int32_t* majority,
                              c3_outlier_t* outliers, int64_t out_cap, int64_t* undecided,
                              int64_t und_cap, int64_t* counts, void* stage_ws,

@@ -39,6 +39,8 @@
 // become non-finite (finite fp32/bf16/fp16 values cannot overflow fp64 here),
 // so a lane whose sums end non-finite re-reads its own segments and
 // classifies every element.  Healthy data never takes that path.
+#include <string.h>
+
 #include <type_traits>
 
 #include "c3_device.h"
@@ -60,12 +62,64 @@ __device__ inline int find_segment(const int64_t* base, int n, int64_t j) {
     return lo;
 }
 
+// find_segment by a whole wave: each round its lanes probe 64 evenly spaced
+// entries of the range that holds the answer, so 121 tensors take two
+// dependent loads instead of seven.  j is uniform; so is the result.
+__device__ inline int find_segment_wave(const int64_t* base, int n, int64_t j, int lane) {
+    int lo = 0;                       // base[lo] <= j
+    while (n > 1) {
+        const int step = (n + 63) >> 6;
+        const int p = lane * step;
+        const int k = __builtin_popcountll(ballot64(p < n && base[lo + p] <= j));   // a prefix, >= 1
+        const int at = (k - 1) * step;
+        n = n - at < step ? n - at : step;
+        lo += at;
+    }
+    return lo;
+}
+
 // a / b, in 32 bits where a allows it (a 64-bit division is a sequence of
 // more than a hundred instructions; the operands here are wave-uniform)
 __device__ inline uint64_t udiv(uint64_t a, uint32_t b) {
     if (b == 1u) return a;
     if ((a >> 32) == 0ull) return (uint32_t)a / b;
     return a / b;
+}
+
+// The replica of tile i of a launch of gtiles tiles per replica.
+__device__ inline int64_t replica_of(int64_t i, int64_t gtiles) {
+    return ((i | gtiles) >> 32) == 0 ? (int64_t)((uint32_t)i / (uint32_t)gtiles) : i / gtiles;
+}
+
+// Where a kernel finds the plan: staged into the workspace, or, when it is
+// small, among the kernel's own arguments, which saves the launch that stages
+// it and the first trip to memory of every look-up (launch_plan_arg).
+struct StagedPlan {
+    const SigPlan* p;
+    static constexpr bool kChunkTable = true;
+    __device__ const SigPlan* plan() const { return p; }
+    __device__ char* workspace() const {
+        return const_cast<char*>(reinterpret_cast<const char*>(p));
+    }
+};
+struct ArgPlan {
+    alignas(16) unsigned char bytes[kArgPlanBytes];
+    char* ws;
+    static constexpr bool kChunkTable = false;      // the chunk-to-tensor table stays behind
+    __device__ const SigPlan* plan() const { return reinterpret_cast<const SigPlan*>(bytes); }
+    __device__ char* workspace() const { return ws; }
+};
+
+template <typename F>
+static void with_plan(const PlanSource& src, const F& launch) {
+    if (src.arg_bytes != 0) {
+        ArgPlan a;
+        memcpy(a.bytes, src.arg, src.arg_bytes);
+        a.ws = static_cast<char*>(src.ws);
+        launch(a);
+    } else {
+        launch(StagedPlan{static_cast<const SigPlan*>(src.ws)});
+    }
 }
 
 // The plan's arrays, and where a tile's bytes are.
@@ -77,7 +131,9 @@ struct PlanView {
     const int64_t* gtile;
     const TensorInfo* tinfo;
     TilePartial* partials;
-    __device__ explicit PlanView(const SigPlan* plan) {
+    template <typename P>
+    __device__ explicit PlanView(const P& src) {
+        const SigPlan* plan = src.plan();
         const char* pb = reinterpret_cast<const char*>(plan);
         ptrs = reinterpret_cast<const uint64_t*>(pb + plan->off_ptrs);
         tile_base = reinterpret_cast<const int64_t*>(pb + plan->off_tile_base);
@@ -85,7 +141,7 @@ struct PlanView {
         order = reinterpret_cast<const int32_t*>(pb + plan->off_order);
         gtile = reinterpret_cast<const int64_t*>(pb + plan->off_gtile);
         tinfo = reinterpret_cast<const TensorInfo*>(pb + plan->off_tmeta);
-        partials = reinterpret_cast<TilePartial*>(const_cast<char*>(pb) + plan->off_partials);
+        partials = reinterpret_cast<TilePartial*>(src.workspace() + plan->off_partials);
     }
 };
 
@@ -131,15 +187,17 @@ __device__ inline LaneFold<4 / NW> fold_tile(int dtype, const uint8_t* tile, uin
 // with DT = kMixed.
 //
 // One workgroup per tile.
-template <int DT, int U>
+template <int DT, int U, typename P>
 __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
-    signature_kernel(const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records,
-                     int gk0, int gk1, int64_t gtiles, int mapped) {
+    signature_kernel(const P src, c3_chunk_record_t* __restrict__ records, int gk0, int gk1,
+                     int64_t gtiles, int mapped, uint32_t* clear) {
+    if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0u;
+    const SigPlan* const plan = src.plan();
     __shared__ TilePartial lds[kSigThreads / 64];
     const int lane = threadIdx.x & 63;
     // the wave index, uniform across the wave (keeps beta and addresses scalar)
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const PlanView pv(plan);
+    const PlanView pv(src);
     const int T = plan->T;
     const int64_t ntiles = gtiles * plan->R;
     const uint64_t tile_bytes = plan->tile_bytes, chunk_bytes = plan->chunk_bytes;
@@ -151,9 +209,9 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
     // tiles blockIdx.x, blockIdx.x + gridDim.x, ...
     for (int64_t i = mapped ? xcd_map_tile(blockIdx.x, ntiles) : (int64_t)blockIdx.x; i < ntiles;
          i += mapped ? ntiles : (int64_t)gridDim.x) {
-        const int64_t r = i / gtiles;
+        const int64_t r = replica_of(i, gtiles);
         const int64_t j = g0 + (i - r * gtiles);
-        const int k = gk0 + find_segment(pv.gtile + gk0, gk1 - gk0, j);
+        const int k = gk0 + find_segment_wave(pv.gtile + gk0, gk1 - gk0, j, lane);
         const int t = pv.order[k];
         const int64_t lt = j - pv.gtile[k];
         const TileSpan ts = tile_span((uint64_t)lt, tpc, chunk_bytes, tile_bytes, pv.tinfo[t].nbytes);
@@ -194,15 +252,17 @@ struct RunTile {
     uint32_t len;
 };
 
-template <int DT, int U>
+template <int DT, int U, typename P>
 __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
-    signature_wave_kernel(const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records,
-                          int gk0, int gk1, int64_t gtiles, int run) {
+    signature_wave_kernel(const P src, c3_chunk_record_t* __restrict__ records, int gk0, int gk1,
+                          int64_t gtiles, int run, uint32_t* clear) {
+    if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0u;
+    const SigPlan* const plan = src.plan();
     __shared__ RunTile done[kSigThreads / 64][kWaveRunMax];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t ntiles = gtiles * plan->R;
-    const PlanView pv(plan);
+    const PlanView pv(src);
     const int T = plan->T;
     const uint64_t tile_bytes = plan->tile_bytes, chunk_bytes = plan->chunk_bytes;
     const uint32_t tpc = plan->tiles_per_chunk;
@@ -213,9 +273,9 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
          w += (int64_t)gridDim.x * (kSigThreads / 64)) {
         const int64_t i0 = w * run;
         const int count = (int)min((int64_t)run, ntiles - i0);
-        int64_t r = i0 / gtiles;
+        int64_t r = replica_of(i0, gtiles);
         int64_t j = g0 + (i0 - r * gtiles);
-        int k = gk0 + find_segment(pv.gtile + gk0, gk1 - gk0, j);
+        int k = gk0 + find_segment_wave(pv.gtile + gk0, gk1 - gk0, j, lane);
         for (int m = 0; m < count; ++m, ++j) {
             if (j == g0 + gtiles) {                    // on to the next replica
                 ++r;
@@ -254,11 +314,16 @@ struct ChunkParts {
     int t;
 };
 
-__device__ inline ChunkParts chunk_parts(const SigPlan* __restrict__ plan, int64_t r, int64_t c) {
+template <typename P>
+__device__ inline ChunkParts chunk_parts(const P& src, int64_t r, int64_t c) {
+    const SigPlan* const plan = src.plan();
     const char* pb = reinterpret_cast<const char*>(plan);
-    const PlanView pv(plan);
+    const PlanView pv(src);
     ChunkParts o;
-    o.t = reinterpret_cast<const int32_t*>(pb + plan->off_chunk_tensor)[c];
+    if constexpr (P::kChunkTable)
+        o.t = reinterpret_cast<const int32_t*>(pb + plan->off_chunk_tensor)[c];
+    else
+        o.t = find_segment(pv.chunk_base, plan->T, c);
     o.k = (uint64_t)(c - pv.chunk_base[o.t]);
     const uint64_t nbytes = pv.tinfo[o.t].nbytes;
     const int64_t tb = pv.tile_base[o.t];
@@ -273,25 +338,27 @@ __device__ inline ChunkParts chunk_parts(const SigPlan* __restrict__ plan, int64
 
 // Record of (replica r, chunk c) by one thread, where a chunk has at most
 // kThreadCombine tiles.
-__device__ inline void combine_chunk(const SigPlan* __restrict__ plan, int64_t r, int64_t c,
-                                     c3_chunk_record_t* out) {
-    const ChunkParts cp = chunk_parts(plan, r, c);
+template <typename P>
+__device__ inline void combine_chunk(const P& src, int64_t r, int64_t c, c3_chunk_record_t* out) {
+    const ChunkParts cp = chunk_parts(src, r, c);
     const TilePartial p = combine_few(cp.pp, (int)cp.nt);
-    write_record(out, PlanView(plan).tinfo[cp.t], cp.t, cp.k, cp.n, p);
+    write_record(out, PlanView(src).tinfo[cp.t], cp.t, cp.k, cp.n, p);
 }
 
 // Combine the partials of each (replica, chunk), sixteen lanes each.
-__global__ void __launch_bounds__(256) finalize_kernel(const SigPlan* __restrict__ plan,
+template <typename P>
+__global__ void __launch_bounds__(256) finalize_kernel(const P src,
                                                        c3_chunk_record_t* __restrict__ records) {
+    const SigPlan* const plan = src.plan();
     const int64_t C = plan->C;
     const int64_t total = C * plan->R;
     const int l = threadIdx.x & 15;
     for (int64_t idx = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); idx < total;
          idx += (int64_t)gridDim.x * 16) {
         const int64_t r = idx / C;
-        const ChunkParts cp = chunk_parts(plan, r, idx - r * C);
+        const ChunkParts cp = chunk_parts(src, r, idx - r * C);
         const TilePartial p = combine_row(cp.pp, cp.nt, l);
-        if (l == 0) write_record(&records[idx], PlanView(plan).tinfo[cp.t], cp.t, cp.k, cp.n, p);
+        if (l == 0) write_record(&records[idx], PlanView(src).tinfo[cp.t], cp.t, cp.k, cp.n, p);
     }
 }
 
@@ -304,18 +371,20 @@ __global__ void __launch_bounds__(256) finalize_kernel(const SigPlan* __restrict
 // ---------------------------------------------------------------------------
 enum { kTailReady = 0, kTailThread = 1, kTailRow = 2 };
 
+template <typename P>
 __global__ void __launch_bounds__(kTailThreads) small_tail_kernel(
-    const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records, int mode, TailOut out) {
+    const P src, c3_chunk_record_t* __restrict__ records, int mode, TailOut out) {
+    const SigPlan* const plan = src.plan();
     __shared__ c3_chunk_record_t rec[kTailMaxRecords];
     const int R = plan->R;
     const int C = (int)plan->C;
     if (mode == kTailRow) {
         const int l = threadIdx.x & 15;
         for (int i = threadIdx.x >> 4; i < R * C; i += kTailThreads / 16) {
-            const ChunkParts cp = chunk_parts(plan, i / C, i % C);
+            const ChunkParts cp = chunk_parts(src, i / C, i % C);
             const TilePartial p = combine_row(cp.pp, cp.nt, l);
             if (l == 0) {
-                write_record(&rec[i], PlanView(plan).tinfo[cp.t], cp.t, cp.k, cp.n, p);
+                write_record(&rec[i], PlanView(src).tinfo[cp.t], cp.t, cp.k, cp.n, p);
                 records[i] = rec[i];
             }
         }
@@ -324,7 +393,7 @@ __global__ void __launch_bounds__(kTailThreads) small_tail_kernel(
             if (mode == kTailReady) {
                 rec[i] = records[i];
             } else {
-                combine_chunk(plan, i / C, i % C, &rec[i]);
+                combine_chunk(src, i / C, i % C, &rec[i]);
                 records[i] = rec[i];
             }
         }
@@ -336,12 +405,15 @@ bool small_tail_fits(int R, int64_t C) {
     return C >= 1 && C <= kTailMaxChunks && R * C <= kTailMaxRecords;
 }
 
-hipError_t launch_small_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
+hipError_t launch_small_tail(const PlanSource& src, const SigPlan& hplan, c3_chunk_record_t* records,
                              bool ready, const TailOut& out, hipStream_t stream) {
     const int mode = ready ? kTailReady
                      : hplan.tiles_per_chunk <= (uint32_t)kThreadCombine ? kTailThread : kTailRow;
-    hipLaunchKernelGGL(small_tail_kernel, dim3(1), dim3(kTailThreads), 0, stream, dplan, records,
-                       mode, out);
+    with_plan(src, [&](const auto& p) {
+        using P = std::decay_t<decltype(p)>;
+        hipLaunchKernelGGL(small_tail_kernel<P>, dim3(1), dim3(kTailThreads), 0, stream, p, records,
+                           mode, out);
+    });
     return hipGetLastError();
 }
 
@@ -356,9 +428,8 @@ bool finalize_first(const SigPlan& hplan, bool small) {
 // ---------------------------------------------------------------------------
 // Tail of c3_check: the records of every (replica, chunk) from their tile
 // partials (at most kThreadCombine a chunk) or as the streaming or finalize
-// kernel wrote them (`ready`), the exact vote of every chunk (exact_vote_row, the rule of
-// c3_consensus) and the lists of c3_localize, in two launches.
-// check_vote_kernel:
+// kernel wrote them (`ready`), the exact vote of every chunk (exact_vote_row,
+// the rule of c3_consensus) and the lists of c3_localize, in one launch:
 //   - a workgroup of kCheckThreads threads takes CPB = kCheckThreads / N
 //     consecutive chunks (a segment), one thread per (chunk, replica slot),
 //     so the R records of a chunk are combined in parallel and meet in LDS;
@@ -366,11 +437,17 @@ bool finalize_first(const SigPlan& hplan, bool small) {
 //   - with a staging area, the first wave scans the segment's outlier and
 //     undecided counts (CPB <= 64 units: one wave) and writes the segment's
 //     entries, summaries taken from the records in LDS, into the segment's
-//     slots of the staging area, with the three counts.
-// check_lists_kernel (one workgroup): scans the segments' counts in segment
-// order and copies every staged entry to its place in the caller's lists.
-// Segments are in chunk order and entries in (chunk, replica) order inside
-// a segment, so the lists come out in c3_localize's order.
+//     slots of the staging area, with the three counts in one word;
+//   - the workgroup that arrives last scans the segments' counts in segment
+//     order and copies every staged entry to its place in the caller's lists.
+//     Segments are in chunk order and entries in (chunk, replica) order inside
+//     a segment, so the lists come out in c3_localize's order.
+// The handoff passes the staging area only, a few KiB, so it goes through
+// agent-scope accesses, which meet where all XCDs look, and a wait for them
+// before the arrival is counted; an agent-scope release would write back the
+// XCD's whole L2, once per workgroup (17.9 us for the tail against 14 for two
+// launches when that was tried).  The counter is cleared by the streaming
+// kernel of the same call.
 // ---------------------------------------------------------------------------
 constexpr int kCheckThreads = 256;
 constexpr int kCheckMaxListUnits = 8192;   // chunks whose lists go through the staging area
@@ -380,22 +457,96 @@ constexpr int kCheckMaxSegments = kCheckMaxListUnits / (kCheckThreads / 32);
 static_assert(64ll * kCheckThreads / 2 < (1ll << 24) && 64 * 64 < (1 << 20), "packed counts");
 
 struct CheckStage {
-    int32_t* seg_counts;      // [n_seg][4]: outliers, undecided, attributed units
+    uint64_t* seg;            // [n_seg]: outliers (24 bits), undecided and attributed units (20 each)
+    uint32_t* done;           // workgroups that have staged their segment
     c3_outlier_t* out;        // [n_seg][out_per_seg]
     int64_t* und;             // [n_seg][CPB]
     int32_t out_per_seg;
     int32_t cpb;
 };
+struct CheckLists {
+    c3_outlier_t* outliers;
+    int64_t out_cap;
+    int64_t* undecided;
+    int64_t und_cap;
+    int64_t* counts;
+};
 
-template <int N>
+__device__ __forceinline__ void agent_store(void* p, uint64_t v) {
+    __hip_atomic_store(static_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t agent_load(const void* p) {
+    return __hip_atomic_load(static_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+constexpr int kOutlierWords = sizeof(c3_outlier_t) / 8;
+static_assert(sizeof(c3_outlier_t) % 8 == 0, "entries are copied in words");
+
+// The lists from the staged segments, by one workgroup.  seg_word, off_o and
+// off_u: kCheckMaxSegments entries each in LDS.
+__device__ inline void place_lists(const CheckStage& stage, int n_seg, const CheckLists& lists,
+                                   uint64_t* seg_word, int32_t* off_o, int32_t* off_u) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave == 0) {
+        // segment offsets in segment order: one wave, 64 segments per step
+        int64_t carry_o = 0, carry_u = 0, carry_a = 0;
+        for (int base = 0; base < n_seg; base += 64) {
+            const int sgi = base + lane;
+            const uint64_t packed = sgi < n_seg ? agent_load(&stage.seg[sgi]) : 0ull;
+            const uint64_t incl = wave_inclusive_scan(packed, lane);
+            const uint64_t excl = incl - packed;
+            if (sgi < n_seg) {
+                seg_word[sgi] = packed;
+                off_o[sgi] = (int32_t)(carry_o + (int64_t)(excl & 0xFFFFFFull));
+                off_u[sgi] = (int32_t)(carry_u + (int64_t)((excl >> 24) & 0xFFFFFull));
+            }
+            const uint64_t tot = shfl_u64(incl, 63);
+            carry_o += (int64_t)(tot & 0xFFFFFFull);
+            carry_u += (int64_t)((tot >> 24) & 0xFFFFFull);
+            carry_a += (int64_t)((tot >> 44) & 0xFFFFFull);
+        }
+        if (lane == 0) {
+            lists.counts[0] = carry_o;
+            lists.counts[1] = carry_u;
+            lists.counts[2] = carry_a;
+        }
+    }
+    __syncthreads();
+    for (int sgi = wave; sgi < n_seg; sgi += kCheckThreads / 64) {
+        const int n_o = (int)(seg_word[sgi] & 0xFFFFFFull), n_u = (int)((seg_word[sgi] >> 24) & 0xFFFFFull);
+        const c3_outlier_t* so = stage.out + (int64_t)sgi * stage.out_per_seg;
+        for (int j = lane; j < n_o; j += 64) {
+            const int64_t d = (int64_t)off_o[sgi] + j;
+            if (d >= lists.out_cap) continue;
+            uint64_t w[kOutlierWords];
+#pragma unroll
+            for (int i = 0; i < kOutlierWords; ++i)
+                w[i] = agent_load(reinterpret_cast<const uint64_t*>(&so[j]) + i);
+#pragma unroll
+            for (int i = 0; i < kOutlierWords; ++i) reinterpret_cast<uint64_t*>(&lists.outliers[d])[i] = w[i];
+        }
+        for (int j = lane; j < n_u; j += 64) {
+            const int64_t d = (int64_t)off_u[sgi] + j;
+            if (d < lists.und_cap)
+                lists.undecided[d] = (int64_t)agent_load(&stage.und[(int64_t)sgi * stage.cpb + j]);
+        }
+    }
+}
+
+template <int N, typename P>
 __global__ void __launch_bounds__(kCheckThreads) check_vote_kernel(
-    const SigPlan* __restrict__ plan, c3_chunk_record_t* __restrict__ records,
+    const P src, c3_chunk_record_t* __restrict__ records,
     bool ready, uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap,
-    int32_t* __restrict__ majority, CheckStage stage) {
+    int32_t* __restrict__ majority, CheckStage stage, CheckLists lists) {
     constexpr int CPB = kCheckThreads / N;
     static_assert(CPB <= 64, "a segment's units must fit one wave");
-    __shared__ c3_chunk_record_t rec[CPB][N];
+    // the records; after them, in the last workgroup, the segments' counts
+    // and offsets
+    __shared__ __align__(16) unsigned char shared[CPB * N * sizeof(c3_chunk_record_t)];
+    static_assert(sizeof(shared) >= kCheckMaxSegments * 16, "segment tables");
+    c3_chunk_record_t(*rec)[N] = reinterpret_cast<c3_chunk_record_t(*)[N]>(shared);
     __shared__ UnitVote votes[CPB];
+    __shared__ uint32_t arrived;
+    const SigPlan* const plan = src.plan();
     const int R = plan->R;
     const int64_t C = plan->C;
     const int slot = threadIdx.x % N;
@@ -407,7 +558,7 @@ __global__ void __launch_bounds__(kCheckThreads) check_vote_kernel(
             rec[cu][slot] = *dst;
         } else {
             c3_chunk_record_t r;
-            combine_chunk(plan, slot, c, &r);
+            combine_chunk(src, slot, c, &r);
             *dst = r;
             rec[cu][slot] = r;
         }
@@ -426,7 +577,7 @@ __global__ void __launch_bounds__(kCheckThreads) check_vote_kernel(
             votes[threadIdx.x] = v;
         }
     }
-    if (stage.seg_counts == nullptr) return;
+    if (stage.seg == nullptr) return;
     __syncthreads();
     if (threadIdx.x < 64) {
         // this segment's entries, in (chunk, replica) order, into its slots
@@ -438,82 +589,37 @@ __global__ void __launch_bounds__(kCheckThreads) check_vote_kernel(
         const uint64_t n_o =
             valid && v.status != C3_INCONCLUSIVE ? (uint64_t)__builtin_popcountll(v.bitmap) : 0ull;
         const uint64_t n_u = valid && v.status == C3_INCONCLUSIVE ? 1ull : 0ull;
-        const uint64_t packed = n_o | (n_u << 32);
+        const uint64_t packed = n_o | (n_u << 24) | ((uint64_t)(n_o != 0ull) << 44);
         const uint64_t incl = wave_inclusive_scan(packed, lane);
-        uint64_t po = (uint32_t)(incl - packed);
-        const uint64_t pu = (incl - packed) >> 32;
+        const uint64_t excl = incl - packed;
+        uint64_t po = excl & 0xFFFFFFull;
+        const uint64_t pu = (excl >> 24) & 0xFFFFFull;
         c3_outlier_t* so = stage.out + (int64_t)blockIdx.x * stage.out_per_seg;
-        for (uint64_t b = n_o ? v.bitmap : 0ull; b != 0ull; b &= b - 1ull) {
+        for (uint64_t b = n_o ? v.bitmap : 0ull; b != 0ull; b &= b - 1ull, ++po) {
             const int r = __builtin_ctzll(b);
-            c3_outlier_t o;
-            outlier_from(o, u, r, v.majority, rec[lane][r], rec[lane][v.majority]);
-            so[po++] = o;
+            union {
+                c3_outlier_t o;
+                uint64_t w[kOutlierWords];
+            } e;
+            outlier_from(e.o, u, r, v.majority, rec[lane][r], rec[lane][v.majority]);
+#pragma unroll
+            for (int i = 0; i < kOutlierWords; ++i)
+                agent_store(reinterpret_cast<uint64_t*>(&so[po]) + i, e.w[i]);
         }
-        if (n_u) stage.und[(int64_t)blockIdx.x * CPB + (int64_t)pu] = u;
-        const uint64_t tot = shfl_u64(incl, 63);
-        const uint64_t n_att = (uint64_t)__builtin_popcountll(ballot64(n_o != 0ull));
-        if (lane == 0) {
-            int32_t* sc = stage.seg_counts + 4 * (int64_t)blockIdx.x;
-            sc[0] = (int32_t)(uint32_t)tot;
-            sc[1] = (int32_t)(tot >> 32);
-            sc[2] = (int32_t)n_att;
-        }
-    }
-}
-
-__global__ void __launch_bounds__(kCheckThreads) check_lists_kernel(
-    CheckStage stage, int n_seg, c3_outlier_t* __restrict__ outliers, int64_t out_cap,
-    int64_t* __restrict__ undecided, int64_t und_cap, int64_t* __restrict__ counts) {
-    __shared__ int64_t seg_off[2][kCheckMaxSegments];
-    __shared__ int32_t seg_n[2][kCheckMaxSegments];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (wave == 0) {
-        // segment offsets in segment order: one wave, 64 segments per step,
-        // the three counts packed into one word (outliers 24 bits, undecided
-        // and attributed 20 bits each: a step of 64 segments holds fewer
-        // than 64 * kCheckThreads / 2 outliers and at most 64 * 64 units)
-        int64_t carry_o = 0, carry_u = 0, carry_a = 0;
-        for (int base = 0; base < n_seg; base += 64) {
-            const int sgi = base + lane;
-            uint64_t o = 0, un = 0, at = 0;
-            if (sgi < n_seg) {
-                const int32_t* sc = stage.seg_counts + 4 * (int64_t)sgi;
-                o = (uint32_t)sc[0];
-                un = (uint32_t)sc[1];
-                at = (uint32_t)sc[2];
-            }
-            const uint64_t packed = o | (un << 24) | (at << 44);
-            const uint64_t incl = wave_inclusive_scan(packed, lane);
-            const uint64_t excl = incl - packed;
-            if (sgi < n_seg) {
-                seg_off[0][sgi] = carry_o + (int64_t)(excl & 0xFFFFFFull);
-                seg_off[1][sgi] = carry_u + (int64_t)((excl >> 24) & 0xFFFFFull);
-                seg_n[0][sgi] = (int32_t)o;
-                seg_n[1][sgi] = (int32_t)un;
-            }
-            const uint64_t tot = shfl_u64(incl, 63);
-            carry_o += (int64_t)(tot & 0xFFFFFFull);
-            carry_u += (int64_t)((tot >> 24) & 0xFFFFFull);
-            carry_a += (int64_t)((tot >> 44) & 0xFFFFFull);
-        }
-        if (lane == 0) {
-            counts[0] = carry_o;
-            counts[1] = carry_u;
-            counts[2] = carry_a;
-        }
+        if (n_u) agent_store(&stage.und[(int64_t)blockIdx.x * CPB + (int64_t)pu], (uint64_t)u);
+        if (lane == 63) agent_store(&stage.seg[blockIdx.x], incl);
+        // every staged store of this wave has reached the point where all
+        // XCDs see it before the workgroup counts itself in
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0)
+            arrived = __hip_atomic_fetch_add(stage.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    for (int sgi = wave; sgi < n_seg; sgi += kCheckThreads / 64) {
-        const c3_outlier_t* so = stage.out + (int64_t)sgi * stage.out_per_seg;
-        for (int j = lane; j < seg_n[0][sgi]; j += 64) {
-            const int64_t d = seg_off[0][sgi] + j;
-            if (d < out_cap) outliers[d] = so[j];
-        }
-        for (int j = lane; j < seg_n[1][sgi]; j += 64) {
-            const int64_t d = seg_off[1][sgi] + j;
-            if (d < und_cap) undecided[d] = stage.und[(int64_t)sgi * stage.cpb + j];
-        }
-    }
+    if (arrived != gridDim.x - 1) return;              // the whole workgroup leaves together
+    asm volatile("" ::: "memory");
+    uint64_t* seg_word = reinterpret_cast<uint64_t*>(shared);
+    int32_t* off = reinterpret_cast<int32_t*>(seg_word + kCheckMaxSegments);
+    place_lists(stage, (int)gridDim.x, lists, seg_word, off, off + kCheckMaxSegments);
 }
 
 int check_group_bound(int R) { return R <= 4 ? 4 : R <= 8 ? 8 : R <= 16 ? 16 : R <= 32 ? 32 : 0; }
@@ -541,7 +647,14 @@ uint64_t check_stage_bytes(int R, int64_t C) {
     return check_stage_parts(N, C, a, b, c, o);
 }
 
-hipError_t launch_check_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chunk_record_t* records,
+// The arrival counter, after the segments' words (16 bytes are kept a segment).
+uint32_t* check_arrivals(int R, int64_t C, void* stage_ws) {
+    const int64_t cpb = kCheckThreads / check_group_bound(R);
+    const int64_t n_seg = (C + cpb - 1) / cpb;
+    return reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(stage_ws) + 8 * n_seg);
+}
+
+hipError_t launch_check_tail(const PlanSource& src, const SigPlan& hplan, c3_chunk_record_t* records,
                              bool ready, uint8_t* status, uint64_t* bitmap, int32_t* majority,
                              c3_outlier_t* outliers, int64_t out_cap, int64_t* undecided,
                              int64_t und_cap, int64_t* counts, void* stage_ws,
@@ -551,40 +664,34 @@ hipError_t launch_check_tail(const SigPlan* dplan, const SigPlan& hplan, c3_chun
     const int64_t cpb = kCheckThreads / N;
     const int64_t blocks = (hplan.C + cpb - 1) / cpb;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    CheckStage st{nullptr, nullptr, nullptr, 0, (int32_t)cpb};
+    CheckStage st{nullptr, nullptr, nullptr, nullptr, 0, (int32_t)cpb};
+    const CheckLists lists{outliers, out_cap, undecided, und_cap, counts};
     if (stage_ws != nullptr) {
         if (hplan.C > kCheckMaxListUnits) return hipErrorInvalidValue;
         uint64_t cnt_b, out_b, und_b;
         check_stage_parts(N, hplan.C, cnt_b, out_b, und_b, st.out_per_seg);
         unsigned char* w = static_cast<unsigned char*>(stage_ws);
-        st.seg_counts = reinterpret_cast<int32_t*>(w);
+        st.seg = reinterpret_cast<uint64_t*>(w);
+        st.done = check_arrivals(hplan.R, hplan.C, stage_ws);
         w += (cnt_b + 255) / 256 * 256;
         st.out = reinterpret_cast<c3_outlier_t*>(w);
         w += (out_b + 255) / 256 * 256;
         st.und = reinterpret_cast<int64_t*>(w);
     }
-    switch (N) {
-        case 4:
-            hipLaunchKernelGGL(check_vote_kernel<4>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, ready, status, bitmap, majority, st);
-            break;
-        case 8:
-            hipLaunchKernelGGL(check_vote_kernel<8>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, ready, status, bitmap, majority, st);
-            break;
-        case 16:
-            hipLaunchKernelGGL(check_vote_kernel<16>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, ready, status, bitmap, majority, st);
-            break;
-        default:
-            hipLaunchKernelGGL(check_vote_kernel<32>, dim3((unsigned)blocks), dim3(kCheckThreads), 0,
-                               stream, dplan, records, ready, status, bitmap, majority, st);
-            break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || stage_ws == nullptr) return e;
-    hipLaunchKernelGGL(check_lists_kernel, dim3(1), dim3(kCheckThreads), 0, stream, st,
-                       (int)blocks, outliers, out_cap, undecided, und_cap, counts);
+    with_plan(src, [&](const auto& p) {
+        using P = std::decay_t<decltype(p)>;
+        auto vote = [&](auto n) {
+            hipLaunchKernelGGL((check_vote_kernel<decltype(n)::value, P>), dim3((unsigned)blocks),
+                               dim3(kCheckThreads), 0, stream, p, records, ready, status, bitmap,
+                               majority, st, lists);
+        };
+        switch (N) {
+            case 4: vote(std::integral_constant<int, 4>{}); break;
+            case 8: vote(std::integral_constant<int, 8>{}); break;
+            case 16: vote(std::integral_constant<int, 16>{}); break;
+            default: vote(std::integral_constant<int, 32>{}); break;
+        }
+    });
     return hipGetLastError();
 }
 
@@ -658,9 +765,9 @@ static bool wave_tiles(int dt, uint64_t tile_bytes, int64_t ntiles) {
 }
 
 template <int DT>
-static hipError_t launch_group(const SigPlan* dplan, c3_chunk_record_t* records, int gk0, int gk1,
+static hipError_t launch_group(const PlanSource& src, c3_chunk_record_t* records, int gk0, int gk1,
                                int64_t gtiles, int R, uint64_t tile_bytes, int grid_blocks,
-                               hipStream_t stream) {
+                               uint32_t* clear, hipStream_t stream) {
     const int64_t ntiles = gtiles * R;
     if (ntiles <= 0) return hipSuccess;
     if (wave_tiles(DT, tile_bytes, ntiles)) {
@@ -674,8 +781,11 @@ static hipError_t launch_group(const SigPlan* dplan, c3_chunk_record_t* records,
         int64_t grid = (ntiles + per - 1) / per;
         if (grid_blocks > 0 && grid > grid_blocks) grid = grid_blocks;
         if (grid > 0x7FFFFFFF) grid = 0x7FFFFFFF;
-        hipLaunchKernelGGL((signature_wave_kernel<DT, kUnroll>), dim3((unsigned)grid),
-                           dim3(kSigThreads), 0, stream, dplan, records, gk0, gk1, gtiles, (int)run);
+        with_plan(src, [&](const auto& p) {
+            using P = std::decay_t<decltype(p)>;
+            hipLaunchKernelGGL((signature_wave_kernel<DT, kUnroll, P>), dim3((unsigned)grid),
+                               dim3(kSigThreads), 0, stream, p, records, gk0, gk1, gtiles, (int)run, clear);
+        });
         return hipGetLastError();
     }
     int64_t grid = grid_blocks > 0 ? grid_blocks : ntiles;
@@ -683,14 +793,17 @@ static hipError_t launch_group(const SigPlan* dplan, c3_chunk_record_t* records,
     const int mapped = grid_blocks <= 0 && xcd_map_applies(ntiles, tile_bytes);
     if (mapped) grid = xcd_map_grid(ntiles);
     if (grid > 0x7FFFFFFF) grid = 0x7FFFFFFF;
-    hipLaunchKernelGGL((signature_kernel<DT, kUnroll>), dim3((unsigned)grid), dim3(kSigThreads), 0,
-                       stream, dplan, records, gk0, gk1, gtiles, mapped);
+    with_plan(src, [&](const auto& p) {
+        using P = std::decay_t<decltype(p)>;
+        hipLaunchKernelGGL((signature_kernel<DT, kUnroll, P>), dim3((unsigned)grid), dim3(kSigThreads),
+                           0, stream, p, records, gk0, gk1, gtiles, mapped, clear);
+    });
     return hipGetLastError();
 }
 
-hipError_t launch_signature(const SigPlan* dplan, const SigPlan& hplan, const SigGroups& groups,
+hipError_t launch_signature(const PlanSource& src, const SigPlan& hplan, const SigGroups& groups,
                             c3_chunk_record_t* records, int grid_blocks, bool finalize,
-                            hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
+                            uint32_t* clear, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
     hipError_t e;
     if (ev0 && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
     int only = -1, types = 0;
@@ -703,8 +816,8 @@ hipError_t launch_signature(const SigPlan* dplan, const SigPlan& hplan, const Si
         constexpr int DT = decltype(dt)::value;
         const int gk0 = DT == kMixed ? 0 : groups.k0[only], gk1 = DT == kMixed ? hplan.T : groups.k1[only];
         const int64_t gt = DT == kMixed ? hplan.tiles_per_replica : groups.tiles[only];
-        return launch_group<DT>(dplan, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks,
-                                stream);
+        return launch_group<DT>(src, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks,
+                                clear, stream);
     };
     // several types in one launch: a launch for each drains the chip between
     // them (767-wide layers with fp32 norms and fp16 biases: 20 us of 320)
@@ -718,8 +831,11 @@ hipError_t launch_signature(const SigPlan* dplan, const SigPlan& hplan, const Si
     if (!hplan.direct && finalize) {
         const int64_t total = hplan.C * hplan.R;
         const int64_t blocks = (total + 15) / 16 < 65536 ? (total + 15) / 16 : 65536;
-        hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, dplan,
-                           records);
+        with_plan(src, [&](const auto& p) {
+            using P = std::decay_t<decltype(p)>;
+            hipLaunchKernelGGL(finalize_kernel<P>, dim3((unsigned)blocks), dim3(256), 0, stream, p,
+                               records);
+        });
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

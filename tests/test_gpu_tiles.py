@@ -134,3 +134,36 @@ def test_partials_combined_alike(tiles, R, chunks):
     assert np.array_equal(c3.outliers_numpy(outl, cnt), c3.outliers_numpy(outl2, cnt2))
     if R <= 8:
         compare_all_records(c3.records_numpy(rec), _oracle(reps, chunk))
+
+
+# the plan as a kernel argument (up to 3.5 KB of it, and 8,192 tiles under 256
+# KiB) and staged in the workspace; a second call that says its plan is still
+# there reads the tensors as they are then
+@pytest.mark.parametrize("R,T,n", [(2, 1, 5000), (2, 9, 900), (2, 10, 900), (2, 11, 900), (2, 12, 900),
+                                   (32, 5, 300), (64, 3, 300), (64, 4, 300), (2, 2, 1024 * 1024 // 4 * 2),
+                                   (2, 2, 1024 * 1024 // 4 * 2 + 1), (3, 70, 500), (2, 130, 3000)])
+def test_plan_argument_and_staged(R, T, n):
+    print("CASE plan", R, T, n, flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(R * 100 + T)
+    types = (torch.float32, torch.bfloat16, torch.uint8) if n < 10_000 else (torch.float32,)
+    base = [_tensor(types[i % len(types)], n + i, gen) for i in range(T)]
+    reps = [base] + [[t.clone() for t in base] for _ in range(R - 1)]
+    for chunk, tile in ((KIB, 0), (3 * KIB, KIB), (KIB * 1024, 0)):
+        plan = c3.SignaturePlan(reps, chunk, tile)
+        outs = plan.new_check_outputs()
+        ws = torch.empty(plan.check_workspace_size(), dtype=torch.uint8, device=DEV)
+        plan.run_check(outs, ws)
+        first = outs[0].clone()
+        compare_all_records(c3.records_numpy(outs[0][:2]), _oracle(reps[:2], chunk))
+        assert outs[6].cpu().tolist() == [0, 0, 0]
+        reps[R - 1][T - 1].view(torch.uint8)[7] ^= 1
+        plan.run_check(outs, ws, plan_staged=True)
+        assert outs[6].cpu().tolist() == ([1, 0, 1] if R > 2 else [0, 1, 0])
+        reps[R - 1][T - 1].view(torch.uint8)[7] ^= 1
+        sig_ws = plan.new_workspace()
+        rec = plan.new_records()
+        plan.run(rec, sig_ws)
+        plan.run(rec, sig_ws, plan_staged=True)
+        torch.cuda.synchronize()
+        assert torch.equal(rec, first)
