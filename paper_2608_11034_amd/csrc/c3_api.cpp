@@ -762,11 +762,17 @@ int c3_timing_consensus(const uint64_t* fingerprints, const void* times, int tim
         tb = t_bitmap;
         tm = t_majority;
     }
-    hipError_t e = c3::launch_consensus(fingerprints, C3_EV_U64, 8, 8 * (int64_t)R, R,
-                                        (int64_t)n, C3_EXACT, kappa, fs, fb, fm, s);
-    if (e == hipSuccess)
-        e = c3::launch_consensus(times, time_kind, tsize, (int64_t)tsize * R, R, (int64_t)n,
-                                 C3_STATISTICAL, kappa, ts, tb, tm, s);
+    hipError_t e;
+    if (R > 16) {
+        e = c3::launch_timing_votes_wide(fingerprints, times, time_kind, R, (int64_t)n, kappa,
+                                         fp_status, fb, fp_majority, t_status, tb, t_majority, s);
+    } else {
+        e = c3::launch_consensus(fingerprints, C3_EV_U64, 8, 8 * (int64_t)R, R, (int64_t)n, C3_EXACT,
+                                 kappa, fs, fb, fm, s);
+        if (e == hipSuccess)
+            e = c3::launch_consensus(times, time_kind, tsize, (int64_t)tsize * R, R, (int64_t)n,
+                                     C3_STATISTICAL, kappa, ts, tb, tm, s);
+    }
     if (e == hipSuccess) e = c3::launch_confirm(fb, tb, R, G, T, window, verdicts, cws, s);
     return e == hipSuccess ? C3_OK : C3_E_HIP;
 }

@@ -118,6 +118,14 @@ hipError_t launch_timing_consensus(const uint64_t* fp, const void* times, int ti
                                    uint8_t* t_status, uint64_t* t_bitmap, int32_t* t_majority,
                                    c3_rank_verdict_t* verdicts, void* ws, hipStream_t stream);
 
+// Exact vote on fingerprints [n_units][R] and statistical vote on times of the
+// same layout, 17 <= R <= 64, in one launch.  Bitmaps always, status and
+// majority of a kind unless its status is null.
+hipError_t launch_timing_votes_wide(const uint64_t* fp, const void* times, int time_kind, int R,
+                                    int64_t n_units, double kappa, uint8_t* f_status,
+                                    uint64_t* f_bitmap, int32_t* f_majority, uint8_t* t_status,
+                                    uint64_t* t_bitmap, int32_t* t_majority, hipStream_t stream);
+
 hipError_t launch_consensus(const void* evidence, int kind, int64_t rstride, int64_t ustride, int R,
                             int64_t n_units, int mode, double kappa, uint8_t* status,
                             uint64_t* bitmap, int32_t* majority_idx, hipStream_t stream);

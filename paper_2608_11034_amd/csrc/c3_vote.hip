@@ -311,38 +311,47 @@ __device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {
 constexpr int stat_least(int nl) { return nl == 2 ? 17 : nl == 4 ? 33 : nl == 8 ? 65 : nl == 12 ? 129 : 193; }
 constexpr int kStatUnits = kVoteThreads / 16;      // units per workgroup
 
-template <int NL, int KIND>
-__global__ void __launch_bounds__(kVoteThreads) statistical_vote_wide_kernel(
-    const char* __restrict__ ev, int64_t rstride, int64_t ustride, int R, int64_t n_units,
-    double kappa, uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap,
-    int32_t* __restrict__ majority_idx) {
-    // fp32 evidence is ordered and compared in fp32 (the widening to fp64 is
-    // exact and monotonic); every arithmetic step is fp64
-    using V = typename std::conditional<KIND == C3_EV_F32, float, double>::type;
-    constexpr int NS = (NL + 3) / 4;
-    constexpr int kPad = 16 / (int)sizeof(V);       // rows start on different LDS banks
-    const V inf = (V)__builtin_huge_val();
-    __shared__ __align__(16) V sorted[kStatUnits][16 * NL + kPad];
-    const int lane = threadIdx.x & 63, l = lane & 15, q4 = lane >> 4;
-    const int slot = threadIdx.x >> 4;
-    const int64_t u = (int64_t)blockIdx.x * kStatUnits + slot;
-    // whole waves past the end leave; lanes of a wave that is partly past it
-    // decide the last unit again and write nothing
-    if ((int64_t)blockIdx.x * kStatUnits + (threadIdx.x >> 6) * 4 >= n_units) return;
-    const bool live = u < n_units;
-    const char* row = ev + (live ? u : n_units - 1) * ustride;
-    V x[NL], k[NL];
-    uint32_t bad = 0;                               // bit j: replica 16 j + l is not finite
-#pragma unroll
-    for (int j = 0; j < NL; ++j) {
-        const int r = 16 * j + l;
-        const bool valid = 16 * (j + 1) <= stat_least(NL) || r < R;
-        x[j] = *reinterpret_cast<const V*>(row + (int64_t)(valid ? r : 0) * rstride);
-        if (!valid) x[j] = inf;
-        k[j] = __builtin_isfinite(x[j]) ? x[j] : inf;
-        bad |= (uint32_t)(valid && !__builtin_isfinite(x[j])) << j;
-        x[j] = k[j];                                // excluded values stay +inf
+// One group's decision: NS bitmap words, whether any bit is set, the majority
+// replica, and whether the unit is conclusive.
+template <int NL>
+struct GroupVote {
+    static constexpr int NS = (NL + 3) / 4;
+    uint64_t B[NS];
+    int mj;
+    bool ok, any;
+};
+
+template <int NL>
+__device__ __forceinline__ void write_group(const GroupVote<NL>& v, int64_t u, int l,
+                                            uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap,
+                                            int32_t* __restrict__ majority_idx) {
+    constexpr int NS = GroupVote<NL>::NS;
+    if (l == 0 && status != nullptr) {
+        status[u] = !v.ok ? (uint8_t)C3_INCONCLUSIVE : v.any ? (uint8_t)C3_ATTRIBUTED : (uint8_t)C3_AGREE;
+        majority_idx[u] = v.ok ? v.mj : -1;
     }
+#pragma unroll
+    for (int w = 0; w < NS; ++w)
+        if (l == w) bitmap[u * NS + w] = v.B[w];
+}
+
+// Whether replica 16 j + l exists, decided at compile time where NL says so.
+template <int NL>
+__device__ __forceinline__ bool group_valid(int j, int l, int R) {
+    return 16 * (j + 1) <= stat_least(NL) || 16 * j + l < R;
+}
+
+// The statistical decision of a unit whose sixteen lanes hold x (replica 16 j
+// + l in x[j], +inf where excluded; bit j of `bad`: a replica that is not
+// finite); s: 16 NL slots of LDS of their own.
+template <int NL, typename V>
+__device__ __forceinline__ GroupVote<NL> stat_group(const V (&x)[NL], uint32_t bad, int R, double kappa,
+                                                    V* s, int l, int q4) {
+    constexpr int NS = GroupVote<NL>::NS;
+    const V inf = (V)__builtin_huge_val();
+    V k[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) k[j] = x[j];
     int nf = R;
     const bool some_bad = ballot64(bad != 0u) != 0ull;
     if (some_bad) nf -= (int)row_sum_u32((uint32_t)__builtin_popcount(bad));
@@ -351,9 +360,8 @@ __global__ void __launch_bounds__(kVoteThreads) statistical_vote_wide_kernel(
     sort_lane<NL>(k, 0);
     sort_merge<2>(k, l);
 #pragma unroll
-    for (int i = 0; i < NL; ++i) sorted[slot][NL * l + i] = k[i];
+    for (int i = 0; i < NL; ++i) s[NL * l + i] = k[i];
     wave_lds_sync();
-    const V* s = sorted[slot];
     auto S = [&](int p) { return (double)s[p]; };
 
     const int pm = (n - 1) / 2;
@@ -441,7 +449,8 @@ __global__ void __launch_bounds__(kVoteThreads) statistical_vote_wide_kernel(
     const double thr = kappa * d;
     // the largest deviation is that of an end: the usual unit flags nothing
     const bool far = ok && d != 0.0 && fmax(fabs(s0 - m), fabs(s1 - m)) > thr;
-    uint64_t B[NS];
+    GroupVote<NL> v;
+    uint64_t (&B)[NS] = v.B;
 #pragma unroll
     for (int w = 0; w < NS; ++w) B[w] = 0;
     bool any = false;
@@ -456,14 +465,158 @@ __global__ void __launch_bounds__(kVoteThreads) statistical_vote_wide_kernel(
             any = any || bits != 0u;
         }
     }
-    if (!live) return;
-    if (l == 0) {
-        status[u] = !ok ? (uint8_t)C3_INCONCLUSIVE : any ? (uint8_t)C3_ATTRIBUTED : (uint8_t)C3_AGREE;
-        majority_idx[u] = ok ? mj : -1;
+    v.mj = mj;
+    v.ok = ok;
+    v.any = any;
+    return v;
+}
+
+// The exact decision of a unit whose sixteen lanes hold the bits e (replica
+// 16 j + l in e[j]).  The usual unit agrees with replica 0.  Otherwise a strict
+// majority has more than R / 2 members, so one of replicas 0 .. floor(R / 2)
+// holds it: they are tried in turn while some unit of the wave is undecided.
+template <int NL>
+__device__ __forceinline__ GroupVote<NL> exact_group(const uint64_t (&e)[NL], int R, int l, int q4) {
+    constexpr int NS = GroupVote<NL>::NS;
+    GroupVote<NL> v;
+#pragma unroll
+    for (int w = 0; w < NS; ++w) v.B[w] = 0;
+    v.mj = 0;
+    v.ok = true;
+    v.any = false;
+    auto from_lane = [&](uint64_t x, int src) { return shfl_u64(x, 16 * q4 + src); };
+    uint64_t cand = from_lane(e[0], 0);
+    bool differs = false;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) differs = differs || (group_valid<NL>(j, l, R) && e[j] != cand);
+    if (ballot64(differs) == 0ull) return v;
+    auto holders = [&](uint64_t c) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < NL; ++j) n += (uint32_t)(group_valid<NL>(j, l, R) && e[j] == c);
+        return (int)row_sum_u32(n);
+    };
+    bool found = 2 * holders(cand) > R;
+#pragma unroll
+    for (int j = 0; j < (NL + 1) / 2 + 1 && j < NL; ++j)
+        for (int src = 0; src < 16 && 16 * j + src <= R / 2; ++src) {
+            if (ballot64(!found) == 0ull) break;
+            const uint64_t c = from_lane(e[j], src);
+            const bool hit = !found && 2 * holders(c) > R;
+            cand = hit ? c : cand;
+            found = found || hit;
+        }
+    v.ok = found;
+    uint32_t lowest = 0xFFFFu;
+#pragma unroll
+    for (int j = NL - 1; j >= 0; --j) {
+        const bool valid = group_valid<NL>(j, l, R), eq = e[j] == cand;
+        lowest = valid && eq ? (uint32_t)(16 * j + l) : lowest;
+        const uint32_t bits = (uint32_t)(ballot64(found && valid && !eq) >> (16 * q4)) & 0xFFFFu;
+        v.B[j >> 2] |= (uint64_t)bits << (16 * (j & 3));
+        v.any = v.any || bits != 0u;
+    }
+    v.mj = (int)row_min_u32(lowest);
+    return v;
+}
+
+// x[j] of a unit's row, excluded values as +inf, and which are not finite.
+template <int NL, typename V>
+__device__ __forceinline__ uint32_t load_times(const char* row, int64_t rstride, int l, int R,
+                                               V (&x)[NL]) {
+    const V inf = (V)__builtin_huge_val();
+    uint32_t bad = 0;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+        const bool valid = group_valid<NL>(j, l, R);
+        x[j] = *reinterpret_cast<const V*>(row + (int64_t)(valid ? 16 * j + l : 0) * rstride);
     }
 #pragma unroll
-    for (int w = 0; w < NS; ++w)
-        if (l == w) bitmap[u * NS + w] = B[w];
+    for (int j = 0; j < NL; ++j) {
+        const bool valid = group_valid<NL>(j, l, R), fin = __builtin_isfinite(x[j]);
+        bad |= (uint32_t)(valid && !fin) << j;
+        x[j] = valid && fin ? x[j] : inf;
+    }
+    return bad;
+}
+
+template <int NL, int KIND>
+__global__ void __launch_bounds__(kVoteThreads) statistical_vote_wide_kernel(
+    const char* __restrict__ ev, int64_t rstride, int64_t ustride, int R, int64_t n_units,
+    double kappa, uint8_t* __restrict__ status, uint64_t* __restrict__ bitmap,
+    int32_t* __restrict__ majority_idx) {
+    // fp32 evidence is ordered and compared in fp32 (the widening to fp64 is
+    // exact and monotonic); every arithmetic step is fp64
+    using V = typename std::conditional<KIND == C3_EV_F32, float, double>::type;
+    constexpr int kPad = 16 / (int)sizeof(V);       // rows start on different LDS banks
+    __shared__ __align__(16) V sorted[kStatUnits][16 * NL + kPad];
+    const int lane = threadIdx.x & 63, l = lane & 15, q4 = lane >> 4;
+    const int slot = threadIdx.x >> 4;
+    const int64_t u = (int64_t)blockIdx.x * kStatUnits + slot;
+    // whole waves past the end leave; lanes of a wave that is partly past it
+    // decide the last unit again and write nothing
+    if ((int64_t)blockIdx.x * kStatUnits + (threadIdx.x >> 6) * 4 >= n_units) return;
+    const bool live = u < n_units;
+    V x[NL];
+    const uint32_t bad = load_times<NL>(ev + (live ? u : n_units - 1) * ustride, rstride, l, R, x);
+    const GroupVote<NL> v = stat_group<NL>(x, bad, R, kappa, sorted[slot], l, q4);
+    if (live) write_group<NL>(v, u, l, status, bitmap, majority_idx);
+}
+
+// Both votes of the timing consensus of wide groups: the fingerprint row and
+// the step-time row of a unit are loaded together by the same sixteen lanes.
+// Status and majority of a kind are written only when asked for (status not
+// null); the bitmaps always, for the confirmation.
+template <int NL, int KIND>
+__global__ void __launch_bounds__(kVoteThreads) timing_votes_wide_kernel(
+    const char* __restrict__ fp, const char* __restrict__ tp, int R, int64_t n_units, double kappa,
+    uint8_t* __restrict__ f_status, uint64_t* __restrict__ f_bitmap, int32_t* __restrict__ f_majority,
+    uint8_t* __restrict__ t_status, uint64_t* __restrict__ t_bitmap, int32_t* __restrict__ t_majority) {
+    using V = typename std::conditional<KIND == C3_EV_F32, float, double>::type;
+    constexpr int kPad = 16 / (int)sizeof(V);
+    __shared__ __align__(16) V sorted[kStatUnits][16 * NL + kPad];
+    const int lane = threadIdx.x & 63, l = lane & 15, q4 = lane >> 4;
+    const int slot = threadIdx.x >> 4;
+    const int64_t u = (int64_t)blockIdx.x * kStatUnits + slot;
+    if ((int64_t)blockIdx.x * kStatUnits + (threadIdx.x >> 6) * 4 >= n_units) return;
+    const bool live = u < n_units;
+    const int64_t first = (live ? u : n_units - 1) * R;      // of the unit's values
+    uint64_t e[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+        e[j] = reinterpret_cast<const uint64_t*>(fp)[first + (group_valid<NL>(j, l, R) ? 16 * j + l : 0)];
+    V x[NL];
+    const uint32_t bad = load_times<NL>(tp + first * (int64_t)sizeof(V), (int64_t)sizeof(V), l, R, x);
+    const GroupVote<NL> ev = exact_group<NL>(e, R, l, q4);
+    const GroupVote<NL> tv = stat_group<NL>(x, bad, R, kappa, sorted[slot], l, q4);
+    if (!live) return;
+    write_group<NL>(ev, u, l, f_status, f_bitmap, f_majority);
+    write_group<NL>(tv, u, l, t_status, t_bitmap, t_majority);
+}
+
+hipError_t launch_timing_votes_wide(const uint64_t* fp, const void* times, int time_kind, int R,
+                                    int64_t n_units, double kappa, uint8_t* f_status,
+                                    uint64_t* f_bitmap, int32_t* f_majority, uint8_t* t_status,
+                                    uint64_t* t_bitmap, int32_t* t_majority, hipStream_t stream) {
+    if (n_units <= 0) return hipSuccess;
+    const int64_t blocks = (n_units + kStatUnits - 1) / kStatUnits;
+    if (blocks > 0x7FFFFFFF || R < stat_least(2) || R > 64) return hipErrorInvalidValue;
+    const char* f = reinterpret_cast<const char*>(fp);
+    const char* t = static_cast<const char*>(times);
+    auto launch = [&](auto nl, auto kind) {
+        hipLaunchKernelGGL((timing_votes_wide_kernel<decltype(nl)::value, decltype(kind)::value>),
+                           dim3((unsigned)blocks), dim3(kVoteThreads), 0, stream, f, t, R, n_units,
+                           kappa, f_status, f_bitmap, f_majority, t_status, t_bitmap, t_majority);
+    };
+    using F32 = std::integral_constant<int, C3_EV_F32>;
+    using F64 = std::integral_constant<int, C3_EV_F64>;
+    if (R <= 32)
+        time_kind == C3_EV_F32 ? launch(std::integral_constant<int, 2>{}, F32{})
+                               : launch(std::integral_constant<int, 2>{}, F64{});
+    else
+        time_kind == C3_EV_F32 ? launch(std::integral_constant<int, 4>{}, F32{})
+                               : launch(std::integral_constant<int, 4>{}, F64{});
+    return hipGetLastError();
 }
 
 template <int NS>
