@@ -396,9 +396,14 @@ __device__ inline void merge_level(TilePartial& p) {
 // By sixteen lanes of a row, all of them active; every lane gets the result.
 __device__ inline TilePartial combine_row(const TilePartial* pp, int64_t nt, int l) {
     TilePartial p = l < nt ? pp[l] : no_partial();
-    for (int64_t x = l + 16; x < nt; x += 16) {
-        const TilePartial q = pp[x];
-        partial_merge(p, q);
+    // the rest in batches, so that a batch's loads are in flight together
+    constexpr int kBatch = 3;
+    for (int64_t x0 = l + 16; x0 < nt; x0 += 16 * kBatch) {
+        TilePartial q[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) q[i] = x0 + 16 * i < nt ? pp[x0 + 16 * i] : no_partial();
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) partial_merge(p, q[i]);
     }
     merge_level<8>(p);
     merge_level<4>(p);

@@ -122,38 +122,49 @@ __global__ void __launch_bounds__(kOptThreads) optimizer_slices_kernel(
     }
     auto at = [&](int k) { return (blk0 + k) * 256 + lane * 4; };
     auto valid_of = [&](int64_t e) { return n - e >= 4 ? 4 : n > e ? (int)(n - e) : 0; };
-    for (int k0 = wave; k0 < nblk; k0 += 4 * kOptUnroll) {
+    auto fold = [&](const OptBlock& b, const float4 (&y)[3], uint32_t beta) {
+#pragma unroll
+        for (int t = 0; t < kOptSlices; ++t) {
+            const u32x4 w = words_of(t < 4 ? b.x[t & 3] : y[t < 4 ? 0 : t - 4]);
+            nh16(w, K, beta, f[t].A, f[t].B);
+            stats_fast<C3_F32>(w, f[t].s[0], f[t].q[0], mf[t]);
+        }
+    };
+    // whole blocks without a test per lane; the slice's last one may be partial
+    const int nwhole = (int)min((int64_t)nblk, n / 256 - blk0);
+    for (int k0 = wave; k0 < nwhole; k0 += 4 * kOptUnroll) {
         OptBlock b[kOptUnroll];
 #pragma unroll
-        for (int u = 0; u < kOptUnroll; ++u) {
-            const int k = k0 + 4 * u;
-            if (k < nblk) {
-                const int64_t e = at(k);
-                const int valid = valid_of(e);
+        for (int u = 0; u < kOptUnroll; ++u)
+            if (k0 + 4 * u < nwhole) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) b[u].x[t] = load_quad(in[t] + e, valid);
+                for (int t = 0; t < 4; ++t)
+                    b[u].x[t] = *reinterpret_cast<const float4*>(in[t] + at(k0 + 4 * u));
             }
-        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kOptUnroll; ++u) {
             const int k = k0 + 4 * u;
-            if (k >= nblk) break;
-            const int64_t e = at(k);
-            const int valid = valid_of(e);
-            const uint32_t beta = block_beta((uint32_t)(blk0 + k));
+            if (k >= nwhole) break;
             float4 y[3];
-            replay_quad(c, b[u], valid, y);
-            if (valid > 0) {
+            replay_quad(c, b[u], 4, y);
 #pragma unroll
-                for (int j = 0; j < 3; ++j) store_quad(o + j * stride + e, y[j], valid);
+            for (int j = 0; j < 3; ++j) *reinterpret_cast<float4*>(o + j * stride + at(k)) = y[j];
+            fold(b[u], y, block_beta((uint32_t)(blk0 + k)));
+        }
+    }
+    if (nwhole < nblk && (nwhole & 3) == wave) {
+        const int64_t e = at(nwhole);
+        const int valid = valid_of(e);
+        if (valid > 0) {
+            OptBlock b;
+            float4 y[3];
 #pragma unroll
-                for (int t = 0; t < kOptSlices; ++t) {
-                    const u32x4 w = words_of(t < 4 ? b[u].x[t & 3] : y[t < 4 ? 0 : t - 4]);
-                    nh16(w, K, beta, f[t].A, f[t].B);
-                    stats_fast<C3_F32>(w, f[t].s[0], f[t].q[0], mf[t]);
-                }
-            }
+            for (int t = 0; t < 4; ++t) b.x[t] = load_quad(in[t] + e, valid);
+            replay_quad(c, b, valid, y);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) store_quad(o + j * stride + e, y[j], valid);
+            fold(b, y, block_beta((uint32_t)(blk0 + nwhole)));
         }
     }
     // a lane that met a NaN or Inf replays its elements once more, classifying
@@ -185,10 +196,26 @@ __global__ void __launch_bounds__(kOptThreads) optimizer_slices_kernel(
                                    f[t].q[0], f[t].mx, f[t].nan_c, f[t].inf_c);
         }
     }
+    // wave_reduce of two slices at a time: after the level of 32 the lower and
+    // upper lanes hold A and B (sum and sum of squares), after that of 16 the
+    // even and odd rows the first and second slice
 #pragma unroll
-    for (int t = 0; t < kOptSlices; ++t) {
-        const TilePartial p = wave_reduce(f[t]);
-        if (lane == 0) lds[wave][t] = p;
+    for (int t = 0; t < kOptSlices; t += 2) {
+        const int t2 = t + 1 < kOptSlices ? t + 1 : t;
+        const uint64_t ab = row_sum(fold16(fold32(f[t].A, f[t].B), fold32(f[t2].A, f[t2].B)));
+        const double sq = row_sum(fold16(fold32(f[t].s[0], f[t].q[0]), fold32(f[t2].s[0], f[t2].q[0])));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (t + i >= kOptSlices) break;
+            TilePartial p;
+            p.A = readlane_u64(ab, 16 * i);
+            p.B = readlane_u64(ab, 32 + 16 * i);
+            from_bits(readlane_u64(bits_of(sq), 16 * i), p.s);
+            from_bits(readlane_u64(bits_of(sq), 32 + 16 * i), p.q);
+            p.sc = p.qc = 0.0;
+            reduce_counts(p, f[t + i].mx, f[t + i].nan_c, f[t + i].inf_c);
+            if (lane == 0) lds[wave][t + i] = p;
+        }
     }
     __syncthreads();
     if (threadIdx.x < kOptSlices) {
