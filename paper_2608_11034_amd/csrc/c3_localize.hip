@@ -18,6 +18,7 @@
 // ascending, replica ascending) by construction.  A unit's bitmap is W =
 // ceil(R / 64) words, bit b of word w naming replica 64 w + b.
 #include <mutex>
+#include <type_traits>
 
 #include "c3_device.h"
 #include "c3_internal.h"
@@ -183,38 +184,52 @@ constexpr int64_t kWordMaxSegs = 1024;
 constexpr int64_t kWordMaxUnits = kWordUnits * kWordMaxSegs;
 static_assert(kWordUnits * C3_MAX_PEERS <= kOutMask && kWordUnits <= kUnitMask, "packed counts");
 
+// The bitmap words of the kWordPerThread units of a thread, all loads in
+// flight together (a loop over a run-time W waited for each: 11.0 us of emit
+// for 65,536 units of three words).
+template <int W>
+struct UnitBits {
+    uint64_t w[W];
+    __device__ int count() const {
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < W; ++i) n += __builtin_popcountll(w[i]);
+        return n;
+    }
+};
+template <int W>
+__device__ inline UnitBits<W> unit_bits(const uint64_t* __restrict__ bitmap, int64_t u, bool in) {
+    UnitBits<W> b;
+#pragma unroll
+    for (int i = 0; i < W; ++i) b.w[i] = in ? bitmap[u * W + i] : 0ull;
+    return b;
+}
+
 // Outliers, undecided and attributed units of one unit, packed.
-template <bool WIDE>
-__device__ inline uint64_t unit_word(uint8_t st, uint64_t bits) {
+template <int W>
+__device__ inline uint64_t unit_word(uint8_t st, const UnitBits<W>& b) {
     if (st == C3_INCONCLUSIVE) return 1ull << kOutBits;
-    const uint64_t n = WIDE ? bits : (uint64_t)__builtin_popcountll(bits);
+    const uint64_t n = (uint64_t)b.count();
     return n | ((uint64_t)(n != 0) << (kOutBits + kUnitBits));
 }
 
-// A unit's bitmap word (one-word bitmaps) or its number of set bits.
-template <bool WIDE>
-__device__ inline uint64_t unit_bits(const uint64_t* __restrict__ bitmap, int W, int64_t u) {
-    if constexpr (WIDE) return (uint64_t)unit_popcount(bitmap, W, u);
-    else return bitmap[u];
-}
-
-template <bool WIDE>
+template <int W>
 __global__ void __launch_bounds__(kLocThreads) localize_count_words_kernel(
-    const uint8_t* __restrict__ status, const uint64_t* __restrict__ bitmap, int W,
-    int64_t n_units, uint64_t* __restrict__ words) {
+    const uint8_t* __restrict__ status, const uint64_t* __restrict__ bitmap, int64_t n_units,
+    uint64_t* __restrict__ words) {
     __shared__ uint64_t lds[kLocThreads / 64];
     const int64_t base = (int64_t)blockIdx.x * kWordUnits + threadIdx.x;
     uint8_t st[kWordPerThread];
-    uint64_t b[kWordPerThread];
+    UnitBits<W> b[kWordPerThread];
 #pragma unroll
     for (int i = 0; i < kWordPerThread; ++i) {          // any order does for a count: adjacent units
         const int64_t u = base + (int64_t)i * kLocThreads;
         st[i] = u < n_units ? status[u] : (uint8_t)C3_AGREE;
-        b[i] = u < n_units ? unit_bits<WIDE>(bitmap, W, u) : 0ull;
+        b[i] = unit_bits<W>(bitmap, u, u < n_units);
     }
     uint64_t w = 0;
 #pragma unroll
-    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<WIDE>(st[i], b[i]);
+    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<W>(st[i], b[i]);
     w = row_sum(fold16(w, w));
     w = fold32(w, w);
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = w;
@@ -225,22 +240,24 @@ __global__ void __launch_bounds__(kLocThreads) localize_count_words_kernel(
     }
 }
 
-template <bool WIDE>
+template <int W>
 __global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
     const uint8_t* __restrict__ status, const uint64_t* __restrict__ bitmap,
     const int32_t* __restrict__ majority_idx, const c3_chunk_record_t* __restrict__ records, int R,
-    int W, int64_t n_units, const uint64_t* __restrict__ words, c3_outlier_t* __restrict__ outliers,
+    int64_t n_units, const uint64_t* __restrict__ words, c3_outlier_t* __restrict__ outliers,
     int64_t out_cap, int64_t* __restrict__ undecided, int64_t und_cap, int64_t* __restrict__ counts) {
     __shared__ int64_t lds[kLocThreads / 64];
     __shared__ uint64_t before[kLocThreads / 64][3];
     const int64_t u0 = (int64_t)blockIdx.x * kWordUnits + (int64_t)threadIdx.x * kWordPerThread;
     uint8_t st[kWordPerThread];
-    uint64_t b[kWordPerThread];
+    int32_t mj[kWordPerThread];
+    UnitBits<W> b[kWordPerThread];
 #pragma unroll
     for (int i = 0; i < kWordPerThread; ++i) {
         const int64_t u = u0 + i;
         st[i] = u < n_units ? status[u] : (uint8_t)C3_AGREE;
-        b[i] = u < n_units ? unit_bits<WIDE>(bitmap, W, u) : 0ull;
+        mj[i] = u < n_units ? majority_idx[u] : -1;
+        b[i] = unit_bits<W>(bitmap, u, u < n_units);
     }
     // the segments before this one; a sum of words could overflow a field
     uint64_t so = 0, su = 0, sa = 0;
@@ -263,7 +280,7 @@ __global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
     }
     uint64_t w = 0;
 #pragma unroll
-    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<WIDE>(st[i], b[i]);
+    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<W>(st[i], b[i]);
     int64_t total;
     const uint64_t excl = (uint64_t)block_inclusive_scan<kLocThreads>((int64_t)w, lds, total) - w;
     int64_t po = 0, pu = 0, pa = 0;                     // block_inclusive_scan ended with a barrier
@@ -288,35 +305,31 @@ __global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
             ++pu;
             continue;
         }
-        if (b[i] == 0ull) continue;
-        const int32_t mj = majority_idx[u];
-        for (int j = 0; j < (WIDE ? W : 1); ++j) {
-            uint64_t bits = WIDE ? bitmap[u * W + j] : b[i];
-            while (bits) {
+#pragma unroll
+        for (int j = 0; j < W; ++j)
+            for (uint64_t bits = b[i].w[j]; bits != 0; bits &= bits - 1) {
                 const int r = 64 * j + __builtin_ctzll(bits);
-                bits &= bits - 1;
-                if (po < out_cap) write_outlier(&outliers[po], u, r, mj, records, R, n_units);
+                if (po < out_cap) write_outlier(&outliers[po], u, r, mj[i], records, R, n_units);
                 ++po;
             }
-        }
     }
 }
 
-template <bool WIDE>
+template <int W>
 static hipError_t launch_words(const uint8_t* status, const uint64_t* bitmap,
                                const int32_t* majority_idx, const c3_chunk_record_t* records, int R,
-                               int W, int64_t n_units, c3_outlier_t* outliers, int64_t out_cap,
+                               int64_t n_units, c3_outlier_t* outliers, int64_t out_cap,
                                int64_t* undecided, int64_t und_cap, int64_t* counts, void* ws,
                                hipStream_t stream) {
     const unsigned n_seg = (unsigned)((n_units + kWordUnits - 1) / kWordUnits);
     uint64_t* words = static_cast<uint64_t*>(ws);
-    hipLaunchKernelGGL(localize_count_words_kernel<WIDE>, dim3(n_seg), dim3(kLocThreads), 0, stream,
-                       status, bitmap, W, n_units, words);
+    hipLaunchKernelGGL(localize_count_words_kernel<W>, dim3(n_seg), dim3(kLocThreads), 0, stream,
+                       status, bitmap, n_units, words);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(localize_emit_words_kernel<WIDE>, dim3(n_seg), dim3(kLocThreads), 0, stream,
-                       status, bitmap, majority_idx, records, R, W, n_units, words, outliers,
-                       out_cap, undecided, und_cap, counts);
+    hipLaunchKernelGGL(localize_emit_words_kernel<W>, dim3(n_seg), dim3(kLocThreads), 0, stream,
+                       status, bitmap, majority_idx, records, R, n_units, words, outliers, out_cap,
+                       undecided, und_cap, counts);
     return hipGetLastError();
 }
 
@@ -343,11 +356,19 @@ hipError_t launch_localize(const uint8_t* status, const uint64_t* bitmap,
                                outliers, out_cap, undecided, und_cap, counts);
         return hipGetLastError();
     }
-    if (n_units <= kWordMaxUnits)
-        return W == 1 ? launch_words<false>(status, bitmap, majority_idx, records, R, W, n_units,
-                                            outliers, out_cap, undecided, und_cap, counts, ws, stream)
-                      : launch_words<true>(status, bitmap, majority_idx, records, R, W, n_units,
-                                           outliers, out_cap, undecided, und_cap, counts, ws, stream);
+    if (n_units <= kWordMaxUnits) {
+        auto launch = [&](auto w) {
+            return launch_words<decltype(w)::value>(status, bitmap, majority_idx, records, R, n_units,
+                                                    outliers, out_cap, undecided, und_cap, counts, ws,
+                                                    stream);
+        };
+        switch (W) {
+            case 1: return launch(std::integral_constant<int, 1>{});
+            case 2: return launch(std::integral_constant<int, 2>{});
+            case 3: return launch(std::integral_constant<int, 3>{});
+            default: return launch(std::integral_constant<int, 4>{});
+        }
+    }
     const int64_t n_seg = (n_units + kSegUnits - 1) / kSegUnits;
     if (n_seg > 0x7FFFFFFF) return hipErrorInvalidValue;
     SegCount* seg = static_cast<SegCount*>(ws);
