@@ -338,7 +338,7 @@ hipError_t launch_confirm(const uint64_t* fp_bitmap, const uint64_t* time_bitmap
     const int64_t Wt = (int64_t)window < T ? (int64_t)window : T;
     if (R > 16 && Wt <= 64 && T > 0) {
         const int64_t n_seg = (T + 63) / 64;
-        const int sw = n_seg >= 4 ? 4 : n_seg >= 2 ? 2 : 1;
+        const int sw = n_seg >= 8 ? 8 : n_seg >= 4 ? 4 : n_seg >= 2 ? 2 : 1;
         const int64_t gw = kWaveConfWaves / sw;
         const int64_t blocks = (G + gw - 1) / gw;
         if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
