@@ -11,6 +11,8 @@ hipcc compiles every source of csrc/ for gfx950 only:
 import glob
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -51,11 +53,22 @@ def build_oob(verbose: bool = False) -> str:
 
 
 def build(verbose: bool = False, extra=None) -> str:
-    cmd = [HIPCC] + FLAGS + (extra or []) + ["-I", os.path.join(HERE, "..", "include")] + \
-        sources() + ["-o", LIB + ".tmp"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    flags = FLAGS + (extra or [])
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+
+    # one compiler per source, side by side, then one link
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in sources()]
+        jobs = [[HIPCC] + [f for f in flags if f != "-shared"] +
+                ["-I", os.path.join(HERE, "..", "include"), "-c", s, "-o", o]
+                for s, o in zip(sources(), objs)]
+        with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+            list(pool.map(run, jobs))
+        run([HIPCC] + flags + objs + ["-o", LIB + ".tmp"])
     os.replace(LIB + ".tmp", LIB)
     build_oob(verbose)
     return LIB

@@ -513,7 +513,8 @@ __device__ __forceinline__ void pass_load_full(const char* __restrict__ base, in
 }
 
 // PU: per-unit results written, bit 0 those of the fingerprints, bit 1
-// those of the step times.
+// those of the step times; bit 2: their bitmaps go past the caches
+// (kPassStreamBytes).
 template <int NMAX, int KIND, bool SHORT, int PU>
 __global__ void __launch_bounds__(PassShape<NMAX>::threads) timing_pass_kernel(
     const char* __restrict__ fp, const char* __restrict__ tp, int64_t G, int64_t T, double kappa,
@@ -558,6 +559,10 @@ __global__ void __launch_bounds__(PassShape<NMAX>::threads) timing_pass_kernel(
         }
     };
     vu32x4 gf[CPF], gt[CPT];
+    auto store_bits = [](uint64_t* p, uint64_t v) {
+        if constexpr ((PU & 4) != 0) __builtin_nontemporal_store(v, p);
+        else *p = v;
+    };
     auto do_step = [&](int64_t st, int64_t nx) -> int64_t {
         const int64_t t0 = st * kPassIters;
         vu32x4 vf[CPF], vt[CPT];
@@ -599,12 +604,12 @@ __global__ void __launch_bounds__(PassShape<NMAX>::threads) timing_pass_kernel(
             const int64_t u = valid ? t * G + g0 + gi : (t0 + kPassIters <= T ? t * G + g0 : g0);
             if constexpr ((PU & 1) != 0) {
                 fo.status[u] = vfp.status;
-                fo.bitmap[u] = vfp.bitmap;
+                store_bits(fo.bitmap + u, vfp.bitmap);
                 fo.majority[u] = vfp.majority;
             }
             if constexpr ((PU & 2) != 0) {
                 to.status[u] = vtm.status;
-                to.bitmap[u] = vtm.bitmap;
+                store_bits(to.bitmap + u, vtm.bitmap);
                 to.majority[u] = vtm.majority;
             }
         }
@@ -709,13 +714,25 @@ static hipError_t launch_votes(const uint64_t* fp, const char* tp, int time_kind
     return launch_votes<NMAX, C3_EV_F64>(fp, tp, R, G, n_units, kappa, fo, to, stream);
 }
 
+// A pass that moves more than the 256 MB memory-side cache holds writes its
+// bitmaps past the caches, where the 16 groups of a workgroup make whole lines
+// of them.  32,768 ranks x 1,024 iterations (512 MB), calls on three sets of
+// buffers in turn: 108 us through the caches, 90.1 with the bitmaps past them,
+// 99.4 with the majority's 64-byte pieces too, 114 with all; on one set of
+// buffers, whose results stay cached, 89.9 and 90.9.
+constexpr int64_t kPassStreamBytes = 256ll << 20;
+
 template <int NMAX, int KIND>
 static hipError_t launch_pass(const char* fp, const char* tp, int64_t G, int64_t T, double kappa,
                               int Wt, c3_rank_verdict_t* verdicts, const VoteOut& fo,
                               const VoteOut& to, size_t lds, hipStream_t stream) {
     const dim3 grid((unsigned)((G + kPassGroups - 1) / kPassGroups));
     const dim3 block(PassShape<NMAX>::threads);
-    const int pu = (fo.status != nullptr ? 1 : 0) | (to.status != nullptr ? 2 : 0);
+    int pu = (fo.status != nullptr ? 1 : 0) | (to.status != nullptr ? 2 : 0);
+    constexpr int rsize = NMAX * (KIND == C3_EV_F64 ? 16 : 12);
+    if (pu != 0 && Wt <= 32 && G % kPassGroups == 0 && T * G * (rsize + 26) > kPassStreamBytes &&
+        (((uintptr_t)fo.bitmap | (uintptr_t)to.bitmap) & 127) == 0)
+        pu |= 4;
 #define C3_PASS(S, P)                                                                     \
     hipLaunchKernelGGL((timing_pass_kernel<NMAX, KIND, S, P>), grid, block, lds, stream, fp, \
                        tp, G, T, kappa, Wt, verdicts, fo, to)
@@ -724,7 +741,10 @@ static hipError_t launch_pass(const char* fp, const char* tp, int64_t G, int64_t
             case 0: C3_PASS(true, 0); break;
             case 1: C3_PASS(true, 1); break;
             case 2: C3_PASS(true, 2); break;
-            default: C3_PASS(true, 3); break;
+            case 3: C3_PASS(true, 3); break;
+            case 5: C3_PASS(true, 5); break;
+            case 6: C3_PASS(true, 6); break;
+            default: C3_PASS(true, 7); break;
         }
     } else {
         switch (pu) {

@@ -18,3 +18,26 @@ def test_short_pass(R, G, T, W, f64, per_unit):
     _case("timing short", R, G, T, W, f64, per_unit)
     fp, tau = _inputs(R, G, T, seed=R * 1000 + G * 7 + T, f64=f64)
     _check(fp, tau, W, per_unit=per_unit)
+
+
+@pytest.mark.parametrize("R,G,T,f64", [(4, 4096, 900, False), (8, 4096, 600, False), (16, 4096, 200, True),
+                                       (8, 4112, 600, False)])
+def test_streamed_bitmaps(R, G, T, f64):
+    """Passes of over 256 MB, whose bitmaps go past the caches, against the
+    separate votes and confirmation."""
+    import torch
+    from paper_2608_11034_amd import c3
+    _case("timing streamed", R, G, T, f64)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(R + T)
+    fp = torch.randint(-2**63, 2**63 - 1, (T, G, 1), generator=gen, device="cuda").expand(T, G, R).contiguous()
+    fp[T // 3:, 5, R - 1] ^= 77
+    tau = torch.randn((T, G, R), generator=gen, device="cuda").mul_(0.02).exp_()
+    tau[:, G - 1, 1] *= 1.5
+    if f64:
+        tau = tau.double()
+    ver, fu, tu = c3.timing_consensus(fp, tau)
+    for got, ev, mode in ((fu, fp, c3.EXACT), (tu, tau, c3.STATISTICAL)):
+        for a, b in zip(got, c3.consensus(ev, mode)):
+            assert torch.equal(a, b)
+    assert torch.equal(ver, c3.confirm(fu[1].view(T, G), tu[1].view(T, G), R, 16))
