@@ -41,7 +41,7 @@ METRIC = "replica GB/s fingerprinted+localized; % of MI355X HBM peak"
 # sources that define the streaming signature kernel: counter-based traffic
 # figures are reported only while these are unchanged
 SIG_SOURCES = ["paper_2608_11034_amd/csrc/c3_signature.hip", "paper_2608_11034_amd/csrc/c3_device.h",
-               "paper_2608_11034_amd/csrc/c3_sigplan.h"]
+               "paper_2608_11034_amd/csrc/c3_fold.h", "paper_2608_11034_amd/csrc/c3_sigplan.h"]
 # the same for the single-pass timing kernel
 TIMING_SOURCES = ["paper_2608_11034_amd/csrc/c3_timing.hip", "paper_2608_11034_amd/csrc/c3_vote_row.h",
                   "paper_2608_11034_amd/csrc/c3_device.h"]

@@ -19,7 +19,8 @@
  *     The library allocates no device memory.  Its state between calls is
  *     a 4 MiB ring of pinned host memory per device (allocated on first
  *     use, kept until the process ends) through which c3_signature and
- *     c3_check stage their plans, so that staging never makes the host wait
+ *     c3_check stage plans that do not fit among a kernel's arguments
+ *     (about 3.5 KB), so that staging never makes the host wait
  *     for the GPU, and the fixed scratch array of c3_localize_noalloc.
  *   - Host arrays passed in (pointer tables, tensor metadata) are consumed
  *     before the call returns; the caller may free them immediately.
@@ -264,11 +265,10 @@ size_t c3_check_workspace_size(const c3_tensor_meta_t *metas, int T, int R, uint
  *               streaming kernels; C3_OPT_PLAN_STAGED skips staging when a
  *               previous c3_signature_ex or c3_check call staged the same
  *               plan into this workspace.
- * One workgroup combines the tile partials, votes the chunks and writes the
- * lists after the streaming pass for plans of up to 256 chunks, 1,024
- * records and 64 replicas.  Otherwise, for R <= 32, one kernel combines and
- * votes and (for up to 8,192 chunks) a second writes the lists; larger
- * groups run the separate steps.  Errors as the three calls.
+ * One workgroup votes the chunks and writes the lists after the streaming pass
+ * for plans of up to 256 chunks, 1,024 records and 64 replicas.  Otherwise, for
+ * R <= 32, one kernel votes and (for up to 8,192 chunks) writes the lists;
+ * larger groups run the separate steps.  Errors as the three calls.
  */
 int c3_check(const void *const *ptrs, const c3_tensor_meta_t *metas, int T, int R,
              uint64_t chunk_bytes, c3_chunk_record_t *records, uint8_t *status, uint64_t *bitmap,

@@ -20,13 +20,14 @@
 // inputs from a second read.
 //
 // The tile: smaller ones give more workgroups, whose waves replay fewer blocks
-// one after the other, and more partials to combine.  us per check by tile:
+// one after the other, and more partials to combine.  us per check by tile,
+// before whole blocks lost their per-lane tests:
 //   8 replicas x 65,536 elements   2 KiB 24.0, 4 KiB 18.2, 8 KiB 16.9, 16 KiB 18.9, 64 KiB 37.4
 //   2 replicas x 16,384            2 KiB 11.5, 4 KiB 11.8, 16 KiB 15.4
 //   8 x 262,144                    8 KiB 32.9, 16 KiB 27.4, 64 KiB 38.9
 //   16 x 524,288                   16 KiB 67.1, 64 KiB 58.0
-// against 20.9, 17.2, 36.8 and 91.0 for the three launches; by default about
-// 32 tiles (c3_api.cpp).
+// against 20.9, 17.2, 36.8 and 91.0 for three launches.  By default about 32
+// tiles (c3_api.cpp), which now take 14.7, 10.1, 26.7 and 56.4.
 #include "c3_adamw_step.h"
 #include "c3_device.h"
 #include "c3_fold.h"

@@ -93,7 +93,7 @@ __device__ inline int64_t replica_of(int64_t i, int64_t gtiles) {
 
 // Where a kernel finds the plan: staged into the workspace, or, when it is
 // small, among the kernel's own arguments, which saves the launch that stages
-// it and the first trip to memory of every look-up (launch_plan_arg).
+// it and the first trip to memory of every look-up (place_plan).
 struct StagedPlan {
     const SigPlan* p;
     static constexpr bool kChunkTable = true;

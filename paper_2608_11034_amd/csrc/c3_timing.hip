@@ -10,7 +10,8 @@
 // masks live in the LDS of a single kernel whose workgroups each own a set
 // of groups over all iterations (the shapes it takes, with or without
 // per-unit results), or else in the workspace (three launches: clear,
-// votes, confirmation).
+// votes, confirmation; c3_vote.hip has the votes of groups above 16, which
+// hand their bitmaps to the confirmation).
 #include "c3_device.h"
 #include "c3_internal.h"
 #include "c3_vote_row.h"
