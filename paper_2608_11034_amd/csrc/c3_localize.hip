@@ -171,22 +171,31 @@ __global__ void __launch_bounds__(kSingleThreads) localize_single_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Two launches for middle sizes.  A segment is kWordUnits units, four per
-// thread, so that 65,536 units occupy 64 workgroups (the 2,048-unit segments
-// of the three launches 32); its counts are one word, and every emitting
-// workgroup sums the at most kWordMaxSegs words before its own, 8 KiB from
-// the L2, in place of the scan launch.  262,144 units, us per call, three
-// launches / two: 25.8 / 14.8 at R = 17, 34.5 / 15.9 at 192, 40.4 / 19.3 at 256.
+// Two launches for middle sizes.  A segment is kWordUnits units, so that
+// 65,536 units occupy 64 workgroups (the 2,048-unit segments of the three
+// launches 32); its counts are one word, and every emitting workgroup sums the
+// at most kWordMaxSegs words before its own, 8 KiB from the L2, in place of
+// the scan launch.  262,144 units, us per call, three launches / two: 25.8 /
+// 10.5 at R = 17, 34.5 / 11.0 at 192, 40.4 / 12.0 at 256.
+// A thread takes four units of one bitmap word, or two of several, whose loads
+// and list entries are twice as long a chain.  Four / two / one units a
+// thread: 65,536 units 10.5 / 10.4 / 13.0 at R = 64, 12.2 / 10.8 / 13.9 at 192
+// and 14.3 / 11.2 / 15.5 at 256; 1,000,000 units 15.7 / 16.4 / 42 at R = 64,
+// 25.2 / 23.2 / 52 at 192 and 34.1 / 30.1 / 61 at 256 (workgroups of 1,024
+// threads are dispatched slowly).
 // ---------------------------------------------------------------------------
-constexpr int kWordPerThread = 4;
-constexpr int64_t kWordUnits = (int64_t)kLocThreads * kWordPerThread;
+constexpr int64_t kWordUnits = 1024;
+template <int W>
+constexpr int kWordPerThread = W == 1 ? 4 : 2;
+template <int W>
+constexpr int kWordThreads = (int)kWordUnits / kWordPerThread<W>;
 constexpr int64_t kWordMaxSegs = 1024;
 constexpr int64_t kWordMaxUnits = kWordUnits * kWordMaxSegs;
 static_assert(kWordUnits * C3_MAX_PEERS <= kOutMask && kWordUnits <= kUnitMask, "packed counts");
 
-// The bitmap words of the kWordPerThread units of a thread, all loads in
-// flight together (a loop over a run-time W waited for each: 11.0 us of emit
-// for 65,536 units of three words).
+// The bitmap words of the units of a thread, all loads in flight together (a
+// loop over a run-time W waited for each: 11.0 against 8.3 us of emit for
+// 65,536 units of three words, four a thread).
 template <int W>
 struct UnitBits {
     uint64_t w[W];
@@ -214,46 +223,46 @@ __device__ inline uint64_t unit_word(uint8_t st, const UnitBits<W>& b) {
 }
 
 template <int W>
-__global__ void __launch_bounds__(kLocThreads) localize_count_words_kernel(
+__global__ void __launch_bounds__(kWordThreads<W>) localize_count_words_kernel(
     const uint8_t* __restrict__ status, const uint64_t* __restrict__ bitmap, int64_t n_units,
     uint64_t* __restrict__ words) {
-    __shared__ uint64_t lds[kLocThreads / 64];
+    __shared__ uint64_t lds[kWordThreads<W> / 64];
     const int64_t base = (int64_t)blockIdx.x * kWordUnits + threadIdx.x;
-    uint8_t st[kWordPerThread];
-    UnitBits<W> b[kWordPerThread];
+    uint8_t st[kWordPerThread<W>];
+    UnitBits<W> b[kWordPerThread<W>];
 #pragma unroll
-    for (int i = 0; i < kWordPerThread; ++i) {          // any order does for a count: adjacent units
-        const int64_t u = base + (int64_t)i * kLocThreads;
+    for (int i = 0; i < kWordPerThread<W>; ++i) {  // any order does for a count: adjacent units
+        const int64_t u = base + (int64_t)i * kWordThreads<W>;
         st[i] = u < n_units ? status[u] : (uint8_t)C3_AGREE;
         b[i] = unit_bits<W>(bitmap, u, u < n_units);
     }
     uint64_t w = 0;
 #pragma unroll
-    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<W>(st[i], b[i]);
+    for (int i = 0; i < kWordPerThread<W>; ++i) w += unit_word<W>(st[i], b[i]);
     w = row_sum(fold16(w, w));
     w = fold32(w, w);
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = w;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < kLocThreads / 64; ++i) w += lds[i];
+        for (int i = 1; i < kWordThreads<W> / 64; ++i) w += lds[i];
         words[blockIdx.x] = w;
     }
 }
 
 template <int W>
-__global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
+__global__ void __launch_bounds__(kWordThreads<W>) localize_emit_words_kernel(
     const uint8_t* __restrict__ status, const uint64_t* __restrict__ bitmap,
     const int32_t* __restrict__ majority_idx, const c3_chunk_record_t* __restrict__ records, int R,
     int64_t n_units, const uint64_t* __restrict__ words, c3_outlier_t* __restrict__ outliers,
     int64_t out_cap, int64_t* __restrict__ undecided, int64_t und_cap, int64_t* __restrict__ counts) {
-    __shared__ int64_t lds[kLocThreads / 64];
-    __shared__ uint64_t before[kLocThreads / 64][3];
-    const int64_t u0 = (int64_t)blockIdx.x * kWordUnits + (int64_t)threadIdx.x * kWordPerThread;
-    uint8_t st[kWordPerThread];
-    int32_t mj[kWordPerThread];
-    UnitBits<W> b[kWordPerThread];
+    __shared__ int64_t lds[kWordThreads<W> / 64];
+    __shared__ uint64_t before[kWordThreads<W> / 64][3];
+    const int64_t u0 = (int64_t)blockIdx.x * kWordUnits + (int64_t)threadIdx.x * kWordPerThread<W>;
+    uint8_t st[kWordPerThread<W>];
+    int32_t mj[kWordPerThread<W>];
+    UnitBits<W> b[kWordPerThread<W>];
 #pragma unroll
-    for (int i = 0; i < kWordPerThread; ++i) {
+    for (int i = 0; i < kWordPerThread<W>; ++i) {
         const int64_t u = u0 + i;
         st[i] = u < n_units ? status[u] : (uint8_t)C3_AGREE;
         mj[i] = u < n_units ? majority_idx[u] : -1;
@@ -261,7 +270,7 @@ __global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
     }
     // the segments before this one; a sum of words could overflow a field
     uint64_t so = 0, su = 0, sa = 0;
-    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kLocThreads) {
+    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kWordThreads<W>) {
         const uint64_t w = words[i];
         so += w & kOutMask;
         su += (w >> kOutBits) & kUnitMask;
@@ -280,12 +289,12 @@ __global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
     }
     uint64_t w = 0;
 #pragma unroll
-    for (int i = 0; i < kWordPerThread; ++i) w += unit_word<W>(st[i], b[i]);
+    for (int i = 0; i < kWordPerThread<W>; ++i) w += unit_word<W>(st[i], b[i]);
     int64_t total;
-    const uint64_t excl = (uint64_t)block_inclusive_scan<kLocThreads>((int64_t)w, lds, total) - w;
+    const uint64_t excl = (uint64_t)block_inclusive_scan<kWordThreads<W>>((int64_t)w, lds, total) - w;
     int64_t po = 0, pu = 0, pa = 0;                     // block_inclusive_scan ended with a barrier
 #pragma unroll
-    for (int i = 0; i < kLocThreads / 64; ++i) {
+    for (int i = 0; i < kWordThreads<W> / 64; ++i) {
         po += (int64_t)before[i][0];
         pu += (int64_t)before[i][1];
         pa += (int64_t)before[i][2];
@@ -298,7 +307,7 @@ __global__ void __launch_bounds__(kLocThreads) localize_emit_words_kernel(
     po += (int64_t)(excl & kOutMask);
     pu += (int64_t)((excl >> kOutBits) & kUnitMask);
 #pragma unroll
-    for (int i = 0; i < kWordPerThread; ++i) {
+    for (int i = 0; i < kWordPerThread<W>; ++i) {
         const int64_t u = u0 + i;
         if (st[i] == C3_INCONCLUSIVE) {
             if (pu < und_cap) undecided[pu] = u;
@@ -323,11 +332,11 @@ static hipError_t launch_words(const uint8_t* status, const uint64_t* bitmap,
                                hipStream_t stream) {
     const unsigned n_seg = (unsigned)((n_units + kWordUnits - 1) / kWordUnits);
     uint64_t* words = static_cast<uint64_t*>(ws);
-    hipLaunchKernelGGL(localize_count_words_kernel<W>, dim3(n_seg), dim3(kLocThreads), 0, stream,
+    hipLaunchKernelGGL(localize_count_words_kernel<W>, dim3(n_seg), dim3(kWordThreads<W>), 0, stream,
                        status, bitmap, n_units, words);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(localize_emit_words_kernel<W>, dim3(n_seg), dim3(kLocThreads), 0, stream,
+    hipLaunchKernelGGL(localize_emit_words_kernel<W>, dim3(n_seg), dim3(kWordThreads<W>), 0, stream,
                        status, bitmap, majority_idx, records, R, n_units, words, outliers, out_cap,
                        undecided, und_cap, counts);
     return hipGetLastError();

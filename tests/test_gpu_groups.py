@@ -60,7 +60,7 @@ def test_statistical_fallbacks(R, dt):
 
 # one workgroup up to 4,096 units, two launches up to 1,048,576, three above;
 # one and several bitmap words, lists cut short
-@pytest.mark.parametrize("R", [3, 130])
+@pytest.mark.parametrize("R", [3, 66, 130, 256])
 @pytest.mark.parametrize("U", [4096, 4097, 5120, 5121, 1048576, 1048577])
 def test_localize_sizes(U, R):
     print("CASE localize", U, R, flush=True)
