@@ -202,9 +202,12 @@ __global__ void __launch_bounds__(kConfThreads) confirm_combine_kernel(
 // Groups of 17 to 64 replicas with W <= 64, in one launch.  A wave takes a
 // group's segments of 64 iterations: lane i loads the words of iteration t0 +
 // i, and lane r collects replica r's bits over the iterations into 64-bit
-// masks.  Outlier words are sparse, so the transposition walks the non-zero
-// words only, broadcasting each by readlane, instead of every bit of every
-// word.  A window's count rises only where a set bit enters, so the largest
+// masks.  The words of most groups are nearly all zero, so few of them are
+// walked, broadcast by readlane; those of a group with a slow or diverged rank
+// are set at every iteration, and such a group's walk was the kernel's time
+// (128 groups of 32 over 512 iterations, one with a slow and a diverged rank:
+// 9.8 us), so they are transposed in six levels of lane exchanges (4.8 us;
+// without outliers 3.5).  A window's count rises only where a set bit enters, so the largest
 // count and the first window over the threshold are those of windows ending
 // at a set bit or starting the segment: a lane evaluates those, and only
 // where they could change what it already has.  `sw` waves share a group's
@@ -214,6 +217,35 @@ __global__ void __launch_bounds__(kConfThreads) confirm_combine_kernel(
 // walked 191 words and 64 windows each: 38.8 us, and 5.9 us to combine, for
 // 128 groups of 32 over 512 iterations.
 constexpr int kWaveConfWaves = 8;
+
+// Most non-zero words of 64 that are walked one by one: about what a transpose
+// costs.
+constexpr int kGatherWords = 6;
+
+// The 64 x 64 bit matrix whose row i lane i holds, transposed: blocks of 32,
+// 16, ... 1 change places between the lanes that differ in that bit.
+template <int S>
+__device__ __forceinline__ uint32_t transpose_level(uint32_t x, uint32_t mask, int lane) {
+    const uint32_t p = row_xor_u32<S>(x);
+    const uint32_t keep = (lane & S) != 0 ? ~mask : mask;
+    const uint32_t t = (lane & S) != 0 ? p >> S : p << S;
+    return (x & keep) | (t & ~keep);
+}
+__device__ __forceinline__ uint64_t transpose64(uint64_t w, int lane) {
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)w, (uint32_t)(w >> 32), false, false);
+    uint32_t x[2] = {h[0], h[1]};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        // [0], [1]: the word of the even and of the odd row of the pair
+        const auto q = __builtin_amdgcn_permlane16_swap(x[i], x[i], false, false);
+        x[i] = (lane & 16) == 0 ? (q[0] & 0xFFFFu) | (q[1] << 16) : (q[0] >> 16) | (q[1] & 0xFFFF0000u);
+        x[i] = transpose_level<8>(x[i], 0x00FF00FFu, lane);
+        x[i] = transpose_level<4>(x[i], 0x0F0F0F0Fu, lane);
+        x[i] = transpose_level<2>(x[i], 0x33333333u, lane);
+        x[i] = transpose_level<1>(x[i], 0x55555555u, lane);
+    }
+    return ((uint64_t)x[1] << 32) | x[0];
+}
 
 struct RankAcc {
     uint32_t flags, dc, sc, mw;
@@ -237,10 +269,12 @@ __global__ void __launch_bounds__(64 * kWaveConfWaves) confirm_wave_kernel(
         const int64_t n_seg = (T + 63) / 64;
         // Iteration t's word, 0 past the end.  A lane's bits past T stay 0.
         auto word = [&](const uint64_t* bm, int64_t t) { return t < T ? bm[t * G + g] : 0ull; };
-        // lane r's bits over the 64 words the lanes hold
+        // lane r's bits over the 64 words the lanes hold: a walk of the
+        // non-zero words, a few in a sound group, or a transpose
         auto gather = [&](uint64_t w) {
-            uint64_t m = 0;
-            for (uint64_t set = ballot64(w != 0ull); set != 0ull; set &= set - 1ull) {
+            uint64_t m = 0, set = ballot64(w != 0ull);
+            if (__builtin_popcountll(set) > kGatherWords) return transpose64(w, lane);
+            for (; set != 0ull; set &= set - 1ull) {
                 const int i = __builtin_ctzll(set);
                 m |= ((readlane_u64(w, i) >> lane) & 1ull) << i;
             }
