@@ -66,16 +66,59 @@ __device__ inline float absmax3(float a, float b, float c) {
     return r;
 }
 
+// fp64 sums of a lane's elements in one quarter of a tile.
+//
+// The squares of bf16 and fp16 elements have at most 22 bits and no chain of a
+// tile rounds them.  Those of fp32 elements have 48, their lowest bits are
+// alike (an odd number's square is 1 mod 8), and a plain chain rounds most of
+// them down: 2-norm of the relative error of a chunk of N(0, 1) elements 2.5e-16
+// over 64 elements a lane (64 KiB tiles), 8.8e-16 over 256 (256 KiB).  So the
+// even and the odd elements have a chain each, and after every kFoldBlocks
+// blocks of the quarter, 8 elements a chain, their sum goes into a compensated
+// pair: 5e-17 to 1e-16 in chunks of 16 KiB to 4 MiB, where rounding the exact
+// sum once is 4e-17 to 6e-17 (folds after 16 blocks: 2e-16).  That is 7 more
+// fp64 instructions to 32: 3 GB of fp32 in 4 MiB chunks 428.5 / 430.4 us, 403 MB
+// in 32 KiB chunks, a wave each, 75.9 / 78.0.  The sums themselves add 24-bit
+// values and round next to nothing.
+constexpr int kFoldBlocks = 4;
+
 template <int DT>
-__device__ inline void stats_fast(const u32x4 v, double& s, double& q, float& mf) {
+struct LaneSums {
+    double s = 0.0, q = 0.0;
+    __device__ __forceinline__ void add(double d, int) {
+        s += d;
+        q = __fma_rn(d, d, q);
+    }
+    __device__ __forceinline__ void fold() {}
+    __device__ __forceinline__ double squares() { return q; }
+};
+template <>
+struct LaneSums<C3_F32> {
+    double s = 0.0, q[2] = {0.0, 0.0}, hi = 0.0, lo = 0.0;
+    __device__ __forceinline__ void add(double d, int i) {
+        s += d;
+        q[i & 1] = __fma_rn(d, d, q[i & 1]);
+    }
+    __device__ __forceinline__ void fold() {
+        double t, e;
+        two_sum(hi, q[0] + q[1], t, e);
+        hi = t;
+        lo += e;
+        q[0] = q[1] = 0.0;
+    }
+    // (with nothing in the chains the last fold changes nothing)
+    __device__ __forceinline__ double squares() {
+        fold();
+        return hi + lo;
+    }
+};
+
+template <int DT>
+__device__ inline void stats_fast(const u32x4 v, LaneSums<DT>& a, float& mf) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
     if constexpr (DT == C3_F32) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            double d = (double)__uint_as_float(w[i]);
-            s += d;
-            q = __fma_rn(d, d, q);
-        }
+        for (int i = 0; i < 4; ++i) a.add((double)__uint_as_float(w[i]), i);
         mf = absmax3(mf, absmax3(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2])),
                      __uint_as_float(w[3]));
     } else if constexpr (DT == C3_BF16 || DT == C3_F16) {
@@ -91,11 +134,7 @@ __device__ inline void stats_fast(const u32x4 v, double& s, double& q, float& mf
             }
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const double d = (double)x[i];
-            s += d;
-            q = __fma_rn(d, d, q);
-        }
+        for (int i = 0; i < 8; ++i) a.add((double)x[i], i);
         mf = absmax3(absmax3(x[0], x[1], x[2]), absmax3(x[3], x[4], x[5]), absmax3(x[6], x[7], mf));
     }
 }
@@ -113,8 +152,8 @@ __device__ inline uint32_t magnitude_bits(float mf) {
 // so none is ever -0), and there are no branches: one lane redoes its column
 // of the tile while the wave waits.
 template <int DT>
-__device__ inline void stats_slow(const u32x4 v, double& s, double& q, uint32_t& mx,
-                                  uint32_t& nan_c, uint32_t& inf_c) {
+__device__ inline void stats_slow(const u32x4 v, LaneSums<DT>& a, uint32_t& mx, uint32_t& nan_c,
+                                  uint32_t& inf_c) {
     constexpr uint32_t inf_bits = DT == C3_F32 ? 0x7F800000u : DT == C3_BF16 ? 0x7F80u : 0x7C00u;
     constexpr int N = DT == C3_F32 ? 4 : 8;
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -130,8 +169,7 @@ __device__ inline void stats_slow(const u32x4 v, double& s, double& q, uint32_t&
         mx = max(mx, fin ? mag : 0u);
         const double d = DT == C3_F32 ? (double)__uint_as_float(x)
                          : DT == C3_BF16 ? (double)__uint_as_float(x << 16) : f16_to_f64(x);
-        s += d;
-        q = __fma_rn(d, d, q);
+        a.add(d, i);
     }
 }
 
@@ -148,9 +186,9 @@ __device__ inline u32x4 load_partial(const uint8_t* p, uint32_t rem) {
 }
 
 // A lane's share of a tile.  The sums are kept in quarters: quarter q holds
-// blocks q, q + 4, ... of the tile, in ascending order, whether one wave
-// folds all four (NQ = 4) or four waves one each (NQ = 1), so the sums have
-// the same bits either way.
+// blocks q, q + 4, ... of the tile, in ascending order and folded after the
+// same ones, whether one wave folds all four (NQ = 4) or four waves one each
+// (NQ = 1), so the sums have the same bits either way.
 template <int NQ>
 struct LaneFold {
     uint64_t A, B;
@@ -169,12 +207,12 @@ template <int DT, int U, int NW>
 __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, uint32_t blk0,
                                              const LaneKeys& K, int wave, int lane) {
     constexpr int NQ = 4 / NW;
-    static_assert((NW == 1 || NW == 4) && U % 4 == 0, "quarters of a tile");
+    static_assert((NW == 1 || NW == 4) && U % (NQ * kFoldBlocks) == 0 && kRedoLoads % kFoldBlocks == 0,
+                  "quarters of a tile");
     LaneFold<NQ> f;
     f.A = f.B = 0;
     f.mx = f.nan_c = f.inf_c = 0u;
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) f.s[i] = f.q[i] = 0.0;
+    LaneSums<DT> a[NQ];
     float mf = 0.0f;
     const uint32_t off = (uint32_t)lane * 16u;
     const int nfull = (int)(len >> 10);
@@ -182,7 +220,17 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
     const __amdgpu_buffer_rsrc_t rs = tile_resource(tile, len);
     int k = wave;
     // k - wave is a multiple of NW U in both loops, so load u of a batch
-    // belongs to quarter u % NQ
+    // belongs to quarter u % NQ, as its block u / NQ of the batch
+    auto take = [&](const u32x4 v, int u) {
+        stats_fast<DT>(v, a[u % NQ], mf);
+        // blocks and folds one after another: side by side their chains take
+        // 128 registers and scratch where 97 do
+        if constexpr (DT == C3_F32 && NW == 4) __builtin_amdgcn_sched_barrier(0);
+        if (u / NQ % kFoldBlocks == kFoldBlocks - 1) {
+            a[u % NQ].fold();
+            if constexpr (DT == C3_F32 && NW == 4) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     for (; k + NW * (U - 1) < nfull; k += NW * U) {
         u32x4 v[U];
 #pragma unroll
@@ -193,7 +241,7 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
         for (int u = 0; u < U; ++u) {
             const uint32_t beta = block_beta(blk0 + (uint32_t)(k + NW * u));
             nh16(v[u], K, beta, f.A, f.B);
-            stats_fast<DT>(v[u], f.s[u % NQ], f.q[u % NQ], mf);
+            take(v[u], u);
         }
     }
     if (k < nfull) {
@@ -208,7 +256,7 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
         for (int u = 0; u < U; ++u) {
             if (k + NW * u < nfull) {
                 nh16(v[u], K, block_beta(blk0 + (uint32_t)(k + NW * u)), f.A, f.B);
-                stats_fast<DT>(v[u], f.s[u % NQ], f.q[u % NQ], mf);
+                take(v[u], u);
             }
         }
     }
@@ -220,7 +268,12 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
         nh16(v, K, (blk0 + (uint32_t)nfull) * kBlockMul, f.A, f.B);
 #pragma unroll
         for (int i = 0; i < NQ; ++i)
-            if (nfull % NQ == i) stats_fast<DT>(v, f.s[i], f.q[i], mf);
+            if (nfull % NQ == i) stats_fast<DT>(v, a[i], mf);
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        f.s[i] = a[i].s;
+        f.q[i] = a[i].squares();
     }
     if constexpr (DT != C3_RAW) {
         bool finite = true;
@@ -231,7 +284,7 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
             // rare: this lane saw a NaN or Inf; redo its statistics classifying
             f.mx = 0u;
             for (int i = 0; i < NQ; ++i) {
-                double si = 0.0, qi = 0.0;
+                LaneSums<DT> ai;
                 for (int kk = wave + i; kk < nfull; kk += 4 * kRedoLoads) {
                     u32x4 v[kRedoLoads];
 #pragma unroll
@@ -241,19 +294,22 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int u = 0; u < kRedoLoads; ++u)
-                        if (kk + 4 * u < nfull)
-                            stats_slow<DT>(v[u], si, qi, f.mx, f.nan_c, f.inf_c);
+                        if (kk + 4 * u < nfull) {
+                            stats_slow<DT>(v[u], ai, f.mx, f.nan_c, f.inf_c);
+                            if (u % kFoldBlocks == kFoldBlocks - 1) ai.fold();
+                        }
                 }
                 if (has_tail && nfull % NQ == i) {
                     const uint8_t* seg = tile + ((size_t)nfull << 10) + off;
                     u32x4 v = (off + 16u <= tail) ? load16(reinterpret_cast<const u32x4*>(seg))
                                                   : load_partial(seg, tail - off);
-                    stats_slow<DT>(v, si, qi, f.mx, f.nan_c, f.inf_c);
+                    stats_slow<DT>(v, ai, f.mx, f.nan_c, f.inf_c);
                 }
+                const double qi = ai.squares();
 #pragma unroll
                 for (int j = 0; j < NQ; ++j)
                     if (j == i) {
-                        f.s[j] = si;
+                        f.s[j] = ai.s;
                         f.q[j] = qi;
                     }
             }
@@ -265,8 +321,8 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
 }
 
 // Lanes meet in a fixed six-level butterfly (lane distances 32 to 1) of plain
-// fp64 adds (error at most 6 ulp of the sum of magnitudes); compensation
-// starts where quarters meet.
+// fp64 adds (error at most 6 ulp of the sum of magnitudes); quarters and tiles
+// meet with compensation.
 __device__ inline void reduce_counts(TilePartial& p, uint32_t mx, uint32_t nan_c, uint32_t inf_c) {
     p.pad = 0u;
     p.maxbits = wave_max_u32(mx);

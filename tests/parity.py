@@ -2,7 +2,7 @@
 
 Tolerance for the fp64 sums (GPU vs oracle), derived from the arithmetic:
 the GPU sums each lane's elements in plain fp64 (at most a few hundred per
-lane), meets lanes in a six-level butterfly and combines waves, tiles and
+lane and tile; squares of fp32 elements in shorter chains), meets lanes in a six-level butterfly and combines waves, tiles and
 chunks with TwoSum compensation, so its error is bounded by roughly
 (n_lane + 8) u sum|x| <= 1e-13 sqrt(n sumsq) for the chunk sizes here; the
 oracle (Neumaier) is within a couple of ulp of the exact sum.  The check is

@@ -2,6 +2,9 @@
 side by side in one launch, and the two kernels that fold a tile (a workgroup,
 or one wave for small tiles in large numbers), against the CPU oracle and
 against each other bit for bit."""
+import math
+from fractions import Fraction
+
 import numpy as np
 import pytest
 import torch
@@ -167,3 +170,41 @@ def test_plan_argument_and_staged(R, T, n):
         plan.run(rec, sig_ws, plan_staged=True)
         torch.cuda.synchronize()
         assert torch.equal(rec, first)
+
+
+# sums of squares of fp32 chunks against the exact sums: the exact result
+# rounded once is off by 4e-17 to 6e-17 (2-norm, relative), and the chains
+# between two folds may add as much again
+@pytest.mark.parametrize("chunk_kib", [16, 48, 100, 500, 640, 1000, 1024])
+def test_squares_of_fp32(chunk_kib):
+    print("CASE squares", chunk_kib, flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(chunk_kib)
+    chunks = 48
+    x = torch.randn(chunks * chunk_kib * KIB // 4, generator=gen, device=DEV)
+    rec = c3.records_numpy(_sign([[x]], chunk_kib * KIB))[0]
+    rows = x.cpu().numpy().astype(np.float64).reshape(chunks, -1)
+    err = [float((Fraction(float(q)) - e) / e)
+           for q, e in zip(rec["sumsq"], (Fraction(math.fsum((r * r).tolist())) for r in rows))]
+    assert math.sqrt(np.mean(np.square(err))) < 1.2e-16
+
+
+# the optimizer check's records are those of the signature over its seven
+# slices with the same tile, sums included: tiles below, at and above those
+# whose waves fold on the way, a slice that ends inside a block, a NaN
+@pytest.mark.parametrize("tile_kib", [1, 16, 32, 64, 256])
+@pytest.mark.parametrize("n", [65536, 65536 - 4097])
+def test_optimizer_records_are_signatures(tile_kib, n):
+    print("CASE optimizer tile", tile_kib, n, flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n)
+    state = [[torch.randn(65536 + n, generator=gen, device=DEV) * s for _ in range(2)]
+             for s in (0.02, 1e-3, 1e-4, 1e-6)]
+    state[3] = [v.abs_() for v in state[3]]
+    state[1][1][65536 + 5000] = float("nan")
+    chk = c3.OptimizerBoundaryCheck(*state, slice_elems=65536, tile_bytes=tile_kib * KIB)
+    rec = chk.run(1, c3.adamw_hparams(3e-4, (0.9, 0.95), 1e-8, 0.1, 1000))[0]
+    slices = [[t[r][65536:] for t in state] + [chk.updated[r, j, :n].clone() for j in range(3)]
+              for r in range(2)]
+    torch.cuda.synchronize()
+    assert torch.equal(rec.view(-1, 64), _sign(slices, 262144, tile_kib * KIB).view(-1, 64))
