@@ -63,6 +63,8 @@ int64_t tensor_nbytes(const c3_tensor_meta_t& m) {
     return (int64_t)n;
 }
 
+constexpr uint64_t kTileMax = 1ull << 24;
+
 // Default tile: the chunk in as few equal tiles of at most kDefaultTileMax
 // as it takes, rounded up to whole KiB (the chunk's last tile is shorter
 // where they do not divide it).  A power of two dividing the chunk, the rule
@@ -88,7 +90,7 @@ int make_plan(const c3_tensor_meta_t* metas, int T, int R, uint64_t chunk_bytes,
     if (tile_bytes == 0)
         tile_bytes = default_tile(chunk_bytes);
     else if (tile_bytes < 1024 || (tile_bytes & (tile_bytes - 1)) != 0 ||
-             chunk_bytes % tile_bytes != 0 || tile_bytes > (1ull << 24))
+             chunk_bytes % tile_bytes != 0 || tile_bytes > kTileMax)
         return C3_E_INVAL;
     const uint64_t tpc = (chunk_bytes + tile_bytes - 1) / tile_bytes;
     p.tile_base.assign(T + 1, 0);
@@ -616,7 +618,8 @@ constexpr uint64_t kOptTiles = 32, kOptTileMax = 64 * 1024;
 
 // The signature tile of a valid state: the caller's, or the smallest power of
 // two up to kOptTileMax that cuts the slice into at most kOptTiles, lowered
-// until it divides the slice; 0 if the state is invalid.
+// until it divides the slice; 0 if the state is invalid (a tile left above
+// kTileMax among that).
 static uint64_t optimizer_tile(const c3_optimizer_state_t* st) {
     if (st == nullptr || st->R < 2 || st->R > C3_MAX_REPLICAS || st->numel < 1 ||
         st->slice_elems < 256 || st->slice_elems % 256 != 0 || st->slice_elems > (1ll << 30))
@@ -627,7 +630,7 @@ static uint64_t optimizer_tile(const c3_optimizer_state_t* st) {
         for (t = 1024; t * kOptTiles < slice && t < kOptTileMax;) t *= 2;
     if (t < 1024 || (t & (t - 1)) != 0) return 0;
     while (slice % t != 0) t /= 2;  // the slice is a multiple of 1024
-    return t;
+    return t <= kTileMax ? t : 0;
 }
 
 size_t c3_optimizer_check_workspace_size(const c3_optimizer_state_t* st) {

@@ -294,3 +294,25 @@ def test_public_headers_compile_alone(header, compiler, tmp_path):
                                    "-o", str(tmp_path / "use")],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+def test_optimizer_check_tile_limits():
+    """The tile that is left after the lowering is at most 16 MiB, as a
+    signature's; a larger one is an argument error, not a tile."""
+    L = c3.lib()
+    ptrs = (ctypes.c_void_p * 2)(256, 512)
+    p = ctypes.cast(ptrs, ctypes.c_void_p)
+
+    def state(S, tile):
+        return c3.OptimizerState(p, p, p, p, 2, 0, 1 << 24, S, tile)
+
+    def ws_size(S, tile):
+        return L.c3_optimizer_check_workspace_size(ctypes.byref(state(S, tile)))
+    assert ws_size(1 << 22, 1 << 24) > 0 and ws_size(1 << 23, 1 << 24) > 0
+    assert ws_size(1024, 1 << 40) > 0                       # lowered to the slice
+    assert ws_size(1 << 23, 1 << 25) == 0 and ws_size(1 << 24, 1 << 30) == 0
+    out = c3.OptimizerCheckOut(*[4096 * (i + 1) for i in range(8)])
+    hp = c3.adamw_hparams(step=1)
+    assert L.c3_optimizer_check(ctypes.byref(state(1 << 23, 1 << 25)), 0, ctypes.byref(hp),
+                                ctypes.byref(out), ctypes.c_void_p(1 << 20), 1 << 40,
+                                ctypes.c_void_p(0)) == -1
