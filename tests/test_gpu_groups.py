@@ -119,3 +119,45 @@ def test_confirm_groups(R, T, G, W):
                   ("divergent_count", "div_count"), ("slow_count", "slow_count"),
                   ("max_window_slow", "max_window"), ("first_straggler_window", "first_window")):
         assert np.array_equal(v[k], ref[rk]), k
+
+
+# rows that are not dense: padded, replica-major, every other unit
+@pytest.mark.parametrize("R", [17, 32, 33, 64, 130, 192, 256])
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+def test_statistical_strides(R, dt):
+    print("CASE strides", R, dt, flush=True)
+    rng = np.random.default_rng(R)
+    U, es = 37, np.dtype(dt).itemsize
+    t = np.exp(0.05 * rng.standard_normal((U, R))).astype(dt)
+    t[rng.random((U, R)) < 0.02] = np.nan
+    ost, obm, omj = oracle.vote_statistical(t, oracle.KAPPA_DEFAULT, replica_axis=1)
+
+    def check(ev, replica_stride, unit_stride):
+        st, bm, mj = c3.consensus(torch.from_numpy(ev).to(DEV), c3.STATISTICAL, R=R, n_units=U,
+                                  replica_stride=replica_stride, unit_stride=unit_stride)
+        assert np.array_equal(st.cpu().numpy(), ost) and np.array_equal(mj.cpu().numpy(), omj)
+        words = (R + 63) // 64
+        assert np.array_equal(bm.cpu().numpy().view(np.uint64).reshape(-1, words),
+                              obm.reshape(-1, words))
+    check(np.ascontiguousarray(t.T), U * es, es)                            # replica-major
+    wide = np.full((2 * U, R + 3), np.nan, dt)
+    wide[::2, :R] = t
+    check(wide, es, 2 * (R + 3) * es)                                       # padded, every other row
+    apart = np.full((U, 2 * R), np.inf, dt)
+    apart[:, ::2] = t
+    check(apart, 2 * es, 2 * R * es)                                        # every other value
+
+
+# the sum of the middle two values and the differences overflow
+@pytest.mark.parametrize("R", [18, 33, 34, 256])
+def test_statistical_overflow(R):
+    print("CASE overflow", R, flush=True)
+    rng = np.random.default_rng(R)
+    big = np.finfo(np.float64).max
+    rows = [np.full(R, big), np.full(R, -big), np.where(np.arange(R) % 2, big, -big),
+            np.where(np.arange(R) < R // 3, 1.0, big), np.where(np.arange(R) < R // 3, 1.0, -big),
+            big * rng.random(R), -big * rng.random(R), big * (2 * rng.random(R) - 1),
+            big * (0.9 + 0.1 * rng.random(R)), -big * (0.9 + 0.1 * rng.random(R))]
+    t = np.stack(rows + [rng.permutation(r) for r in rows])
+    for kappa in (oracle.KAPPA_DEFAULT, 0.01, 1e300):
+        _stat(t, kappa)
