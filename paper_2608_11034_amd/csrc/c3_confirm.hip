@@ -370,12 +370,12 @@ hipError_t launch_confirm(const uint64_t* fp_bitmap, const uint64_t* time_bitmap
     const int64_t n_ranks = (int64_t)R * G;
     if (n_ranks == 0) return hipSuccess;
     const int64_t Wt = (int64_t)window < T ? (int64_t)window : T;
-    if (R > 16 && Wt <= 64 && T > 0) {
-        const int64_t n_seg = (T + 63) / 64;
-        const int sw = n_seg >= 8 ? 8 : n_seg >= 4 ? 4 : n_seg >= 2 ? 2 : 1;
-        const int64_t gw = kWaveConfWaves / sw;
-        const int64_t blocks = (G + gw - 1) / gw;
-        if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    const int64_t wave_segs = (T + 63) / 64;
+    const int sw = wave_segs >= 8 ? 8 : wave_segs >= 4 ? 4 : wave_segs >= 2 ? 2 : 1;
+    const int64_t gw = kWaveConfWaves / sw;
+    const int64_t blocks = (G + gw - 1) / gw;
+    // (more groups than a grid of fewer than 2^32 threads has waves for: two launches)
+    if (R > 16 && Wt <= 64 && T > 0 && blocks * 64 * kWaveConfWaves < ((int64_t)1 << 32)) {
         hipLaunchKernelGGL(confirm_wave_kernel, dim3((unsigned)blocks), dim3(64 * kWaveConfWaves), 0,
                            stream, fp_bitmap, time_bitmap, R, G, T, (int)Wt, sw, verdicts);
         return hipGetLastError();

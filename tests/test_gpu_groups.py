@@ -161,3 +161,18 @@ def test_statistical_overflow(R):
     t = np.stack(rows + [rng.permutation(r) for r in rows])
     for kappa in (oracle.KAPPA_DEFAULT, 0.01, 1e300):
         _stat(t, kappa)
+
+
+# more groups than one launch has waves for
+def test_confirm_past_the_wave_launch():
+    print("CASE confirm past the wave launch", flush=True)
+    R, G = 17, (1 << 26) + 5
+    fp = torch.zeros((1, G), dtype=torch.int64, device=DEV)
+    tm = torch.zeros((1, G), dtype=torch.int64, device=DEV)
+    fp[0, G - 1], tm[0, 9] = 1 << 16, 1 << 3
+    v = c3.confirm(fp, tm, R, 4).view(torch.int32).view(R, G, 6)
+    torch.cuda.synchronize()
+    assert int(v[16, G - 1, 1]) == 0 and int(v[16, G - 1, 2]) == 1 and int(v[3, 9, 3]) == 1
+    assert int(v[:, :, 2].sum()) == 1 and int(v[:, :, 3].sum()) == 1
+    del v, fp, tm
+    torch.cuda.empty_cache()
