@@ -507,8 +507,8 @@ size_t c3_timing_consensus_workspace_size(int R, int64_t G, int64_t T, int windo
  *   - otherwise, for R <= 16 and W <= 64: a clearing kernel, one kernel
  *     voting both kinds that ORs each outlier bit into per-rank masks in the
  *     workspace, and a confirmation kernel over those masks;
- *   - otherwise, for R > 16: one kernel voting both kinds, with the bitmaps in
- *     the workspace when not requested, and c3_confirm's;
+ *   - otherwise, for R > 16 and T * G below 2^28: one kernel voting both kinds,
+ *     with the bitmaps in the workspace when not requested, and c3_confirm's;
  *   - otherwise the three separate steps (c3_consensus twice, c3_confirm),
  *     with the per-unit results kept in the workspace when not requested.
  * Errors: C3_E_INVAL (sizes, kinds, kappa, outputs half given),

@@ -766,7 +766,7 @@ int c3_timing_consensus(const uint64_t* fingerprints, const void* times, int tim
         tm = t_majority;
     }
     hipError_t e;
-    if (R > 16) {
+    if (R > 16 && (int64_t)n <= c3::kGroupMaxUnits) {
         e = c3::launch_timing_votes_wide(fingerprints, times, time_kind, R, (int64_t)n, kappa,
                                          fp_status, fb, fp_majority, t_status, tb, t_majority, s);
     } else {

@@ -118,8 +118,12 @@ hipError_t launch_timing_consensus(const uint64_t* fp, const void* times, int ti
                                    uint8_t* t_status, uint64_t* t_bitmap, int32_t* t_majority,
                                    c3_rank_verdict_t* verdicts, void* ws, hipStream_t stream);
 
+// Units that a launch of sixteen lanes each can decide: a grid has fewer than
+// 2^32 threads, in workgroups of 256.
+constexpr int64_t kGroupMaxUnits = ((int64_t)1 << 28) - 16;
+
 // Exact vote on fingerprints [n_units][R] and statistical vote on times of the
-// same layout, 17 <= R <= 64, in one launch.  Bitmaps always, status and
+// same layout, 17 <= R <= 64, n_units <= kGroupMaxUnits, in one launch.  Bitmaps always, status and
 // majority of a kind unless its status is null.
 hipError_t launch_timing_votes_wide(const uint64_t* fp, const void* times, int time_kind, int R,
                                     int64_t n_units, double kappa, uint8_t* f_status,

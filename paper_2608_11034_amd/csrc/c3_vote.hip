@@ -620,7 +620,7 @@ hipError_t launch_timing_votes_wide(const uint64_t* fp, const void* times, int t
                                     uint64_t* t_bitmap, int32_t* t_majority, hipStream_t stream) {
     if (n_units <= 0) return hipSuccess;
     const int64_t blocks = (n_units + kStatUnits - 1) / kStatUnits;
-    if (blocks > 0x7FFFFFFF || R < stat_least(2) || R > 64) return hipErrorInvalidValue;
+    if (n_units > kGroupMaxUnits || R < stat_least(2) || R > 64) return hipErrorInvalidValue;
     const char* f = reinterpret_cast<const char*>(fp);
     const char* t = static_cast<const char*>(times);
     auto launch = [&](auto nl, auto kind) {
@@ -695,8 +695,10 @@ hipError_t launch_consensus(const void* evidence, int kind, int64_t rstride, int
     // fp64 times of 17 to 32 replicas: sixteen lanes a unit, 36 us per 262,144
     // units at R = 17, 24 and 32, against 46, 38 and 43 for a thread per unit
     // (256 VGPRs); in fp32 a thread per unit is the faster one, 20-24 against
-    // 30 us.
-    if (mode == C3_STATISTICAL && kind == C3_EV_F64 && R >= stat_least(2) && R <= 32)
+    // 30 us.  More units than sixteen lanes each can be launched for stay with a
+    // thread per unit.
+    if (mode == C3_STATISTICAL && kind == C3_EV_F64 && R >= stat_least(2) && R <= 32 &&
+        n_units <= kGroupMaxUnits)
         return launch_stat<2>(static_cast<const char*>(evidence), kind, rstride, ustride, R, n_units,
                               kappa, status, bitmap, majority_idx, stream);
     if (R <= 32) {

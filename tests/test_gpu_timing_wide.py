@@ -88,3 +88,29 @@ def test_wide_timing(R, f64, G, T, W, kinds):
                   ("divergent_count", "div_count"), ("slow_count", "slow_count"),
                   ("max_window_slow", "max_window"), ("first_straggler_window", "first_window")):
         assert np.array_equal(v[k], ver_ref[rk]), k
+
+
+# more units than sixteen lanes each can be launched for (2^28): a thread per
+# unit.  One row read for every unit, and timing rows equal but for a few.
+def test_units_past_the_group_launch():
+    _case("units past the group launch")
+    n, R = (1 << 28) + 3, 17
+    row = torch.ones(R, dtype=torch.float64, device=DEV)
+    row[5] = 9.0
+    st, bm, mj = c3.consensus(row, c3.STATISTICAL, R=R, n_units=n, replica_stride=8, unit_stride=0)
+    torch.cuda.synchronize()
+    assert int(st.min()) == int(st.max()) == 1 and int(bm.min()) == int(bm.max()) == 1 << 5
+    assert int(mj.min()) == int(mj.max()) == 9      # the ninth of the sixteen ones
+    del st, bm, mj
+    G, T = 16, (1 << 24) + 1
+    fp = torch.full((T, G, R), 77, dtype=torch.int64, device=DEV)
+    tau = torch.ones((T, G, R), dtype=torch.float32, device=DEV)
+    fp[T - 1, 3, 4] = 1
+    tau[5:25, 7, 16] = 2.0
+    ver, _, _ = c3.timing_consensus(fp, tau, window=16, per_unit=False)
+    v = c3.verdicts_numpy(ver).reshape(R, G)
+    assert v["first_divergent_iter"][4, 3] == T - 1 and v["divergent_count"].sum() == 1
+    assert v["slow_count"][16, 7] == v["slow_count"].sum() == 20
+    assert v["first_straggler_window"][16, 7] == 0 and v["max_window_slow"][16, 7] == 16
+    del fp, tau, ver
+    torch.cuda.empty_cache()
