@@ -344,8 +344,9 @@ typedef struct {
     int64_t slice_elems;             /* S: multiple of 256 (65536 in Sec. 9) */
     uint64_t tile_bytes;             /* signature tile: a power of two >= 1024,
                                         lowered until it divides 4 S, at most
-                                        16 MiB then; 0 = one of
-                                        at most 64 KiB, for 32 tiles or more */
+                                        16 MiB then; 0 = whole KiB, at most 64,
+                                        by S and R, whether or not they divide
+                                        the slice */
 } c3_optimizer_state_t;
 
 /* Device outputs of c3_optimizer_check, all caller-owned.  Unit u of the

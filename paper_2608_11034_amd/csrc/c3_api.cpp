@@ -612,13 +612,21 @@ int c3_localize(const uint8_t* status, const uint64_t* bitmap, const int32_t* ma
 // replica, exact vote and localization, enqueued by one host call as two
 // launches.
 // ---------------------------------------------------------------------------
-// Unless the caller says otherwise a slice is cut into this many tiles, or
-// into tiles of this size if that is more (c3_optimizer.hip has the times).
-constexpr uint64_t kOptTiles = 32, kOptTileMax = 64 * 1024;
+// Unless the caller says otherwise a slice is cut into 32 tiles, or into as many
+// as give few replicas 256 workgroups if those still have 4 KiB, of whole KiB
+// and at most 64 KiB each, the last one shorter (c3_optimizer.hip has the
+// times).
+constexpr uint64_t kOptTiles = 32, kOptWorkgroups = 256, kOptTileMin = 4096, kOptTileMax = 64 * 1024;
 
-// The signature tile of a valid state: the caller's, or the smallest power of
-// two up to kOptTileMax that cuts the slice into at most kOptTiles, lowered
-// until it divides the slice; 0 if the state is invalid (a tile left above
+static uint64_t optimizer_default_tile(uint64_t slice, int R) {
+    const uint64_t n = std::max<uint64_t>(kOptTiles, kOptWorkgroups / (uint64_t)R);
+    const uint64_t all = align_up((slice + kOptTiles - 1) / kOptTiles, 1024);
+    const uint64_t few = align_up((slice + n - 1) / n, 1024);
+    return std::min(std::max(few, std::min(all, kOptTileMin)), kOptTileMax);
+}
+
+// The signature tile of a valid state: the caller's, lowered until it divides
+// the slice, or the rule's; 0 if the state is invalid (a tile left above
 // kTileMax among that).
 static uint64_t optimizer_tile(const c3_optimizer_state_t* st) {
     if (st == nullptr || st->R < 2 || st->R > C3_MAX_REPLICAS || st->numel < 1 ||
@@ -626,8 +634,7 @@ static uint64_t optimizer_tile(const c3_optimizer_state_t* st) {
         return 0;
     const uint64_t slice = (uint64_t)st->slice_elems * 4;
     uint64_t t = st->tile_bytes;
-    if (t == 0)
-        for (t = 1024; t * kOptTiles < slice && t < kOptTileMax;) t *= 2;
+    if (t == 0) return optimizer_default_tile(slice, st->R);
     if (t < 1024 || (t & (t - 1)) != 0) return 0;
     while (slice % t != 0) t /= 2;  // the slice is a multiple of 1024
     return t <= kTileMax ? t : 0;

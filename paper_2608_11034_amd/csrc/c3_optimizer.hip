@@ -20,14 +20,20 @@
 // inputs from a second read.
 //
 // The tile: smaller ones give more workgroups, whose waves replay fewer blocks
-// one after the other, and more partials to combine.  us per check by tile,
-// before whole blocks lost their per-lane tests:
-//   8 replicas x 65,536 elements   2 KiB 24.0, 4 KiB 18.2, 8 KiB 16.9, 16 KiB 18.9, 64 KiB 37.4
-//   2 replicas x 16,384            2 KiB 11.5, 4 KiB 11.8, 16 KiB 15.4
-//   8 x 262,144                    8 KiB 32.9, 16 KiB 27.4, 64 KiB 38.9
-//   16 x 524,288                   16 KiB 67.1, 64 KiB 58.0
-// against 20.9, 17.2, 36.8 and 91.0 for three launches.  By default about 32
-// tiles (c3_api.cpp), which now take 14.7, 10.1, 26.7 and 56.4.
+// one after the other, and more partials to combine.  us per check by tile:
+//                  2      4      8     16     32     64 KiB
+//   2 x  64 KiB  10.6   10.5   11.2
+//   2 x 256 KiB  12.4   11.4   12.0   13.2   16.8
+//   2 x   1 MiB  21.1   15.2   13.8   14.3   17.8   25.3
+//   4 x 512 KiB  21.0   15.5   13.1   14.2   17.9   25.5
+//   8 x 256 KiB  21.3   15.1   13.7   14.6   18.4
+//   8 x   1 MiB  59.3   36.7   27.7   22.5   23.2   29.0
+//   8 x   4 MiB                76.3   58.3   54.1   49.8
+// so by default about 256 workgroups, or 32 a replica for eight and more
+// (c3_api.cpp).  Tiles need not divide the slice: powers of two that do, of 1 KiB
+// for a slice of an odd number of KiB, take 33.9 us for 8 x 257 KiB and 203 for
+// 8 x 2,047 KiB, whole KiB 13.9 and 34.8.  (Three launches took 20.7 us for 8 x
+// 256 KiB and 91 for 16 x 2 MiB, where these two take 13.9 and 50.9.)
 #include "c3_adamw_step.h"
 #include "c3_device.h"
 #include "c3_fold.h"

@@ -316,3 +316,18 @@ def test_optimizer_check_tile_limits():
     assert L.c3_optimizer_check(ctypes.byref(state(1 << 23, 1 << 25)), 0, ctypes.byref(hp),
                                 ctypes.byref(out), ctypes.c_void_p(1 << 20), 1 << 40,
                                 ctypes.c_void_p(0)) == -1
+
+
+def test_optimizer_check_default_tiles():
+    """Tiles of whole KiB whatever the slice divides by: 32 of them, or 256 / R
+    where each has 4 KiB, or tiles of 64 KiB; the workspace is R replicas x 7
+    slices x 64 bytes a tile."""
+    L = c3.lib()
+    ptrs = (ctypes.c_void_p * 16)(*[256] * 16)
+    p = ctypes.cast(ptrs, ctypes.c_void_p)
+    for R, kib, tiles in ((2, 1, 1), (2, 5, 5), (2, 33, 17), (2, 129, 33), (2, 257, 65), (2, 1000, 125),
+                          (2, 8200, 129), (3, 512, 74), (8, 1, 1), (8, 32, 32), (8, 33, 17), (8, 64, 32),
+                          (8, 257, 29), (8, 500, 32), (16, 2047, 32), (16, 2048, 32), (16, 4097, 65)):
+        st = c3.OptimizerState(p, p, p, p, R, 0, 1 << 24, kib * 256, 0)
+        need = -(-R * 7 * 64 * tiles // 256) * 256
+        assert L.c3_optimizer_check_workspace_size(ctypes.byref(st)) == need, (R, kib)

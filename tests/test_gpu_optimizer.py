@@ -214,3 +214,15 @@ def test_boundary_check_full_workload_fault_and_clean_slices():
         assert found_inputs == planted
     del chk, w
     torch.cuda.empty_cache()
+
+
+# slices of an odd number of blocks, in whole-KiB tiles that do not divide
+# them; the last slice ends inside a tile and inside a block
+@pytest.mark.parametrize("S", [256 * 33, 256 * 257, 256 * 500, 256 * 2047])
+def test_boundary_check_odd_slices(S):
+    R, h = 2, HPS[1]
+    host, dev = _state(R, S + 3 * S // 4 + 101, seed=S)
+    chk = c3.OptimizerBoundaryCheck(*dev, slice_elems=S)
+    for k in (0, 1):
+        _case("boundary odd", S, k)
+        _compare_check(_gpu_check(chk, k, _hp(h)), adamw.boundary_check(host, k, h, S))
