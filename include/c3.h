@@ -19,8 +19,8 @@
  *     The library allocates no device memory.  Its state between calls is
  *     a 4 MiB ring of pinned host memory per device (allocated on first
  *     use, kept until the process ends) through which c3_signature and
- *     c3_check stage plans that do not fit among a kernel's arguments
- *     (about 3.5 KB), so that staging never makes the host wait
+ *     c3_check stage plans that do not go along as a kernel's argument
+ *     (over 3.5 KB, or for many tiles), so that staging never makes the host wait
  *     for the GPU, and the fixed scratch array of c3_localize_noalloc.
  *   - Host arrays passed in (pointer tables, tensor metadata) are consumed
  *     before the call returns; the caller may free them immediately.

@@ -377,16 +377,21 @@ int adamw_prepare(const float* const* param, const float* const* grad,
 // The plan as the kernels get it: with the kernels' arguments when it fits
 // (without the chunk-to-tensor table, which they then search for), else staged
 // into the workspace on the stream unless the caller says that it is there.
-// us per call, staged / as an argument: 3 x 1M fp32 15.1 / 12.1, the 3 GB fp32
-// shard (256 KiB tiles) 430.9 / 427.9.  Over many smaller tiles the look-ups,
-// which go through the scalar cache then, cost more than the launch saved:
-// 12,352 tiles of 128 KiB 244.7 / 246.2.
-constexpr int64_t kArgPlanMaxTiles = 8192;
+// An argument saves a launch and costs at every look-up, which goes through the
+// scalar cache then, the more the larger the plan.  us per check, staged / as
+// an argument, bf16, 8 replicas of 3 tensors and 2 of 1 (fp32 alike):
+//   tiles                2,048        4,096        8,192        12,288        35,000        65,000
+//   256 KiB  8 x 3   95.8 / 92.8     170 / 168    320 / 321    466 / 466   1,298 / 1,309 2,479 / 2,509
+//            2 x 1   97.7 / 93.7     174 / 170    328 / 324    485 / 481   1,353 / 1,349 2,486 / 2,487
+//   128 KiB  8 x 3   54.3 / 51.3    91.0 / 89.6   165 / 165    245 / 250     675 / 701   1,246 / 1,293
+//            2 x 1   53.0 / 49.6    92.4 / 89.6   169 / 170    247 / 250     675 / 691   1,239 / 1,274
+// The 3 GB fp32 shard, 11,444 tiles of 256 KiB, 430.9 / 427.9.
+constexpr int64_t kArgPlanMaxTiles = 8192, kArgPlanMaxLargeTiles = 16384;   // under 256 KiB, others
 
 hipError_t place_plan(void* ws, const Plan& p, const std::vector<unsigned char>& buf, bool staged,
                       hipStream_t s, c3::PlanSource& src) {
-    if (p.h.off_chunk_tensor <= c3::kArgPlanBytes &&
-        (p.h.tile_bytes >= c3::kDefaultTileMax || p.h.tiles_per_replica * p.h.R <= kArgPlanMaxTiles)) {
+    const int64_t most = p.h.tile_bytes >= c3::kDefaultTileMax ? kArgPlanMaxLargeTiles : kArgPlanMaxTiles;
+    if (p.h.off_chunk_tensor <= c3::kArgPlanBytes && p.h.tiles_per_replica * p.h.R <= most) {
         src = {ws, buf.data(), (size_t)p.h.off_chunk_tensor};
         return hipSuccess;
     }
