@@ -138,6 +138,7 @@ int make_plan(const c3_tensor_meta_t* metas, int T, int R, uint64_t chunk_bytes,
     h.tile_bytes = tile_bytes;
     h.tiles_per_chunk = (uint32_t)tpc;
     h.direct = h.tiles_per_chunk == 1 ? 1u : 0u;
+    h.folds = c3::folded_tiles(chunk_bytes, tile_bytes) ? 1u : 0u;
     uint64_t off = align_up(sizeof(SigPlan), 256);
     h.off_ptrs = off;
     off = align_up(off + 8ull * (uint64_t)R * (uint64_t)T, 256);

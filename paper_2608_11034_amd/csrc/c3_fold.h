@@ -72,17 +72,25 @@ __device__ inline float absmax3(float a, float b, float c) {
 // tile rounds them.  Those of fp32 elements have 48, their lowest bits are
 // alike (an odd number's square is 1 mod 8), and a plain chain rounds most of
 // them down: 2-norm of the relative error of a chunk of N(0, 1) elements 2.5e-16
-// over 64 elements a lane (64 KiB tiles), 8.8e-16 over 256 (256 KiB).  So the
-// even and the odd elements have a chain each, and after every kFoldBlocks
-// blocks of the quarter, 8 elements a chain, their sum goes into a compensated
-// pair: 5e-17 to 1e-16 in chunks of 16 KiB to 4 MiB, where rounding the exact
-// sum once is 4e-17 to 6e-17 (folds after 16 blocks: 2e-16).  That is 7 more
-// fp64 instructions to 32: 3 GB of fp32 in 4 MiB chunks 428.5 / 430.4 us, 403 MB
-// in 32 KiB chunks, a wave each, 75.9 / 78.0.  The sums themselves add 24-bit
-// values and round next to nothing.
+// over 64 elements a lane (64 KiB tiles), 8.8e-16 over 256 (256 KiB).
+//
+// Chunks that are powers of two, and tiles that a caller asks for, have tiles
+// that are powers of two and plain chains.  Other chunks have larger tiles than
+// the power of two that divides them (100 KiB in place of 4), and folds make up
+// for it (FOLD, folded_tiles): the even and the odd elements have a chain each,
+// and after every kFoldBlocks blocks of the quarter, 8 elements a chain, their
+// sum goes into a compensated pair.  Error of chunks of 48, 100, 160, 500 and
+// 1000 KiB in tiles of the power of two 8.3e-17, 6.2e-17, 9.3e-17, 5.2e-17 and
+// 6.4e-17, in the larger tiles 1.6e-16, 2.9e-16, 5.4e-16, 8.6e-16 and 8.8e-16,
+// with folds 7.7e-17, 6.5e-17, 8.1e-17, 5.2e-17 and 5.9e-17 (folds after 16
+// blocks 2e-16; rounding the exact sum once 4e-17 to 6e-17).  That is 7 more fp64
+// instructions to 32, within the noise of a call: 3 GB in 1000 KiB chunks 448 /
+// 445 us, 805 MB in 96 KiB chunks 125.0 / 124.8, 403 MB in 33 KiB chunks, a wave
+// each, 82.9 / 84.0.  The sums themselves add 24-bit values and round next to
+// nothing.
 constexpr int kFoldBlocks = 4;
 
-template <int DT>
+template <int DT, bool FOLD>
 struct LaneSums {
     double s = 0.0, q = 0.0;
     __device__ __forceinline__ void add(double d, int) {
@@ -93,7 +101,7 @@ struct LaneSums {
     __device__ __forceinline__ double squares() { return q; }
 };
 template <>
-struct LaneSums<C3_F32> {
+struct LaneSums<C3_F32, true> {
     double s = 0.0, q[2] = {0.0, 0.0}, hi = 0.0, lo = 0.0;
     __device__ __forceinline__ void add(double d, int i) {
         s += d;
@@ -113,8 +121,8 @@ struct LaneSums<C3_F32> {
     }
 };
 
-template <int DT>
-__device__ inline void stats_fast(const u32x4 v, LaneSums<DT>& a, float& mf) {
+template <int DT, bool FOLD>
+__device__ inline void stats_fast(const u32x4 v, LaneSums<DT, FOLD>& a, float& mf) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
     if constexpr (DT == C3_F32) {
 #pragma unroll
@@ -151,8 +159,8 @@ __device__ inline uint32_t magnitude_bits(float mf) {
 // non-finite element counts as +0, which changes no sum (they start at +0,
 // so none is ever -0), and there are no branches: one lane redoes its column
 // of the tile while the wave waits.
-template <int DT>
-__device__ inline void stats_slow(const u32x4 v, LaneSums<DT>& a, uint32_t& mx, uint32_t& nan_c,
+template <int DT, bool FOLD>
+__device__ inline void stats_slow(const u32x4 v, LaneSums<DT, FOLD>& a, uint32_t& mx, uint32_t& nan_c,
                                   uint32_t& inf_c) {
     constexpr uint32_t inf_bits = DT == C3_F32 ? 0x7F800000u : DT == C3_BF16 ? 0x7F80u : 0x7C00u;
     constexpr int N = DT == C3_F32 ? 4 : 8;
@@ -203,7 +211,7 @@ struct LaneFold {
 // offset the lane's 16 bytes, so no load spends vector instructions on its
 // address.  Each block's beta is pinned in a scalar register, so every key
 // sum is one three-input add.
-template <int DT, int U, int NW>
+template <int DT, int U, int NW, bool FOLD>
 __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, uint32_t blk0,
                                              const LaneKeys& K, int wave, int lane) {
     constexpr int NQ = 4 / NW;
@@ -212,7 +220,7 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
     LaneFold<NQ> f;
     f.A = f.B = 0;
     f.mx = f.nan_c = f.inf_c = 0u;
-    LaneSums<DT> a[NQ];
+    LaneSums<DT, FOLD> a[NQ];
     float mf = 0.0f;
     const uint32_t off = (uint32_t)lane * 16u;
     const int nfull = (int)(len >> 10);
@@ -225,10 +233,10 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
         stats_fast<DT>(v, a[u % NQ], mf);
         // blocks and folds one after another: side by side their chains take
         // 128 registers and scratch where 97 do
-        if constexpr (DT == C3_F32 && NW == 4) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (DT == C3_F32 && FOLD && NW == 4) __builtin_amdgcn_sched_barrier(0);
         if (u / NQ % kFoldBlocks == kFoldBlocks - 1) {
             a[u % NQ].fold();
-            if constexpr (DT == C3_F32 && NW == 4) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (DT == C3_F32 && FOLD && NW == 4) __builtin_amdgcn_sched_barrier(0);
         }
     };
     for (; k + NW * (U - 1) < nfull; k += NW * U) {
@@ -284,7 +292,7 @@ __device__ inline LaneFold<4 / NW> fold_lane(const uint8_t* tile, uint32_t len, 
             // rare: this lane saw a NaN or Inf; redo its statistics classifying
             f.mx = 0u;
             for (int i = 0; i < NQ; ++i) {
-                LaneSums<DT> ai;
+                LaneSums<DT, FOLD> ai;
                 for (int kk = wave + i; kk < nfull; kk += 4 * kRedoLoads) {
                     u32x4 v[kRedoLoads];
 #pragma unroll

@@ -103,12 +103,10 @@ __device__ __forceinline__ void replay_quad(const AdamwConst& c, const OptBlock&
 
 // blocks: 1 KiB blocks (256 elements) per tile; partials [R][7][gridDim.x].
 // Every base is 16-byte aligned, offset and stride are multiples of 256.
-// LONG: tiles of more than 4 kFoldBlocks blocks, whose waves fold the sums of
-// squares on the way; up to there the chains hold them (LaneSums).  (224
-// registers, two waves a SIMD for three: 2 replicas x 524,288 elements 26.8 us
-// against 25.3 without folds, 8 x 262,144 23.1 against 22.5; the pairs in LDS
-// 28.6 and 23.7.)
-template <bool LONG>
+// FOLD: tiles of more than 4 kFoldBlocks blocks that do not divide the slice as
+// a power of two, whose sums of squares are folded on the way (LaneSums); 224
+// registers, two waves a SIMD for three.
+template <bool FOLD>
 __global__ void __launch_bounds__(kOptThreads) optimizer_slices_kernel(
     AdamwPtrs ptrs, AdamwConst c, int64_t offset, int64_t n, int blocks, float* __restrict__ out,
     int64_t stride, TilePartial* __restrict__ partials) {
@@ -126,7 +124,7 @@ __global__ void __launch_bounds__(kOptThreads) optimizer_slices_kernel(
     const LaneKeys K = lane_keys(lane);
 
     LaneFold<1> f[kOptSlices];
-    LaneSums<C3_F32> sums[kOptSlices];
+    LaneSums<C3_F32, FOLD> sums[kOptSlices];
     float mf[kOptSlices];
 #pragma unroll
     for (int t = 0; t < kOptSlices; ++t) {
@@ -146,13 +144,13 @@ __global__ void __launch_bounds__(kOptThreads) optimizer_slices_kernel(
     };
     // block k of the tile is block k / 4 of its quarter
     auto fold_sums = [&](int k) {
-        if (!LONG || (k >> 2) % kFoldBlocks != kFoldBlocks - 1) return;
+        if (!FOLD || (k >> 2) % kFoldBlocks != kFoldBlocks - 1) return;
 #pragma unroll
         for (int t = 0; t < kOptSlices; ++t) sums[t].fold();
     };
     auto take_sums = [&](int t) {
         f[t].s[0] = sums[t].s;
-        f[t].q[0] = LONG ? sums[t].squares() : sums[t].q[0] + sums[t].q[1];
+        f[t].q[0] = sums[t].squares();
     };
     // whole blocks without a test per lane; the slice's last one may be partial
     const int nwhole = (int)min((int64_t)nblk, n / 256 - blk0);
@@ -205,7 +203,7 @@ __global__ void __launch_bounds__(kOptThreads) optimizer_slices_kernel(
     if (!finite) {
 #pragma unroll
         for (int t = 0; t < kOptSlices; ++t) {
-            sums[t] = LaneSums<C3_F32>();
+            sums[t] = LaneSums<C3_F32, FOLD>();
             f[t].mx = 0u;
         }
         for (int k = wave; k < nblk; k += 4) {
@@ -294,7 +292,8 @@ hipError_t launch_optimizer_check(const AdamwPtrs& ptrs, const AdamwConst& c, in
     TilePartial* pp = static_cast<TilePartial*>(partials);
     if (nt > 0x7FFFFFFF) return hipErrorInvalidValue;
     const int blocks = (int)(tile_bytes / 1024);
-    hipLaunchKernelGGL(blocks > 4 * kFoldBlocks ? optimizer_slices_kernel<true> : optimizer_slices_kernel<false>,
+    const bool folds = blocks > 4 * kFoldBlocks && folded_tiles((uint64_t)stride * 4, tile_bytes);
+    hipLaunchKernelGGL(folds ? optimizer_slices_kernel<true> : optimizer_slices_kernel<false>,
                        dim3((unsigned)nt, (unsigned)R), dim3(kOptThreads), 0, stream, ptrs, c, offset, n,
                        blocks, updated, stride, pp);
     const hipError_t e = hipGetLastError();

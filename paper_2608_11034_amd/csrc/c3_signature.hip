@@ -166,17 +166,17 @@ __device__ inline TileSpan tile_span(uint64_t lt, uint32_t tpc, uint64_t chunk_b
 // fold_lane for a compile-time type, or (kMixed) the tensor's own
 constexpr int kMixed = -1;
 
-template <int DT, int U, int NW>
+template <int DT, int U, int NW, bool FOLD>
 __device__ inline LaneFold<4 / NW> fold_tile(int dtype, const uint8_t* tile, uint32_t len, uint32_t blk0,
                                      const LaneKeys& K, int wave, int lane) {
     if constexpr (DT != kMixed) {
-        return fold_lane<DT, U, NW>(tile, len, blk0, K, wave, lane);
+        return fold_lane<DT, U, NW, FOLD>(tile, len, blk0, K, wave, lane);
     } else {
         switch (__builtin_amdgcn_readfirstlane(dtype)) {
-            case C3_F32: return fold_lane<C3_F32, U, NW>(tile, len, blk0, K, wave, lane);
-            case C3_BF16: return fold_lane<C3_BF16, U, NW>(tile, len, blk0, K, wave, lane);
-            case C3_F16: return fold_lane<C3_F16, U, NW>(tile, len, blk0, K, wave, lane);
-            default: return fold_lane<C3_RAW, U, NW>(tile, len, blk0, K, wave, lane);
+            case C3_F32: return fold_lane<C3_F32, U, NW, FOLD>(tile, len, blk0, K, wave, lane);
+            case C3_BF16: return fold_lane<C3_BF16, U, NW, false>(tile, len, blk0, K, wave, lane);
+            case C3_F16: return fold_lane<C3_F16, U, NW, false>(tile, len, blk0, K, wave, lane);
+            default: return fold_lane<C3_RAW, U, NW, false>(tile, len, blk0, K, wave, lane);
         }
     }
 }
@@ -187,7 +187,7 @@ __device__ inline LaneFold<4 / NW> fold_tile(int dtype, const uint8_t* tile, uin
 // with DT = kMixed.
 //
 // One workgroup per tile.
-template <int DT, int U, typename P>
+template <int DT, int U, bool FOLD, typename P>
 __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
     signature_kernel(const P src, c3_chunk_record_t* __restrict__ records, int gk0, int gk1,
                      int64_t gtiles, int mapped, uint32_t* clear) {
@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
         const TileSpan ts = tile_span((uint64_t)lt, tpc, chunk_bytes, tile_bytes, pv.tinfo[t].nbytes);
         const uint8_t* tile = reinterpret_cast<const uint8_t*>(pv.ptrs[r * T + t]) + ts.off;
 
-        const LaneFold<1> f = fold_tile<DT, U, 4>(pv.tinfo[t].dtype, tile, ts.len, ts.blk0,
+        const LaneFold<1> f = fold_tile<DT, U, 4, FOLD>(pv.tinfo[t].dtype, tile, ts.len, ts.blk0,
                                                      K, wave, lane);
         const TilePartial wp = wave_reduce(f);
         if (lane == 0) lds[wave] = wp;
@@ -252,7 +252,7 @@ struct RunTile {
     uint32_t len;
 };
 
-template <int DT, int U, typename P>
+template <int DT, int U, bool FOLD, typename P>
 __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
     signature_wave_kernel(const P src, c3_chunk_record_t* __restrict__ records, int gk0, int gk1,
                           int64_t gtiles, int run, uint32_t* clear) {
@@ -289,7 +289,7 @@ __global__ void __launch_bounds__(kSigThreads, C3_SIG_WAVES_PER_EU)
                 tile_span((uint64_t)lt, tpc, chunk_bytes, tile_bytes, pv.tinfo[t].nbytes);
             const uint8_t* tile = reinterpret_cast<const uint8_t*>(pv.ptrs[r * T + t]) + ts.off;
             const LaneFold<4> f =
-                fold_tile<DT, U, 1>(pv.tinfo[t].dtype, tile, ts.len, ts.blk0, K, 0, lane);
+                fold_tile<DT, U, 1, FOLD>(pv.tinfo[t].dtype, tile, ts.len, ts.blk0, K, 0, lane);
             const TilePartial p = wave_reduce(f);
             if (lane == 0) done[wave][m] = RunTile{p, r, lt, t, ts.len};
         }
@@ -764,7 +764,7 @@ static bool wave_tiles(int dt, uint64_t tile_bytes, int64_t ntiles) {
     return dt != C3_F32 && tile_bytes <= kWaveTileMax && ntiles >= 8192;
 }
 
-template <int DT>
+template <int DT, bool FOLD>
 static hipError_t launch_group(const PlanSource& src, c3_chunk_record_t* records, int gk0, int gk1,
                                int64_t gtiles, int R, uint64_t tile_bytes, int grid_blocks,
                                uint32_t* clear, hipStream_t stream) {
@@ -783,7 +783,7 @@ static hipError_t launch_group(const PlanSource& src, c3_chunk_record_t* records
         if (grid > 0x7FFFFFFF) grid = 0x7FFFFFFF;
         with_plan(src, [&](const auto& p) {
             using P = std::decay_t<decltype(p)>;
-            hipLaunchKernelGGL((signature_wave_kernel<DT, kUnroll, P>), dim3((unsigned)grid),
+            hipLaunchKernelGGL((signature_wave_kernel<DT, kUnroll, FOLD, P>), dim3((unsigned)grid),
                                dim3(kSigThreads), 0, stream, p, records, gk0, gk1, gtiles, (int)run, clear);
         });
         return hipGetLastError();
@@ -795,7 +795,7 @@ static hipError_t launch_group(const PlanSource& src, c3_chunk_record_t* records
     if (grid > 0x7FFFFFFF) grid = 0x7FFFFFFF;
     with_plan(src, [&](const auto& p) {
         using P = std::decay_t<decltype(p)>;
-        hipLaunchKernelGGL((signature_kernel<DT, kUnroll, P>), dim3((unsigned)grid), dim3(kSigThreads),
+        hipLaunchKernelGGL((signature_kernel<DT, kUnroll, FOLD, P>), dim3((unsigned)grid), dim3(kSigThreads),
                            0, stream, p, records, gk0, gk1, gtiles, mapped, clear);
     });
     return hipGetLastError();
@@ -812,11 +812,12 @@ hipError_t launch_signature(const PlanSource& src, const SigPlan& hplan, const S
             only = d;
             ++types;
         }
-    auto launch = [&](auto dt) {
+    auto launch = [&](auto dt, auto fold) {
         constexpr int DT = decltype(dt)::value;
+        constexpr bool FOLD = decltype(fold)::value;
         const int gk0 = DT == kMixed ? 0 : groups.k0[only], gk1 = DT == kMixed ? hplan.T : groups.k1[only];
         const int64_t gt = DT == kMixed ? hplan.tiles_per_replica : groups.tiles[only];
-        return launch_group<DT>(src, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks,
+        return launch_group<DT, FOLD>(src, records, gk0, gk1, gt, hplan.R, hplan.tile_bytes, grid_blocks,
                                 clear, stream);
     };
     // several types in one launch: a launch for each drains the chip between
@@ -824,11 +825,17 @@ hipError_t launch_signature(const PlanSource& src, const SigPlan& hplan, const S
     // launch per type / one: 0.04 GB 33.1 / 16.1, 1.1 GB in 96 KiB tiles 203.9 /
     // 189.5, 8.6 GB in 128 KiB tiles 1,279 / 1,260, 4.3 and 17.2 GB in 256 KiB
     // tiles 634 / 618 and 2,418 / 2,414
-    if (types > 1) e = launch(std::integral_constant<int, kMixed>{});
-    else if (only == C3_F32) e = launch(std::integral_constant<int, C3_F32>{});
-    else if (only == C3_BF16) e = launch(std::integral_constant<int, C3_BF16>{});
-    else if (only == C3_F16) e = launch(std::integral_constant<int, C3_F16>{});
-    else e = launch(std::integral_constant<int, C3_RAW>{});
+    using std::integral_constant;
+    const bool f = hplan.folds != 0;           // of fp32 tensors only
+    if (types > 1)
+        e = f ? launch(integral_constant<int, kMixed>{}, std::true_type{})
+              : launch(integral_constant<int, kMixed>{}, std::false_type{});
+    else if (only == C3_F32)
+        e = f ? launch(integral_constant<int, C3_F32>{}, std::true_type{})
+              : launch(integral_constant<int, C3_F32>{}, std::false_type{});
+    else if (only == C3_BF16) e = launch(integral_constant<int, C3_BF16>{}, std::false_type{});
+    else if (only == C3_F16) e = launch(integral_constant<int, C3_F16>{}, std::false_type{});
+    else e = launch(integral_constant<int, C3_RAW>{}, std::false_type{});
     if (e != hipSuccess) return e;
     if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
     if (!hplan.direct && finalize) {

@@ -23,6 +23,7 @@ struct SigPlan {
                                 // of them shorter where the size does not divide the chunk
     uint32_t tiles_per_chunk;
     uint32_t direct;            // 1: one tile per chunk, tiles write records
+    uint32_t folds;             // folded_tiles(chunk_bytes, tile_bytes); read on the host
     // byte offsets (from the SigPlan base) of the arrays below
     uint64_t off_ptrs;          // u64  [R*T] replica-major tensor base addresses
     uint64_t off_tile_base;     // i64  [T+1] first tile of each tensor
@@ -34,6 +35,12 @@ struct SigPlan {
     uint64_t off_partials;      // TilePartial [R * tiles_per_replica]
     uint64_t total_bytes;
 };
+
+// Whether the sums of squares of fp32 tiles are folded on the way (LaneSums):
+// tiles other than a power of two that divides the chunk.
+inline bool folded_tiles(uint64_t chunk_bytes, uint64_t tile_bytes) {
+    return (tile_bytes & (tile_bytes - 1)) != 0 || chunk_bytes % tile_bytes != 0;
+}
 
 struct TensorInfo {
     uint64_t nbytes;
