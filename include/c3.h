@@ -182,7 +182,7 @@ typedef struct {
  *     for that promise: a stale plan reads stale pointers.
  *   tile_bytes: bytes folded into one partial; 0 chooses the default (the
  *     chunk in as few equal tiles of at most 256 KiB as it takes, whole KiB
- *     each).  Any other value must be a power-of-two multiple of 1024
+ *     each; 128 KiB for odd multiples of 128 KiB from 384 on).  Any other value must be a power-of-two multiple of 1024
  *     dividing chunk_bytes (checked); the fp64 sums may differ in the last
  *     bits between tile sizes, everything else is identical. */
 typedef struct {

@@ -67,9 +67,15 @@ constexpr uint64_t kTileMax = 1ull << 24;
 
 // Default tile: the chunk in as few equal tiles of at most kDefaultTileMax
 // as it takes, rounded up to whole KiB (the chunk's last tile is shorter
-// where they do not divide it).  A power of two dividing the chunk, the rule
-// before, gave a chunk of 100 KiB tiles of 4 KiB.
+// where they do not divide it), or half kDefaultTileMax where that divides a
+// larger chunk and the whole does not.  us per check, 12.9 GB of bf16, largest
+// power of two that divides the chunk / equal tiles: 192 KiB (64 / 192 KiB tiles)
+// 1,910 / 1,842, 320 KiB (64 / 160) 1,916 / 1,834, 1000 KiB (8 / 250) 7,314 /
+// 1,847, but 384 KiB (128 / 192) 1,812 / 1,844, 640 KiB (128 / 214) 1,807 / 1,844,
+// 896 KiB (128 / 224) 1,812 / 1,857; fp32 and raw bytes alike.
 uint64_t default_tile(uint64_t chunk_bytes) {
+    const uint64_t half = c3::kDefaultTileMax / 2;
+    if (chunk_bytes > c3::kDefaultTileMax && chunk_bytes % c3::kDefaultTileMax == half) return half;
     const uint64_t n = (chunk_bytes + c3::kDefaultTileMax - 1) / c3::kDefaultTileMax;
     return align_up((chunk_bytes + n - 1) / n, 1024);
 }

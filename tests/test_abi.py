@@ -331,3 +331,19 @@ def test_optimizer_check_default_tiles():
         st = c3.OptimizerState(p, p, p, p, R, 0, 1 << 24, kib * 256, 0)
         need = -(-R * 7 * 64 * tiles // 256) * 256
         assert L.c3_optimizer_check_workspace_size(ctypes.byref(st)) == need, (R, kib)
+
+
+def test_default_signature_tiles():
+    """Equal whole-KiB tiles of at most 256 KiB, and 128 KiB for larger chunks
+    that are odd multiples of it: the workspaces are those of that many
+    partials of 64 bytes a replica, none where a chunk is one tile."""
+    L = c3.lib()
+    meta = (c3.TensorMeta * 1)()
+    meta[0].dtype, meta[0].ndim = c3.RAW, 1
+    for kib, tiles in ((1, 1), (100, 1), (128, 1), (192, 1), (256, 1), (257, 2), (320, 2), (384, 3),
+                       (512, 2), (640, 5), (768, 3), (896, 7), (1000, 4), (1152, 9), (1280, 5),
+                       (4096, 16), (4224, 33)):
+        meta[0].shape[0] = kib * 1024 * 64                 # 64 chunks
+        one = L.c3_signature_workspace_size(meta, 1, 1, kib * 1024)
+        two = L.c3_signature_workspace_size(meta, 1, 3, kib * 1024)
+        assert two - one == (2 * 64 * tiles * 64 if tiles > 1 else 0), kib
