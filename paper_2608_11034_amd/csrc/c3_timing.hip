@@ -731,7 +731,8 @@ static hipError_t launch_pass(const char* fp, const char* tp, int64_t G, int64_t
     const dim3 block(PassShape<NMAX>::threads);
     int pu = (fo.status != nullptr ? 1 : 0) | (to.status != nullptr ? 2 : 0);
     constexpr int rsize = NMAX * (KIND == C3_EV_F64 ? 16 : 12);
-    if (pu != 0 && Wt <= 32 && G % kPassGroups == 0 && T * G * (rsize + 26) > kPassStreamBytes &&
+    const int usize = rsize + 13 * __builtin_popcount((unsigned)pu);     // read, and results written
+    if (pu != 0 && Wt <= 32 && G % kPassGroups == 0 && T * G * usize > kPassStreamBytes &&
         (((uintptr_t)fo.bitmap | (uintptr_t)to.bitmap) & 127) == 0)
         pu |= 4;
 #define C3_PASS(S, P)                                                                     \

@@ -20,7 +20,7 @@ def test_short_pass(R, G, T, W, f64, per_unit):
     _check(fp, tau, W, per_unit=per_unit)
 
 
-@pytest.mark.parametrize("R,G,T,f64", [(4, 4096, 900, False), (8, 4096, 600, False), (16, 4096, 200, True),
+@pytest.mark.parametrize("R,G,T,f64", [(4, 4096, 900, False), (8, 4096, 600, False), (16, 4096, 240, True),
                                        (8, 4112, 600, False)])
 def test_streamed_bitmaps(R, G, T, f64):
     """Passes of over 256 MB, whose bitmaps go past the caches, against the
@@ -40,4 +40,31 @@ def test_streamed_bitmaps(R, G, T, f64):
     for got, ev, mode in ((fu, fp, c3.EXACT), (tu, tau, c3.STATISTICAL)):
         for a, b in zip(got, c3.consensus(ev, mode)):
             assert torch.equal(a, b)
+    assert torch.equal(ver, c3.confirm(fu[1].view(T, G), tu[1].view(T, G), R, 16))
+
+
+@pytest.mark.parametrize("R,G,T,f64", [(4, 4096, 1088, False), (8, 4096, 640, False), (8, 4096, 480, True),
+                                       (16, 4096, 336, False), (16, 4096, 256, True)])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_streamed_bitmaps_of_one_kind(kind, R, G, T, f64):
+    """The same with the per-unit results of one kind only."""
+    import torch
+    from paper_2608_11034_amd import c3
+    _case("timing streamed, one kind", kind, R, G, T, f64)
+    assert T * G * (R * (16 if f64 else 12) + 13) > 256 << 20
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(R + T)
+    fp = torch.randint(-2**63, 2**63 - 1, (T, G, 1), generator=gen, device="cuda").expand(T, G, R).contiguous()
+    fp[T // 3:, 5, R - 1] ^= 77
+    tau = torch.randn((T, G, R), generator=gen, device="cuda").mul_(0.02).exp_()
+    tau[:, G - 1, 1] *= 1.5
+    if f64:
+        tau = tau.double()
+    fu, tu = c3.consensus(fp, c3.EXACT), c3.consensus(tau, c3.STATISTICAL)
+    want = (fu, tu)[kind]
+    got = tuple(torch.full_like(x, 99) for x in want)
+    ver = torch.empty((R * G, 24), dtype=torch.uint8, device="cuda")
+    c3.timing_consensus(fp, tau, out=(ver, got, None) if kind == 0 else (ver, None, got))
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
     assert torch.equal(ver, c3.confirm(fu[1].view(T, G), tu[1].view(T, G), R, 16))
