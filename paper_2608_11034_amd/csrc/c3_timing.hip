@@ -770,6 +770,13 @@ static hipError_t launch_pass(const char* fp, const char* tp, int64_t G, int64_t
 //   R = 8, 64 groups   T = 16: 8.3 / 4.0    64: 9.4 / 5.7    256: 8.9 / 13.0   1024: 11.4 / 41.6
 //   R = 8, 2,048       T = 16: 8.5 / 4.2    64: 10.0 / 6.1   256: 15.4 / 13.8  1024: 45.3 / 42.8
 //   R = 16, 64 groups  T = 16: 9.5 / 4.8    64: 10.4 / 8.0   256: 9.9 / 20.8   1024: 11.9 / 69.3
+// The line is where every form gains, whoever waits for the call: up to R T =
+// 512 the pass takes 60 to 70% of three launches back to back from the host (R =
+// 4, 8, 16, 16 to 4,000 groups).  Between 768 and 2,048 fp32 verdicts still gain, but
+// fp64 with per-unit results does not: back to back from the host, which hides
+// 3 us of three launches, R = 8, T = 192: 12.6 / 11.0 fp32, 13.1 / 13.6; R = 16,
+// T = 64, 2,048 groups: 13.2 / 9.9, 14.0 / 14.9; R = 16, T = 128, 64 groups: 12.3 /
+// 12.8, 13.1 / 18.9; R = 8, T = 256, 2,048 groups: 15.6 / 13.3, 20.4 / 20.3.
 constexpr int64_t kPassShortRows = 512;          // R * T of a short walk
 
 static bool pass_applies(const void* fp, const void* times, int time_kind, int R, int64_t G,
