@@ -287,7 +287,7 @@ class SignaturePlan:
         self.metas = make_metas(replicas[0])
         self.C = num_chunks(replicas[0], chunk_bytes)
         self.ws_bytes = signature_workspace_size(replicas[0], self.R, chunk_bytes, tile_bytes)
-        # launch options of a call without any, which the library only reads
+        # launch options of a call with none but the tile, which the library only reads
         self._plain = LaunchOpts(None, None, 0, 0, self.tile_bytes)
         self._plain_ref = ctypes.byref(self._plain)
 
@@ -299,6 +299,7 @@ class SignaturePlan:
 
     def _opts(self, ev_begin, ev_end, grid_blocks, plan_staged):
         if ev_begin is None and ev_end is None and not grid_blocks and not plan_staged:
+            self._plain.tile_bytes = self.tile_bytes
             return self._plain_ref
         return ctypes.byref(LaunchOpts(ev_begin.cuda_event if ev_begin is not None else None,
                                        ev_end.cuda_event if ev_end is not None else None,

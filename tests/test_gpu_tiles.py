@@ -243,3 +243,23 @@ def test_optimizer_records_are_signatures(tile_kib, n):
               for r in range(2)]
     torch.cuda.synchronize()
     assert torch.equal(rec.view(-1, 64), _sign(slices, 262144, tile_kib * KIB).view(-1, 64))
+
+
+# the tile that a plan object names at the call is the one that is taken
+def test_plan_tile_set_later():
+    print("CASE tile set later", flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    x = torch.randn(5000, generator=gen, device=DEV)
+    plan = c3.SignaturePlan([[x], [x]], 4 * KIB, KIB)
+    rec, ws = plan.new_records(), plan.new_workspace()
+    plan.tile_bytes = 2 * KIB
+    plan.run(rec, ws)
+    assert torch.equal(rec, _sign([[x], [x]], 4 * KIB, 2 * KIB))
+    outs = plan.new_check_outputs()
+    check_ws = torch.empty(plan.check_workspace_size(), dtype=torch.uint8, device=DEV)
+    plan.tile_bytes = 3000
+    with pytest.raises(c3.C3Error):
+        plan.run(rec, ws)
+    with pytest.raises(c3.C3Error):
+        plan.run_check(outs, check_ws)
