@@ -713,9 +713,16 @@ int c3_optimizer_check(const c3_optimizer_state_t* st, int64_t k, const c3_adamw
 // ---------------------------------------------------------------------------
 static bool timing_fused(int R, int window) { return R <= 16 && window <= 64; }
 
+// Both votes of groups above 16 in one launch, which writes no status and no
+// majority that the caller has not asked for.
+static bool timing_wide(int R, uint64_t n_units) {
+    return R > 16 && n_units <= (uint64_t)c3::kGroupMaxUnits;
+}
+
 static uint64_t timing_fallback_bytes(int R, int64_t G, int64_t T) {
     const uint64_t n = (uint64_t)T * (uint64_t)G;
-    const uint64_t one = align_up(n, 256) + align_up(8 * n, 256) + align_up(4 * n, 256);
+    const uint64_t one = align_up(8 * n, 256) +
+                         (timing_wide(R, n) ? 0 : align_up(n, 256) + align_up(4 * n, 256));
     return 2 * one + align_up(c3::confirm_ws_bytes(R, G, T), 256);
 }
 
@@ -767,27 +774,30 @@ int c3_timing_consensus(const uint64_t* fingerprints, const void* times, int tim
         w += align_up(bytes, 256);
         return p;
     };
-    uint8_t* fs = reinterpret_cast<uint8_t*>(carve(n));
+    const bool wide = timing_wide(R, n);
     uint64_t* fb = reinterpret_cast<uint64_t*>(carve(8 * n));
-    int32_t* fm = reinterpret_cast<int32_t*>(carve(4 * n));
-    uint8_t* ts = reinterpret_cast<uint8_t*>(carve(n));
     uint64_t* tb = reinterpret_cast<uint64_t*>(carve(8 * n));
-    int32_t* tm = reinterpret_cast<int32_t*>(carve(4 * n));
+    uint8_t *fs = fp_status, *ts = t_status;
+    int32_t *fm = fp_majority, *tm = t_majority;
+    if (!wide) {
+        uint8_t* const s2[2] = {carve(n), carve(n)};
+        unsigned char* const m2[2] = {carve(4 * n), carve(4 * n)};
+        if (!fp_out) {
+            fs = s2[0];
+            fm = reinterpret_cast<int32_t*>(m2[0]);
+        }
+        if (!t_out) {
+            ts = s2[1];
+            tm = reinterpret_cast<int32_t*>(m2[1]);
+        }
+    }
     void* cws = carve(0);
-    if (fp_out) {
-        fs = fp_status;
-        fb = fp_bitmap;
-        fm = fp_majority;
-    }
-    if (t_out) {
-        ts = t_status;
-        tb = t_bitmap;
-        tm = t_majority;
-    }
+    if (fp_out) fb = fp_bitmap;
+    if (t_out) tb = t_bitmap;
     hipError_t e;
-    if (R > 16 && (int64_t)n <= c3::kGroupMaxUnits) {
+    if (wide) {
         e = c3::launch_timing_votes_wide(fingerprints, times, time_kind, R, (int64_t)n, kappa,
-                                         fp_status, fb, fp_majority, t_status, tb, t_majority, s);
+                                         fs, fb, fm, ts, tb, tm, s);
     } else {
         e = c3::launch_consensus(fingerprints, C3_EV_U64, 8, 8 * (int64_t)R, R, (int64_t)n, C3_EXACT,
                                  kappa, fs, fb, fm, s);

@@ -347,3 +347,20 @@ def test_default_signature_tiles():
         one = L.c3_signature_workspace_size(meta, 1, 1, kib * 1024)
         two = L.c3_signature_workspace_size(meta, 1, 3, kib * 1024)
         assert two - one == (2 * 64 * tiles * 64 if tiles > 1 else 0), kib
+
+
+def test_timing_workspace_of_wide_groups():
+    """Bitmaps of both kinds and the confirmation's workspace; status and
+    majority of both kinds too where the votes are separate launches."""
+    L = c3.lib()
+
+    def up(n):
+        return -(-n // 256) * 256
+    for R, G, T, W in ((17, 1, 1, 16), (20, 10, 30, 16), (64, 128, 511, 70), (33, 7, 100, 16)):
+        n = G * T
+        want = 2 * up(8 * n) + up(L.c3_confirm_workspace_size(R, G, T))
+        assert L.c3_timing_consensus_workspace_size(R, G, T, W) == want
+    for R, G, T, W in ((8, 10, 100, 70), (17, 16, (1 << 24) + 1, 16)):
+        n = G * T
+        want = 2 * (up(n) + up(8 * n) + up(4 * n)) + up(L.c3_confirm_workspace_size(R, G, T))
+        assert L.c3_timing_consensus_workspace_size(R, G, T, W) == want
