@@ -262,7 +262,8 @@ class SignaturePlan:
     """Host-side marshalling of one replica set: pointer table and metadata.
 
     Building it once and calling ``run`` repeatedly only avoids re-marshalling
-    in Python; the library still stages the plan on every call.
+    in Python; the library still checks the plan on every call and passes it to
+    the kernels or stages it.
     """
 
     def __init__(self, replicas, chunk_bytes: int, tile_bytes: int = 0):

@@ -34,10 +34,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // A replay that moves more than the 256 MB memory-side cache holds streams
 // past the caches: the inputs are read once and the updates not read by this
-// kernel.  2 replicas x 16.8M elements (940 MB), us: plain 181.2, non-temporal
-// loads 174.2, loads and stores 163.7 (5.7 TB/s); two quads a thread 161.5
-// against 156.1 for one.  Smaller replays keep their updates cached for the
-// signature that follows.
+// kernel.  us per call, plain / non-temporal loads / loads and stores: 2 replicas
+// x 16.8M elements (940 MB) 178.7 / 172.5 / 160.3, on three sets of buffers in
+// turn 172 / 169 / 163; 8 x 4.0M 163.4 / 159.2 / 146.9; 2 x 6.0M (336 MB) 61.3 / 58.9
+// / 54.3.  (Two quads a thread were 3% slower than one.)  Smaller replays keep
+// their updates cached for the signature that follows.
 constexpr int64_t kStreamBytes = 256 << 20;
 
 template <bool NT>

@@ -177,9 +177,10 @@ inline bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)
 // stream.  A slot is reused only after the kernel that read it has
 // completed: the plan fetch kernel stores the slot's sequence number into a
 // pinned coherent word when it is done, which costs nothing on the stream
-// (an event recorded per call idled the GPU about 6 us per call).  A plan larger than a slot (256 KB, about 1,500 tensors at
-// R = 8) falls back to a pageable copy.  The buffer
-// holds whole 16-byte words, so the staged size is rounded up to 16.
+// (an event recorded per call idled the GPU about 6 us per call).  A plan larger
+// than a slot (256 KB, about 1,500 tensors at R = 8) falls back to a pageable
+// copy.  The buffer holds whole 16-byte words, so the staged size is rounded up
+// to 16.
 // ---------------------------------------------------------------------------
 constexpr int kStageSlots = 16;
 constexpr size_t kStageSlotBytes = 256 * 1024;

@@ -53,7 +53,7 @@ __device__ inline void comp_add(double& s, double& c, double s2, double c2) {
 }
 
 // ---------------------------------------------------------------------------
-// wave64 cross-lane helpers (xor butterflies through ds_bpermute / DPP)
+// wave64 cross-lane helpers (ds_bpermute, DPP and lane swaps)
 // ---------------------------------------------------------------------------
 __device__ inline uint32_t shfl_xor_u32(uint32_t v, int m) {
     return (uint32_t)__shfl_xor((int)v, m, 64);
@@ -62,16 +62,10 @@ __device__ inline uint64_t shfl_xor_u64(uint64_t v, int m) {
     uint32_t lo = shfl_xor_u32((uint32_t)v, m), hi = shfl_xor_u32((uint32_t)(v >> 32), m);
     return ((uint64_t)hi << 32) | lo;
 }
-__device__ inline double shfl_xor_f64(double v, int m) {
-    return __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(v), m));
-}
 __device__ inline uint64_t shfl_u64(uint64_t v, int src) {
     uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, src, 64);
     uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(v >> 32), src, 64);
     return ((uint64_t)hi << 32) | lo;
-}
-__device__ inline double shfl_f64(double v, int src) {
-    return __longlong_as_double((long long)shfl_u64((uint64_t)__double_as_longlong(v), src));
 }
 
 __device__ inline uint64_t ballot64(bool p) { return __ballot(p); }

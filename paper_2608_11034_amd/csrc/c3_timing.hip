@@ -431,8 +431,8 @@ __global__ void __launch_bounds__(kConfirmThreads) timing_confirm_kernel(
 // iterations (pass_applies).
 // Per-unit results are written as 16- to 128-byte pieces of each
 // iteration's row; on the 32,768-rank workload the pass with those of both
-// kinds takes 91.2 us of kernel time against 106.2 us for the three
-// launches of the workspace path (clear, votes, confirmation).
+// kinds takes 91.2 us of kernel time through the caches against 106.2 us for
+// the three launches of the workspace path (clear, votes, confirmation).
 // ---------------------------------------------------------------------------
 constexpr int kPassGroups = 16;                  // groups per workgroup
 constexpr int kPassIters = 64 / kPassGroups;     // iterations per wave step

@@ -2,8 +2,9 @@
 
 The paper's table of published configurations lists data-parallel peer
 degrees up to 192 (Table 2).  Above 64 replicas a unit's outlier bitmap is
-ceil(R / 64) words; c3_consensus decides one unit per wave (exact votes from
-17 replicas, statistical ones from 33) and c3_localize walks every word.
+ceil(R / 64) words; from 33 replicas on c3_consensus takes a wave per unit for
+exact votes and sixteen lanes per unit for statistical ones (in fp64 from 17),
+and c3_localize walks every word.
 Checked element by element: status, every bitmap word, majority index, and
 the outlier and undecided lists (single-workgroup and multi-pass
 localization, with and without truncation).
@@ -100,9 +101,10 @@ def test_exact_consensus_wide_matches_oracle(R):
 @pytest.mark.parametrize("R", [17, 20, 31, 32, 33, 48, 64, 65, 97, 128, 129, 192, 255, 256])
 @pytest.mark.parametrize("dt", [np.float32, np.float64])
 def test_statistical_consensus_wide_matches_oracle(R, dt):
-    """R = 17-32 takes the 32-slot thread-per-unit kernel (padding slots
-    past R, so the sort runs over the finite values and +inf), every R above
-    32 the wave kernel: one sort of the finite values."""
+    """R = 17-32 in fp32 takes the 32-slot thread-per-unit kernel (padding
+    slots past R, so the sort runs over the finite values and +inf), fp64 from
+    17 and every R above 32 sixteen lanes per unit: one sort of the finite
+    values."""
     _case("statistical wide", R, dt)
     rng = np.random.default_rng(1000 + R)
     U = 1201
