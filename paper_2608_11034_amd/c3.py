@@ -282,15 +282,23 @@ class SignaturePlan:
                 if x.dtype != ref.dtype or x.shape != ref.shape:
                     raise C3Error(f"tensor {t} differs in dtype or shape between replicas")
         self.R, self.T, self.device = len(replicas), T, dev
-        self.chunk_bytes, self.tile_bytes = int(chunk_bytes), int(tile_bytes)
+        self.chunk_bytes = int(chunk_bytes)
+        # launch options of a call with none but the tile, which the library only reads
+        self._plain = LaunchOpts(None, None, 0, 0, int(tile_bytes))
+        self._plain_ref = ctypes.byref(self._plain)
         self.keep = [x for rep in replicas for x in rep]
         self.ptrs = (ctypes.c_void_p * (self.R * T))(*[x.data_ptr() for x in self.keep])
         self.metas = make_metas(replicas[0])
         self.C = num_chunks(replicas[0], chunk_bytes)
         self.ws_bytes = signature_workspace_size(replicas[0], self.R, chunk_bytes, tile_bytes)
-        # launch options of a call with none but the tile, which the library only reads
-        self._plain = LaunchOpts(None, None, 0, 0, self.tile_bytes)
-        self._plain_ref = ctypes.byref(self._plain)
+
+    @property
+    def tile_bytes(self) -> int:
+        return self._plain.tile_bytes
+
+    @tile_bytes.setter
+    def tile_bytes(self, n: int):
+        self._plain.tile_bytes = int(n)
 
     def new_records(self):
         return _empty((self.R, self.C, 64), torch.uint8, self.device)
@@ -300,7 +308,6 @@ class SignaturePlan:
 
     def _opts(self, ev_begin, ev_end, grid_blocks, plan_staged):
         if ev_begin is None and ev_end is None and not grid_blocks and not plan_staged:
-            self._plain.tile_bytes = self.tile_bytes
             return self._plain_ref
         return ctypes.byref(LaunchOpts(ev_begin.cuda_event if ev_begin is not None else None,
                                        ev_end.cuda_event if ev_end is not None else None,
