@@ -20,8 +20,8 @@
  *     a 4 MiB ring of pinned host memory per device (allocated on first
  *     use, kept until the process ends) through which c3_signature and
  *     c3_check stage plans that do not go along as a kernel's argument
- *     (over 3.5 KB, or for many tiles), so that staging never makes the host wait
- *     for the GPU, and the fixed scratch array of c3_localize_noalloc.
+ *     (over 3.5 KB, or for many tiles), so that staging never makes the host
+ *     wait for the GPU, and the fixed scratch array of c3_localize_noalloc.
  *   - Host arrays passed in (pointer tables, tensor metadata) are consumed
  *     before the call returns; the caller may free them immediately.
  *   - Every call enqueues work on `stream` and returns without waiting; its
@@ -182,9 +182,10 @@ typedef struct {
  *     for that promise: a stale plan reads stale pointers.
  *   tile_bytes: bytes folded into one partial; 0 chooses the default (the
  *     chunk in as few equal tiles of at most 256 KiB as it takes, whole KiB
- *     each; 128 KiB for odd multiples of 128 KiB from 384 on).  Any other value must be a power-of-two multiple of 1024
- *     dividing chunk_bytes (checked); the fp64 sums may differ in the last
- *     bits between tile sizes, everything else is identical. */
+ *     each; 128 KiB for odd multiples of 128 KiB from 384 on).  Any other
+ *     value must be a power-of-two multiple of 1024 dividing chunk_bytes
+ *     (checked); the fp64 sums may differ in the last bits between tile
+ *     sizes, everything else is identical. */
 typedef struct {
     c3_event_t ev_kernel_begin;
     c3_event_t ev_kernel_end;
@@ -377,7 +378,8 @@ size_t c3_optimizer_check_workspace_size(const c3_optimizer_state_t *st);
  *      four input slices, read in place, and the three updated slices),
  *      one chunk each;
  *   3. c3_consensus (exact) over the seven units; 4. c3_localize.
- * The outputs are those of these four calls (the signature with this tile).
+ * The outputs are those of these four calls (the signature with this tile;
+ * fp64 sums in the last bits apart for a default tile that does not divide S).
  * Two launches: one replays and signs in a single pass over the inputs, and
  * one workgroup combines the tile partials into the records, votes and writes
  * the lists.

@@ -386,19 +386,26 @@ int adamw_prepare(const float* const* param, const float* const* grad,
 // (without the chunk-to-tensor table, which they then search for), else staged
 // into the workspace on the stream unless the caller says that it is there.
 // An argument saves a launch and costs at every look-up, which goes through the
-// scalar cache then, the more the larger the plan.  us per check, staged / as
-// an argument, bf16, 8 replicas of 3 tensors and 2 of 1 (fp32 alike):
-//   tiles                2,048        4,096        8,192        12,288        35,000        65,000
-//   256 KiB  8 x 3   95.8 / 92.8     170 / 168    320 / 321    466 / 466   1,298 / 1,309 2,479 / 2,509
-//            2 x 1   97.7 / 93.7     174 / 170    328 / 324    485 / 481   1,353 / 1,349 2,486 / 2,487
-//   128 KiB  8 x 3   54.3 / 51.3    91.0 / 89.6   165 / 165    245 / 250     675 / 701   1,246 / 1,293
-//            2 x 1   53.0 / 49.6    92.4 / 89.6   169 / 170    247 / 250     675 / 691   1,239 / 1,274
-// The 3 GB fp32 shard, 11,444 tiles of 256 KiB, 430.9 / 427.9.
-constexpr int64_t kArgPlanMaxTiles = 8192, kArgPlanMaxLargeTiles = 16384;   // under 256 KiB, others
+// scalar cache then: little where there is one tensor, more where a tile's has
+// to be found.  us per signature, bf16, staged / as an argument:
+//   tiles of 256 KiB       8,192       16,384       24,576         35,000          65,000
+//   2 replicas of 1    312 / 307    609 / 604    908 / 905   1,285 / 1,288   2,372 / 2,378
+//   32 of 1            312 / 308    610 / 605    907 / 906   1,289 / 1,290   2,375 / 2,390
+//   2 of 2             312 / 311    608 / 610    905 / 911   1,281 / 1,298   2,367 / 2,398
+//   8 of 3             314 / 314    610 / 613    906 / 913   1,284 / 1,295   2,363 / 2,397
+//   3 of 6             313 / 313    609 / 615    908 / 912   1,279 / 1,294   2,362 / 2,392
+// and per check in tiles of 128 KiB, 2 of 1 and 8 of 3: 4,096 tiles 92.4 / 89.6 and
+// 91.0 / 89.6, 8,192 even, 12,288 247 / 250 and 245 / 250, 65,000 1,239 / 1,274 and
+// 1,246 / 1,293 (fp32 alike).  The 3 GB fp32 shard, 11,444 tiles of 256 KiB in 3
+// tensors, 430.9 / 427.9.
+constexpr int64_t kArgPlanMaxTiles = 8192;          // under 256 KiB
+constexpr int64_t kArgPlanMaxLarge = 12288;         // of 256 KiB
+constexpr int64_t kArgPlanMaxLargeOne = 32768;      // of 256 KiB, of one tensor
 
 hipError_t place_plan(void* ws, const Plan& p, const std::vector<unsigned char>& buf, bool staged,
                       hipStream_t s, c3::PlanSource& src) {
-    const int64_t most = p.h.tile_bytes >= c3::kDefaultTileMax ? kArgPlanMaxLargeTiles : kArgPlanMaxTiles;
+    const int64_t most = p.h.tile_bytes < c3::kDefaultTileMax ? kArgPlanMaxTiles
+                         : p.h.T > 1 ? kArgPlanMaxLarge : kArgPlanMaxLargeOne;
     if (p.h.off_chunk_tensor <= c3::kArgPlanBytes && p.h.tiles_per_replica * p.h.R <= most) {
         src = {ws, buf.data(), (size_t)p.h.off_chunk_tensor};
         return hipSuccess;

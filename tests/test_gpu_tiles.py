@@ -140,7 +140,7 @@ def test_partials_combined_alike(tiles, R, chunks):
 
 
 # the plan as a kernel argument (up to 3.5 KB of it, and 8,192 tiles under 256
-# KiB or 16,384 others) and staged in the workspace; a second call that says its plan is still
+# KiB) and staged in the workspace; a second call that says its plan is still
 # there reads the tensors as they are then
 @pytest.mark.parametrize("R,T,n", [(2, 1, 5000), (2, 9, 900), (2, 10, 900), (2, 11, 900), (2, 12, 900),
                                    (32, 5, 300), (64, 3, 300), (64, 4, 300), (2, 2, 1024 * 1024 // 4 * 2),
@@ -172,17 +172,17 @@ def test_plan_argument_and_staged(R, T, n):
         assert torch.equal(rec, first)
 
 
-# 256 KiB tiles up to and past the number that still takes the plan as an
-# argument: one tensor on 64 replicas and alone
-@pytest.mark.parametrize("tiles", [256, 257])
-def test_plan_argument_large_tiles(tiles):
-    print("CASE plan, large tiles", tiles, flush=True)
+# 256 KiB tiles up to and past the numbers that still take the plan as an
+# argument, of one tensor and of two: on 64 replicas and alone
+@pytest.mark.parametrize("T,tiles", [(1, 512), (1, 513), (2, 96), (2, 97)])
+def test_plan_argument_large_tiles(T, tiles):
+    print("CASE plan, large tiles", T, tiles, flush=True)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(tiles)
-    x = torch.randn(tiles * 65536 - 5, generator=gen, device=DEV)
-    alone = _sign([[x]], 1024 * KIB)
-    assert torch.equal(_sign([[x]] * 64, 1024 * KIB), alone.expand(64, *alone.shape[1:]))
-    compare_all_records(c3.records_numpy(alone), _oracle([[x]], 1024 * KIB))
+    rep = [torch.randn(tiles * 65536 - 5 - t, generator=gen, device=DEV) for t in range(T)]
+    alone = _sign([rep], 1024 * KIB)
+    assert torch.equal(_sign([rep] * 64, 1024 * KIB), alone.expand(64, *alone.shape[1:]))
+    compare_all_records(c3.records_numpy(alone), _oracle([rep], 1024 * KIB))
 
 
 # sums of squares of fp32 chunks that are no power of two, whose tiles are
